@@ -66,8 +66,8 @@ enum mp3_status {
                              MP3_KF_CHECK_FINITE) in the catalogue or delta       */
 };
 
-/* MP3_F32_BF16X3 is MP3_F32 whose contractions on the matrix cores (nodal,
- * grid-Gamma and particle forms with at most 32 bins) take BF16-split inputs:
+/* MP3_F32_BF16X3 is MP3_F32 whose contractions on the matrix cores (nodal
+ * and particle forms with at most 32 bins) may take BF16-split inputs:
  * each float32 operand x is carried as hi = bf16(x), lo = bf16(x - hi) and each
  * product as hi*hi + hi*lo + lo*hi, accumulated in float32 (relative error of
  * about 2^-16 per product against 2^-24).  Everything else is as MP3_F32. */
@@ -196,8 +196,7 @@ int mp3_multipole_fields(mp3_plan_t plan, const void* delta, int32_t l, int32_t 
  *   zeta_l[b1,b2] = (4 pi / N^3) sum_x delta_x sum_m sum_{s,t} Gamma_{s,t}
  *                   a_{lm,b1}(x+s) conj(a_{lm,b2}(x+t)),
  *   Gamma_{s,t} = prod_d int B3(u) B3(u - s_d) B3(u - t_d) du, evaluated exactly
- *   as the integral of the three B-spline interpolants (5-point Gauss-Legendre
- *   per cell and axis).  pos, w, np_off ignored.
+ *   as sums over points (a rule per axis that is exact for such products).  pos, w, np_off ignored.
  *
  * MP3_SUM_PARTICLE (Sec. 2.2, the particle sum after Eq. DDD-sum-privertex; the
  * primary vertex is the catalogue's contrast n/nbar - 1):
@@ -218,9 +217,8 @@ int mp3_zeta(mp3_plan_t plan, const void* delta, const float* pos, const float* 
 
 /* Gradient of J = sum_{j,l,b1,b2} dzeta[j][l][b1][b2] zeta_l^{(j)}[b1][b2] for
  * every form; the paper gives no gradient, this is the chain rule of mp3_zeta
- * and mp3_deposit.  The grid-Gamma form's adjoint takes the bins in chunks
- * that fit the LDS of its shift stencil.
- * The nodal and particle forms work in the eigenbasis of each symmetrised
+ * and mp3_deposit.
+ * Every form works in the eigenbasis of each symmetrised
  * cotangent (dzeta_l + dzeta_l^T) / 2 = V diag(d) V^T, decomposed per (l,
  * mock) on the device in float64: their fields come from the radial window
  * rotated by V, so the adjoint sources are diagonal in the bins; the
@@ -256,15 +254,14 @@ int mp3_zeta_backward(mp3_plan_t plan, const void* delta, const double* dzeta,
  * nor computed twice.  Particle form: the per-call steps (tile sort, stencil
  * records, power histogram) run once and each (l, m)'s stored fields feed
  * both the gather contraction and the adjoint sources.  Grid-Gamma form:
- * the adjoint's node values of each (l, m) are also contracted for zeta.
- * BF16-split plans and nodal plans above 32 bins run mp3_zeta and then
- * mp3_zeta_backward.  The nodal and particle forms contract zeta over the
- * fields of the cotangent's eigenbasis (see mp3_zeta_backward) and rotate it
- * back, zeta = V zetabar V^T (exactly symmetric); the particle form then
+ * each (l, m)'s stored fields feed both kernels.
+ * Nodal and particle BF16-split plans and nodal plans above 32 bins run
+ * mp3_zeta and then mp3_zeta_backward.  zeta is contracted over the fields of
+ * the cotangent's eigenbasis (see mp3_zeta_backward) and rotated back,
+ * zeta = V zetabar V^T (exactly symmetric); the particle form then
  * subtracts its volume means.  The results agree with the two separate calls
  * to rounding (per multipole: an entry's rounding follows the largest entry
- * of its multipole; the grid-Gamma contraction visits the nodes in another
- * order). */
+ * of its multipole). */
 int mp3_zeta_value_and_grad(mp3_plan_t plan, const void* delta, const double* dzeta,
                             double* zeta, void* ddelta, const float* pos, const float* w,
                             const int64_t* np_off, void* dw, void* workspace,
@@ -405,18 +402,15 @@ enum mp3_tune_knob {
                                  x and z passes of mp3_zeta_backward and the one sweep of
                                  mp3_zeta_value_and_grad): 0 = as many as fit 1 GiB of fields
                                  (default), else 1 .. 1024, capped at (lmax+1)(lmax+2)/2     */
-  MP3_TUNE_GAMMA_ADJOINT = 7, /* kernel of the grid-Gamma adjoint (B-spline plans): 0 = the
-                                 stencil over the shifts of the connection coefficients
-                                 (default), 1 = the transposed node quadrature; Daubechies-4
-                                 plans always take the stencil                               */
+  MP3_TUNE_GAMMA_ADJOINT = 7, /* kept for callers that set it: 0 or 1, without effect (the grid-Gamma
+                                 adjoint has one kernel)                                     */
   MP3_NTUNE = 8
 };
 
 /* Set a knob.  Out-of-range values return MP3_EINVAL and leave the knob as
  * it was.  The workspace size depends on MP3_TUNE_ZPASS_WGS,
- * MP3_TUNE_CONTRACT_WGS, MP3_TUNE_DEPOSIT_TILE, MP3_TUNE_ITEM_GROUP (the
- * fields of every item of a group are held at once) and MP3_TUNE_GAMMA_ADJOINT:
- * query mp3_workspace_size
+ * MP3_TUNE_CONTRACT_WGS, MP3_TUNE_DEPOSIT_TILE and MP3_TUNE_ITEM_GROUP (the
+ * fields of every item of a group are held at once): query mp3_workspace_size
  * again after changing them.  Not to be called while work of the plan is in
  * flight on another thread. */
 int mp3_tune_set(mp3_plan_t plan, int knob, int32_t value);

@@ -170,8 +170,6 @@ def autotune(plan, delta, pos=None, w=None, np_off=None, dzeta=None, backward: b
         knobs += ["fft_x_plan", "zpass_wgs"]
         if plan.summation != "nodal":
             knobs.append("contract_wgs")
-        if do_bwd and plan.summation == "gamma" and getattr(plan, "basis", "b3") == "b3":
-            knobs.append("gamma_adjoint")
         for _ in range(max(1, rounds)):
             for k in knobs:
                 times[k] = _descend(plan, k, path, reps, log)

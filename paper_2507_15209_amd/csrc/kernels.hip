@@ -1000,6 +1000,56 @@ __global__ void __launch_bounds__(512) k_zpass_store(const c2<T>* fields, c2<T>*
   }
 }
 
+// The adjoint's first axis from bin-interleaved sources: the transpose of
+// k_zpass_store.  A pencil of every bin is read in one contiguous run, turned
+// into LDS rows and z-transformed from there into [b][x][y][qz].
+template <int N, typename T>
+__global__ void __launch_bounds__(512) k_zpass_load(const c2<T>* in, c2<T>* fields, int nbins, int nbt, int b0,
+                                                     int ppw, const c2<T>* tw) {
+  using F = Fft<N, VZN>;
+  constexpr int RS = zrow<N>();
+  constexpr long long N3 = (long long)N * N * N;
+  extern __shared__ __align__(16) char smem[];
+  c2<T>* A = reinterpret_cast<c2<T>*>(smem);
+  c2<T>* tws = A + nbins * RS;
+  const long long mock = blockIdx.y;
+  stage_twiddles<N, T>(tw, tws);
+  const int p0 = blockIdx.x * ppw;
+  const int p1 = min(p0 + ppw, N * N);
+  const c2<T>* imock = in + mock * nbt * N3;
+  c2<T>* fmock = fields + (mock * nbt + b0) * N3;
+  const int nbc = blockDim.x / F::TPC;
+  const int rounds = pencil_rounds<N, VZN>(nbins);
+  for (int p = p0; p < p1; ++p) {
+    const c2<T>* src = imock + (long long)p * N * nbt + b0;
+    __syncthreads();
+    for (int idx = threadIdx.x; idx < N * nbins; idx += blockDim.x) {
+      const int z = idx / nbins, b = idx - z * nbins;
+      A[b * RS + lds_pos<true>(z)] = src[(long long)z * nbt + b];
+    }
+    __syncthreads();
+    for (int rr = 0; rr < rounds; ++rr) {
+      int j = threadIdx.x % F::TPC;
+      asm volatile("" : "+v"(j));
+      const int b = rr * nbc + threadIdx.x / F::TPC;
+      const bool active = b < nbins;
+      c2<T>* col = A + (active ? b : 0) * RS;
+      c2<T> v[F::RMAX];
+      if (active) {
+#pragma unroll
+        for (int r = 0; r < F::RMAX; ++r) v[r] = col[lds_pos<true>(F::in_index(j, r))];
+      }
+      col_sync<64 % F::TPC == 0>();
+      fft_column<N, +1, T, true, VZN, 64 % F::TPC == 0>(v, col, 1, j, tws, active);
+      if (active) {
+        c2<T>* dst = fmock + (long long)b * N3 + (long long)p * N;
+#pragma unroll
+        for (int e = 0; e < F::RMAX; ++e) dst[F::out_index(j, e)] = v[e];
+      }
+    }
+  }
+}
+
 // particles per (2^shift)^3-cell tile (sort key), tile id mock * NT + (tx * NTd + ty) * NTd + tz
 __device__ __forceinline__ int tile_of(const float* p, int n, double sc, int ntd, int shift) {
   int t = 0;
@@ -1237,180 +1287,6 @@ __global__ void __launch_bounds__(256) k_gather_contract(const c2<T>* fields, co
     }
     __syncthreads();
   }
-  ctr.finish(reinterpret_cast<double*>(smem), partials + ((long long)mock * gridDim.x + blockIdx.x) * nbins * nbins,
-             nbins);
-}
-
-// ---------------------------------------------------------------------------
-// grid summation with connection coefficients
-// ---------------------------------------------------------------------------
-// sum_x delta_x sum_{s,t} Gamma(s,t) a(x+s) conj(b(x+t)) equals the integral of
-// the three cubic B-spline interpolants, a degree-9 polynomial per axis on each
-// cell, integrated exactly by 5-point Gauss-Legendre.  A workgroup takes a
-// tile of 4^3 cells, holds the 7^3 coefficients it touches (all bins) in LDS
-// and, per x node, interpolates along x, y (half of the y nodes at a time)
-// and z into LDS rows A[b][node] with weights w_node delta_B(node), which the
-// contraction consumes.  Interpolation weights M[s][t] = B3(xi_s + 1 - t) and
-// node weights are set on the host.
-struct GammaQuad {
-  float m[5][4];     // B3 weight of tap t at node s (node xi_s in the unit cell)
-  float wq[5];       // Gauss-Legendre weights on [0, 1]
-  double md[5][4];
-  double wqd[5];
-};
-
-template <typename T> __device__ __forceinline__ T gq_m(const GammaQuad& q, int s, int t);
-template <> __device__ __forceinline__ float gq_m<float>(const GammaQuad& q, int s, int t) { return q.m[s][t]; }
-template <> __device__ __forceinline__ double gq_m<double>(const GammaQuad& q, int s, int t) { return q.md[s][t]; }
-template <typename T> __device__ __forceinline__ T gq_w(const GammaQuad& q, int s);
-template <> __device__ __forceinline__ float gq_w<float>(const GammaQuad& q, int s) { return q.wq[s]; }
-template <> __device__ __forceinline__ double gq_w<double>(const GammaQuad& q, int s) { return q.wqd[s]; }
-
-constexpr int GT = 4;              // cells per tile edge
-constexpr int GC = GT + 3;         // coefficients per tile edge
-constexpr int GN = 5 * GT;         // quadrature nodes per tile edge
-constexpr int GYH = GN / 2;        // y nodes per half
-constexpr int GK = GYH * GN;       // nodes per contraction slice (200)
-constexpr int GRS = GK + GK / 16 + 1;
-
-template <typename T>
-struct GammaLds {
-  // byte offsets into dynamic LDS for nbins bins
-  size_t C, D, P, Pd, Q, Qd, A, W, total;
-  __host__ __device__ GammaLds(int nbins) {
-    size_t o = 0;
-    auto take = [&](size_t b) { size_t r = o; o = (o + b + 15) & ~(size_t)15; return r; };
-    C = take((size_t)GC * GC * GC * nbins * sizeof(c2<T>));
-    D = take((size_t)GC * GC * GC * sizeof(T));
-    P = take((size_t)GC * GC * nbins * sizeof(c2<T>));
-    Pd = take((size_t)GC * GC * sizeof(T));
-    Q = take((size_t)GYH * GC * nbins * sizeof(c2<T>));
-    Qd = take((size_t)GYH * GC * sizeof(T));
-    A = take((size_t)nbins * GRS * sizeof(c2<T>));
-    W = take((size_t)GK * sizeof(T));
-    total = o;
-  }
-};
-
-// 1024 threads: the per-node phases are short, and one workgroup fills the
-// CU's LDS, so the waves of that one workgroup are what hides LDS latency
-// Bins: the workgroup contracts nbins local bins, local bin b < na being
-// field bin a0 + b and the rest field bins c0 + (b - na) of the nbt stored
-// bins (all of them with a0 = 0, na = nbins = nbt), so that plans with more
-// bins than the tile's LDS holds take them in pairs of chunks.
-template <typename T, bool MF, bool SPLIT = false, bool QUAD = false>
-__global__ void __launch_bounds__(1024) k_gamma_contract(const c2<T>* fields, const T* delta, int n, int nbins,
-                                                         GammaQuad gq, double* partials, int nbt, int a0, int na,
-                                                         int c0) {
-  extern __shared__ __align__(16) char smem[];
-  const GammaLds<T> L(nbins);
-  c2<T>* C = reinterpret_cast<c2<T>*>(smem + L.C);
-  T* D = reinterpret_cast<T*>(smem + L.D);
-  c2<T>* P = reinterpret_cast<c2<T>*>(smem + L.P);
-  T* Pd = reinterpret_cast<T*>(smem + L.Pd);
-  c2<T>* Q = reinterpret_cast<c2<T>*>(smem + L.Q);
-  T* Qd = reinterpret_cast<T*>(smem + L.Qd);
-  c2<T>* A = reinterpret_cast<c2<T>*>(smem + L.A);
-  T* W = reinterpret_cast<T*>(smem + L.W);
-  const int tid = threadIdx.x, nt = blockDim.x;
-  const long long mock = blockIdx.y;
-  const long long n3 = (long long)n * n * n;
-  const c2<T>* fm = fields + mock * n3 * nbt;
-  const T* dm = delta + mock * n3;
-  const int td = n / GT;
-  const long long ntiles = (long long)td * td * td;
-  Contractor<T, MF, SPLIT, QUAD> ctr;
-  ctr.init(nbins);
-  for (long long tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    const int tx = (int)(tile / ((long long)td * td)), ty = (int)((tile / td) % td), tz = (int)(tile % td);
-    const int x0 = tx * GT - 1, y0 = ty * GT - 1, z0 = tz * GT - 1;     // first coefficient (periodic)
-    __syncthreads();
-    for (int e = tid; e < GC * GC * GC * nbins; e += nt) {
-      const int b = e % nbins, c = e / nbins;
-      const int i = c / (GC * GC), j = (c / GC) % GC, k = c % GC;
-      const long long cell = ((long long)wrapi(x0 + i, n) * n + wrapi(y0 + j, n)) * n + wrapi(z0 + k, n);
-      C[e] = fm[cell * nbt + (b < na ? a0 + b : c0 + b - na)];
-    }
-    for (int c = tid; c < GC * GC * GC; c += nt) {
-      const int i = c / (GC * GC), j = (c / GC) % GC, k = c % GC;
-      D[c] = dm[((long long)wrapi(x0 + i, n) * n + wrapi(y0 + j, n)) * n + wrapi(z0 + k, n)];
-    }
-    for (int xn = 0; xn < GN; ++xn) {
-      const int cx = xn / 5, sx = xn % 5;
-      __syncthreads();
-      // x interpolation: P[j][k][b], Pd[j][k]
-      for (int e = tid; e < GC * GC * nbins; e += nt) {
-        const int b = e % nbins, jk = e / nbins;
-        c2<T> acc = mk<T>(0, 0);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const c2<T> v = C[((cx + t) * GC * GC + jk) * nbins + b];
-          const T m = gq_m<T>(gq, sx, t);
-          acc.x += m * v.x;
-          acc.y += m * v.y;
-        }
-        P[e] = acc;
-      }
-      for (int jk = tid; jk < GC * GC; jk += nt) {
-        T acc = 0;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) acc += gq_m<T>(gq, sx, t) * D[(cx + t) * GC * GC + jk];
-        Pd[jk] = acc;
-      }
-      for (int half = 0; half < 2; ++half) {
-        __syncthreads();
-        // y interpolation for this half of the y nodes: Q[yh][k][b], Qd[yh][k]
-        for (int e = tid; e < GYH * GC * nbins; e += nt) {
-          const int b = e % nbins, yk = e / nbins;
-          const int yh = yk / GC, k = yk % GC;
-          const int yn = half * GYH + yh, cy = yn / 5, sy = yn % 5;
-          c2<T> acc = mk<T>(0, 0);
-#pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            const c2<T> v = P[((cy + t) * GC + k) * nbins + b];
-            const T m = gq_m<T>(gq, sy, t);
-            acc.x += m * v.x;
-            acc.y += m * v.y;
-          }
-          Q[e] = acc;
-        }
-        for (int yk = tid; yk < GYH * GC; yk += nt) {
-          const int yh = yk / GC, k = yk % GC;
-          const int yn = half * GYH + yh, cy = yn / 5, sy = yn % 5;
-          T acc = 0;
-#pragma unroll
-          for (int t = 0; t < 4; ++t) acc += gq_m<T>(gq, sy, t) * Pd[(cy + t) * GC + k];
-          Qd[yk] = acc;
-        }
-        __syncthreads();
-        // z interpolation into the contraction rows; weights w_x w_y w_z delta_B
-        for (int e = tid; e < GK * nbins; e += nt) {
-          const int b = e % nbins, node = e / nbins;
-          const int yh = node / GN, zn = node % GN, cz = zn / 5, sz = zn % 5;
-          c2<T> acc = mk<T>(0, 0);
-#pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            const c2<T> v = Q[(yh * GC + cz + t) * nbins + b];
-            const T m = gq_m<T>(gq, sz, t);
-            acc.x += m * v.x;
-            acc.y += m * v.y;
-          }
-          A[b * GRS + lds_pos<true>(node)] = acc;
-        }
-        for (int node = tid; node < GK; node += nt) {
-          const int yh = node / GN, zn = node % GN, cz = zn / 5, sz = zn % 5;
-          const int sy = (half * GYH + yh) % 5;
-          T acc = 0;
-#pragma unroll
-          for (int t = 0; t < 4; ++t) acc += gq_m<T>(gq, sz, t) * Qd[yh * GC + cz + t];
-          W[node] = acc * gq_w<T>(gq, sx) * gq_w<T>(gq, sy) * gq_w<T>(gq, sz);
-        }
-        __syncthreads();
-        ctr.add(A, W, nbins, GRS, GK);
-      }
-    }
-  }
-  __syncthreads();
   ctr.finish(reinterpret_cast<double*>(smem), partials + ((long long)mock * gridDim.x + blockIdx.x) * nbins * nbins,
              nbins);
 }
@@ -1669,17 +1545,6 @@ k_zpass_adjoint(c2<T>* fields, const T* delta, const T* __restrict__ lam_d, T* d
     if constexpr (FUSED)
       ctr.finish(reinterpret_cast<double*>(smem), partials + (((long long)g * batch + mock) * nwg + chunk) * nb2,
                  nbins);
-  }
-}
-
-// lam_s[l][j][b][b'] = (dzeta[j][l][b][b'] + dzeta[j][l][b'][b]) / 2 for every l (blockIdx.x = l)
-template <typename T>
-__global__ void k_lam_sym(const double* dzeta, T* lam_s, int nbins, int lmax, int batch) {
-  const int j = blockIdx.y, l = blockIdx.x;
-  const double* dz = dzeta + ((long long)j * (lmax + 1) + l) * nbins * nbins;
-  for (int t = threadIdx.x; t < nbins * nbins; t += blockDim.x) {
-    const int b = t / nbins, bp = t % nbins;
-    lam_s[((long long)l * batch + j) * nbins * nbins + t] = (T)(0.5 * (dz[b * nbins + bp] + dz[bp * nbins + b]));
   }
 }
 
@@ -2242,642 +2107,6 @@ __global__ void __launch_bounds__(256) k_scatter_source(const int* tcell, const 
   }
 }
 
-// ---------------------------------------------------------------------------
-// adjoint of the grid summation with connection coefficients
-// ---------------------------------------------------------------------------
-// zeta is the exact 5-point Gauss-Legendre quadrature over every cell of
-// delta_B(u) sum lam atilde_{b1}(u) conj(atilde_{b2}(u)), so for one (l, m)
-//   c_b(x)    = sum_q B3(u_q - x) w_q delta_B(u_q) v_b(u_q),   v_b = sum_b' lam_s[b][b'] conj(atilde_b'),
-//   direct(x) += wm sum_q B3(u_q - x) w_q F(u_q),               F = sum_b Re(atilde_b v_b):
-// the transposes of the three interpolations of k_gamma_contract applied to
-// the node sources.  A workgroup takes a 4^3-cell tile as the forward does,
-// per x node and per y cell (5 y nodes x 20 z nodes) interpolates the fields
-// to the nodes, forms v and F there, and folds the sources back through the
-// transposed z, y and x interpolations into a 7^3-coefficient LDS accumulator,
-// which it adds to c and direct with global atomics (neighbouring tiles
-// overlap by three coefficients per axis).
-constexpr int AGY = 5;                      // y nodes per adjoint slice (one y cell)
-constexpr int AGK = AGY * GN;               // nodes per slice (100)
-constexpr int AGRS = AGK + AGK / 16 + 1;
-constexpr int AGH = 4;                      // bins per thread in the per-node step
-constexpr int AGP = 5;                      // threads per node in that step (AGP * AGH >= bins)
-
-template <typename T>
-struct GammaAdjLds {
-  size_t C, D, Ct, Dt, P, Pd, Pt, Pdt, Q, Qd, Qt, Qdt, A, W, Wq, Fh, lam, total;
-  __host__ __device__ GammaAdjLds(int nbins) {
-    size_t o = 0;
-    auto take = [&](size_t b) { size_t r = o; o = (o + b + 15) & ~(size_t)15; return r; };
-    const size_t c = sizeof(c2<T>), r = sizeof(T);
-    C = take((size_t)GC * GC * GC * nbins * c);
-    D = take((size_t)GC * GC * GC * r);
-    Ct = take((size_t)GC * GC * GC * nbins * c);
-    Dt = take((size_t)GC * GC * GC * r);
-    P = take((size_t)GC * GC * nbins * c);
-    Pd = take((size_t)GC * GC * r);
-    Pt = take((size_t)GC * GC * nbins * c);
-    Pdt = take((size_t)GC * GC * r);
-    Q = take((size_t)AGY * GC * nbins * c);
-    Qd = take((size_t)AGY * GC * r);
-    Qt = take((size_t)AGY * GC * nbins * c);
-    Qdt = take((size_t)AGY * GC * r);
-    A = take((size_t)nbins * AGRS * c);
-    W = take((size_t)AGK * r);
-    Wq = take((size_t)AGK * r);
-    Fh = take((size_t)AGP * AGK * r);
-    lam = take((size_t)nbins * nbins * r);
-    total = o;
-  }
-};
-
-// float: 1024 threads, for the same reason as k_gamma_contract; double needs
-// more than the 128 registers a 1024-thread workgroup leaves each lane.
-// FUSED: the node values and weights of each slice are also contracted for
-// zeta (the partials of k_gamma_contract), so value and gradient share one
-// interpolation of the fields.
-template <typename T, bool FUSED = false, bool MF = false, bool QUAD = false>
-__global__ void __launch_bounds__(sizeof(T) == 4 ? 1024 : 512) k_gamma_adjoint(const c2<T>* fields, const T* delta, const T* lam_s, int n,
-                                                        int nbins, GammaQuad gq, T wm, c2<T>* cout, T* direct,
-                                                        double* partials) {
-  extern __shared__ __align__(16) char smem[];
-  const GammaAdjLds<T> L(nbins);
-  c2<T>* C = reinterpret_cast<c2<T>*>(smem + L.C);
-  T* D = reinterpret_cast<T*>(smem + L.D);
-  c2<T>* Ct = reinterpret_cast<c2<T>*>(smem + L.Ct);
-  T* Dt = reinterpret_cast<T*>(smem + L.Dt);
-  c2<T>* P = reinterpret_cast<c2<T>*>(smem + L.P);
-  T* Pd = reinterpret_cast<T*>(smem + L.Pd);
-  c2<T>* Pt = reinterpret_cast<c2<T>*>(smem + L.Pt);
-  T* Pdt = reinterpret_cast<T*>(smem + L.Pdt);
-  c2<T>* Q = reinterpret_cast<c2<T>*>(smem + L.Q);
-  T* Qd = reinterpret_cast<T*>(smem + L.Qd);
-  c2<T>* Qt = reinterpret_cast<c2<T>*>(smem + L.Qt);
-  T* Qdt = reinterpret_cast<T*>(smem + L.Qdt);
-  c2<T>* A = reinterpret_cast<c2<T>*>(smem + L.A);
-  T* W = reinterpret_cast<T*>(smem + L.W);
-  T* Wq = reinterpret_cast<T*>(smem + L.Wq);
-  T* Fh = reinterpret_cast<T*>(smem + L.Fh);
-  T* lam = reinterpret_cast<T*>(smem + L.lam);
-  const int tid = threadIdx.x, nt = blockDim.x;
-  const long long mock = blockIdx.y;
-  const long long n3 = (long long)n * n * n;
-  const c2<T>* fm = fields + mock * n3 * nbins;
-  const T* dm = delta + mock * n3;
-  c2<T>* cm = cout + mock * nbins * n3;
-  T* rm = direct + mock * n3;
-  const int nb2 = nbins * nbins;
-  for (int t = tid; t < nb2; t += nt) lam[t] = lam_s[mock * nb2 + t];
-  Contractor<T, MF, false, QUAD> ctr;
-  if constexpr (FUSED) ctr.init(nbins);
-  const int td = n / GT;
-  const long long ntiles = (long long)td * td * td;
-  constexpr int NC = GC * GC * GC;
-  for (long long tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    const int tx = (int)(tile / ((long long)td * td)), ty = (int)((tile / td) % td), tz = (int)(tile % td);
-    const int x0 = tx * GT - 1, y0 = ty * GT - 1, z0 = tz * GT - 1;     // first coefficient (periodic)
-    __syncthreads();
-    for (int e = tid; e < NC * nbins; e += nt) {
-      const int b = e % nbins, c = e / nbins;
-      const int i = c / (GC * GC), j = (c / GC) % GC, k = c % GC;
-      const long long cell = ((long long)wrapi(x0 + i, n) * n + wrapi(y0 + j, n)) * n + wrapi(z0 + k, n);
-      C[e] = fm[cell * nbins + b];
-      Ct[e] = mk<T>(0, 0);
-    }
-    for (int c = tid; c < NC; c += nt) {
-      const int i = c / (GC * GC), j = (c / GC) % GC, k = c % GC;
-      D[c] = dm[((long long)wrapi(x0 + i, n) * n + wrapi(y0 + j, n)) * n + wrapi(z0 + k, n)];
-      Dt[c] = (T)0;
-    }
-    for (int xn = 0; xn < GN; ++xn) {
-      const int cx = xn / 5, sx = xn % 5;
-      __syncthreads();
-      // x interpolation: P[j][k][b], Pd[j][k]; clear the transposed accumulators
-      for (int e = tid; e < GC * GC * nbins; e += nt) {
-        const int b = e % nbins, jk = e / nbins;
-        c2<T> acc = mk<T>(0, 0);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const c2<T> v = C[((cx + t) * GC * GC + jk) * nbins + b];
-          const T m = gq_m<T>(gq, sx, t);
-          acc.x += m * v.x;
-          acc.y += m * v.y;
-        }
-        P[e] = acc;
-        Pt[e] = mk<T>(0, 0);
-      }
-      for (int jk = tid; jk < GC * GC; jk += nt) {
-        T acc = 0;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) acc += gq_m<T>(gq, sx, t) * D[(cx + t) * GC * GC + jk];
-        Pd[jk] = acc;
-        Pdt[jk] = (T)0;
-      }
-      for (int cy = 0; cy < GT; ++cy) {
-        __syncthreads();
-        // y interpolation for the 5 y nodes of cell cy: Q[yh][k][b], Qd[yh][k]
-        for (int e = tid; e < AGY * GC * nbins; e += nt) {
-          const int b = e % nbins, yk = e / nbins;
-          const int yh = yk / GC, k = yk % GC;
-          c2<T> acc = mk<T>(0, 0);
-#pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            const c2<T> v = P[((cy + t) * GC + k) * nbins + b];
-            const T m = gq_m<T>(gq, yh, t);
-            acc.x += m * v.x;
-            acc.y += m * v.y;
-          }
-          Q[e] = acc;
-        }
-        for (int yk = tid; yk < AGY * GC; yk += nt) {
-          const int yh = yk / GC, k = yk % GC;
-          T acc = 0;
-#pragma unroll
-          for (int t = 0; t < 4; ++t) acc += gq_m<T>(gq, yh, t) * Pd[(cy + t) * GC + k];
-          Qd[yk] = acc;
-        }
-        __syncthreads();
-        // z interpolation to the nodes: A[b][node], node = yh * GN + zn; weights
-        for (int e = tid; e < AGK * nbins; e += nt) {
-          const int b = e % nbins, node = e / nbins;
-          const int yh = node / GN, zn = node % GN, cz = zn / 5, sz = zn % 5;
-          c2<T> acc = mk<T>(0, 0);
-#pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            const c2<T> v = Q[(yh * GC + cz + t) * nbins + b];
-            const T m = gq_m<T>(gq, sz, t);
-            acc.x += m * v.x;
-            acc.y += m * v.y;
-          }
-          A[b * AGRS + lds_pos<true>(node)] = acc;
-        }
-        for (int node = tid; node < AGK; node += nt) {
-          const int yh = node / GN, zn = node % GN, cz = zn / 5, sz = zn % 5;
-          T acc = 0;
-#pragma unroll
-          for (int t = 0; t < 4; ++t) acc += gq_m<T>(gq, sz, t) * Qd[yh * GC + cz + t];
-          const T wq = gq_w<T>(gq, sx) * gq_w<T>(gq, yh) * gq_w<T>(gq, sz);
-          W[node] = acc * wq;                  // w_q delta_B(u_q)
-          Wq[node] = wq;
-        }
-        __syncthreads();
-        // FUSED: contraction of the node values (read only in this phase)
-        if constexpr (FUSED) ctr.add(A, W, nbins, AGRS, AGK);
-        // per node and AGH bins: v_b = sum_b' lam_s[b][b'] conj(a_b'), F; the
-        // node's field values are read from LDS once into registers
-        c2<T> vh[AGH];
-        const bool vthread = tid < AGP * AGK;
-        const int vnode = tid / AGP, vh0 = (tid % AGP) * AGH;
-        if (vthread) {
-          const int zp = lds_pos<true>(vnode);
-          c2<T> av[AGP * AGH];
-#pragma unroll
-          for (int bp = 0; bp < AGP * AGH; ++bp) av[bp] = bp < nbins ? A[bp * AGRS + zp] : mk<T>(0, 0);
-          T f = 0;
-#pragma unroll
-          for (int i = 0; i < AGH; ++i) {
-            const int b = vh0 + i;
-            c2<T> v = mk<T>(0, 0);
-            if (b < nbins) {
-              const T* lrow = lam + b * nbins;
-#pragma unroll
-              for (int bp = 0; bp < AGP * AGH; ++bp) {
-                if (bp < nbins) {
-                  const T lv = lrow[bp];
-                  v.x += lv * av[bp].x;
-                  v.y -= lv * av[bp].y;
-                }
-              }
-              const c2<T> a = A[b * AGRS + zp];
-              f += a.x * v.x - a.y * v.y;
-            }
-            vh[i] = v;
-          }
-          Fh[tid] = f;
-        }
-        __syncthreads();
-        // node sources: S_b = w_q delta_B v_b over A; direct source w_q F into Fh[AGP node]
-        if (vthread) {
-          const int zp = lds_pos<true>(vnode);
-          const T wv = W[vnode];
-#pragma unroll
-          for (int i = 0; i < AGH; ++i) {
-            const int b = vh0 + i;
-            if (b < nbins) A[b * AGRS + zp] = mk<T>(wv * vh[i].x, wv * vh[i].y);
-          }
-        }
-        __syncthreads();
-        if (tid < AGK) {
-          T f = 0;
-#pragma unroll
-          for (int q = 0; q < AGP; ++q) f += Fh[AGP * tid + q];
-          Fh[AGP * tid] = Wq[tid] * f;
-        }
-        __syncthreads();
-        // transposed z: Qt[yh][kz][b] = sum_{tz, sz} M[sz][tz] S_b(yh, 5 (kz - tz) + sz)
-        for (int e = tid; e < AGY * GC * nbins; e += nt) {
-          const int b = e % nbins, yk = e / nbins;
-          const int yh = yk / GC, kz = yk % GC;
-          c2<T> acc = mk<T>(0, 0);
-#pragma unroll
-          for (int tz = 0; tz < 4; ++tz) {
-            const int cz = kz - tz;
-            if (cz < 0 || cz >= GT) continue;
-#pragma unroll
-            for (int sz = 0; sz < 5; ++sz) {
-              const c2<T> v = A[b * AGRS + lds_pos<true>(yh * GN + 5 * cz + sz)];
-              const T m = gq_m<T>(gq, sz, tz);
-              acc.x += m * v.x;
-              acc.y += m * v.y;
-            }
-          }
-          Qt[e] = acc;
-        }
-        for (int yk = tid; yk < AGY * GC; yk += nt) {
-          const int yh = yk / GC, kz = yk % GC;
-          T acc = 0;
-#pragma unroll
-          for (int tz = 0; tz < 4; ++tz) {
-            const int cz = kz - tz;
-            if (cz < 0 || cz >= GT) continue;
-#pragma unroll
-            for (int sz = 0; sz < 5; ++sz) acc += gq_m<T>(gq, sz, tz) * Fh[AGP * (yh * GN + 5 * cz + sz)];
-          }
-          Qdt[yk] = acc;
-        }
-        __syncthreads();
-        // transposed y: Pt[cy + ty][kz][b] += sum_yh M[yh][ty] Qt[yh][kz][b]
-        for (int e = tid; e < 4 * GC * nbins; e += nt) {
-          const int b = e % nbins, tk = e / nbins;
-          const int tyy = tk / GC, kz = tk % GC;
-          c2<T> acc = mk<T>(0, 0);
-#pragma unroll
-          for (int yh = 0; yh < AGY; ++yh) {
-            const c2<T> v = Qt[(yh * GC + kz) * nbins + b];
-            const T m = gq_m<T>(gq, yh, tyy);
-            acc.x += m * v.x;
-            acc.y += m * v.y;
-          }
-          c2<T>& o = Pt[((cy + tyy) * GC + kz) * nbins + b];
-          o.x += acc.x;
-          o.y += acc.y;
-        }
-        for (int tk = tid; tk < 4 * GC; tk += nt) {
-          const int tyy = tk / GC, kz = tk % GC;
-          T acc = 0;
-#pragma unroll
-          for (int yh = 0; yh < AGY; ++yh) acc += gq_m<T>(gq, yh, tyy) * Qdt[yh * GC + kz];
-          Pdt[(cy + tyy) * GC + kz] += acc;
-        }
-      }
-      __syncthreads();
-      // transposed x: Ct[cx + tx][j][k][b] += M[sx][tx] Pt[j][k][b]
-      for (int e = tid; e < 4 * GC * GC * nbins; e += nt) {
-        const int b = e % nbins, r = e / nbins;
-        const int txx = r / (GC * GC), jk = r % (GC * GC);
-        const c2<T> v = Pt[jk * nbins + b];
-        const T m = gq_m<T>(gq, sx, txx);
-        c2<T>& o = Ct[((cx + txx) * GC * GC + jk) * nbins + b];
-        o.x += m * v.x;
-        o.y += m * v.y;
-      }
-      for (int r = tid; r < 4 * GC * GC; r += nt) {
-        const int txx = r / (GC * GC), jk = r % (GC * GC);
-        Dt[(cx + txx) * GC * GC + jk] += gq_m<T>(gq, sx, txx) * Pdt[jk];
-      }
-    }
-    __syncthreads();
-    // fold the tile into the grid (neighbouring tiles share coefficients)
-    for (int e = tid; e < NC * nbins; e += nt) {
-      const int b = e % nbins, c = e / nbins;
-      const int i = c / (GC * GC), j = (c / GC) % GC, k = c % GC;
-      const long long cell = ((long long)wrapi(x0 + i, n) * n + wrapi(y0 + j, n)) * n + wrapi(z0 + k, n);
-      c2<T>* o = cm + (long long)b * n3 + cell;
-      atomicAdd(&o->x, Ct[e].x);
-      atomicAdd(&o->y, Ct[e].y);
-    }
-    for (int c = tid; c < NC; c += nt) {
-      const int i = c / (GC * GC), j = (c / GC) % GC, k = c % GC;
-      atomicAdd(&rm[((long long)wrapi(x0 + i, n) * n + wrapi(y0 + j, n)) * n + wrapi(z0 + k, n)], wm * Dt[c]);
-    }
-  }
-  if constexpr (FUSED) {
-    __syncthreads();
-    ctr.finish(reinterpret_cast<double*>(smem), partials + ((long long)mock * gridDim.x + blockIdx.x) * nbins * nbins,
-               nbins);
-  }
-}
-
-// ---------------------------------------------------------------------------
-// grid-Gamma adjoint by bin chunks (plans whose tiles of every bin do not fit
-// the LDS): v_b = sum_b' lam_s[b][b'] conj(atilde_b') is the conjugate of the
-// interpolant of U_b = sum_b' lam_s[b][b'] a_b' (the interpolation is real
-// and linear), so with U mixed on the grid first, each bin's sources
-//   c_b(x) = sum_q B3(u_q - x) w_q delta_B(u_q) conj(U~_b(u_q))
-// and each bin's share of the primary term
-//   F = sum_b Re(atilde_b conj(U~_b))
-// need only that bin's a and U: a tile takes the bins in chunks.
-// ---------------------------------------------------------------------------
-// U[mock][x][b] = sum_b' lam_s[mock][b][b'] F[mock][x][b'] (bin-interleaved)
-template <typename T>
-__global__ void k_bin_mix(const c2<T>* F, const T* lam_s, c2<T>* U, long long n3, int nbins) {
-  extern __shared__ __align__(16) char smem_mix[];
-  T* lam = reinterpret_cast<T*>(smem_mix);
-  const long long mock = blockIdx.y;
-  const int nb2 = nbins * nbins;
-  for (int t = threadIdx.x; t < nb2; t += blockDim.x) lam[t] = lam_s[mock * nb2 + t];
-  __syncthreads();
-  const c2<T>* fm = F + mock * n3 * nbins;
-  c2<T>* um = U + mock * n3 * nbins;
-  const long long total = n3 * nbins;
-  for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < total; e += (long long)gridDim.x * blockDim.x) {
-    const long long x = e / nbins;
-    const int b = (int)(e - x * nbins);
-    const c2<T>* row = fm + x * nbins;
-    const T* lrow = lam + b * nbins;
-    T re = 0, im = 0;
-    for (int bp = 0; bp < nbins; ++bp) {
-      const c2<T> a = row[bp];
-      re += lrow[bp] * a.x;
-      im += lrow[bp] * a.y;
-    }
-    um[e] = mk<T>(re, im);
-  }
-}
-
-template <typename T>
-struct GammaBinsLds {
-  size_t C, Cu, Ct, D, Dt, P, Pu, Pt, Pd, Pdt, Q, Qu, Qt, Qd, Qdt, A, Au, W, Wq, Fn, total;
-  __host__ __device__ GammaBinsLds(int nbc) {
-    size_t o = 0;
-    auto take = [&](size_t b) { size_t r = o; o = (o + b + 15) & ~(size_t)15; return r; };
-    const size_t c = sizeof(c2<T>), r = sizeof(T);
-    const size_t nc = (size_t)GC * GC * GC;
-    C = take(nc * nbc * c);
-    Cu = take(nc * nbc * c);
-    Ct = take(nc * nbc * c);
-    D = take(nc * r);
-    Dt = take(nc * r);
-    P = take((size_t)GC * GC * nbc * c);
-    Pu = take((size_t)GC * GC * nbc * c);
-    Pt = take((size_t)GC * GC * nbc * c);
-    Pd = take((size_t)GC * GC * r);
-    Pdt = take((size_t)GC * GC * r);
-    Q = take((size_t)AGY * GC * nbc * c);
-    Qu = take((size_t)AGY * GC * nbc * c);
-    Qt = take((size_t)AGY * GC * nbc * c);
-    Qd = take((size_t)AGY * GC * r);
-    Qdt = take((size_t)AGY * GC * r);
-    A = take((size_t)nbc * AGRS * c);
-    Au = take((size_t)nbc * AGRS * c);
-    W = take((size_t)AGK * r);
-    Wq = take((size_t)AGK * r);
-    Fn = take((size_t)AGK * r);
-    total = o;
-  }
-};
-
-// bins b0 .. b0 + nbc - 1 of nbt; adds the sources into cout (zeroed by the
-// caller) and wm times this chunk's share of the primary term into direct
-template <typename T>
-__global__ void __launch_bounds__(512) k_gamma_adjoint_bins(const c2<T>* fields, const c2<T>* U, const T* delta,
-                                                            int n, int nbt, int b0, int nbc, GammaQuad gq, T wm,
-                                                            c2<T>* cout, T* direct) {
-  extern __shared__ __align__(16) char smem[];
-  const GammaBinsLds<T> L(nbc);
-  c2<T>* C = reinterpret_cast<c2<T>*>(smem + L.C);
-  c2<T>* Cu = reinterpret_cast<c2<T>*>(smem + L.Cu);
-  c2<T>* Ct = reinterpret_cast<c2<T>*>(smem + L.Ct);
-  T* D = reinterpret_cast<T*>(smem + L.D);
-  T* Dt = reinterpret_cast<T*>(smem + L.Dt);
-  c2<T>* P = reinterpret_cast<c2<T>*>(smem + L.P);
-  c2<T>* Pu = reinterpret_cast<c2<T>*>(smem + L.Pu);
-  c2<T>* Pt = reinterpret_cast<c2<T>*>(smem + L.Pt);
-  T* Pd = reinterpret_cast<T*>(smem + L.Pd);
-  T* Pdt = reinterpret_cast<T*>(smem + L.Pdt);
-  c2<T>* Q = reinterpret_cast<c2<T>*>(smem + L.Q);
-  c2<T>* Qu = reinterpret_cast<c2<T>*>(smem + L.Qu);
-  c2<T>* Qt = reinterpret_cast<c2<T>*>(smem + L.Qt);
-  T* Qd = reinterpret_cast<T*>(smem + L.Qd);
-  T* Qdt = reinterpret_cast<T*>(smem + L.Qdt);
-  c2<T>* A = reinterpret_cast<c2<T>*>(smem + L.A);
-  c2<T>* Au = reinterpret_cast<c2<T>*>(smem + L.Au);
-  T* W = reinterpret_cast<T*>(smem + L.W);
-  T* Wq = reinterpret_cast<T*>(smem + L.Wq);
-  T* Fn = reinterpret_cast<T*>(smem + L.Fn);
-  const int tid = threadIdx.x, nt = blockDim.x;
-  const long long mock = blockIdx.y;
-  const long long n3 = (long long)n * n * n;
-  const c2<T>* fm = fields + mock * n3 * nbt;
-  const c2<T>* um = U + mock * n3 * nbt;
-  const T* dm = delta + mock * n3;
-  c2<T>* cm = cout + mock * nbt * n3;
-  T* rm = direct + mock * n3;
-  const int td = n / GT;
-  const long long ntiles = (long long)td * td * td;
-  constexpr int NC = GC * GC * GC;
-  for (long long tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    const int tx = (int)(tile / ((long long)td * td)), ty = (int)((tile / td) % td), tz = (int)(tile % td);
-    const int x0 = tx * GT - 1, y0 = ty * GT - 1, z0 = tz * GT - 1;
-    __syncthreads();
-    for (int e = tid; e < NC * nbc; e += nt) {
-      const int b = e % nbc, c = e / nbc;
-      const int i = c / (GC * GC), j = (c / GC) % GC, k = c % GC;
-      const long long cell = ((long long)wrapi(x0 + i, n) * n + wrapi(y0 + j, n)) * n + wrapi(z0 + k, n);
-      C[e] = fm[cell * nbt + b0 + b];
-      Cu[e] = um[cell * nbt + b0 + b];
-      Ct[e] = mk<T>(0, 0);
-    }
-    for (int c = tid; c < NC; c += nt) {
-      const int i = c / (GC * GC), j = (c / GC) % GC, k = c % GC;
-      D[c] = dm[((long long)wrapi(x0 + i, n) * n + wrapi(y0 + j, n)) * n + wrapi(z0 + k, n)];
-      Dt[c] = (T)0;
-    }
-    for (int xn = 0; xn < GN; ++xn) {
-      const int cx = xn / 5, sx = xn % 5;
-      __syncthreads();
-      // x interpolation of a, U and delta; clear the transposed accumulators
-      for (int e = tid; e < GC * GC * nbc; e += nt) {
-        const int b = e % nbc, jk = e / nbc;
-        c2<T> acc = mk<T>(0, 0), accu = mk<T>(0, 0);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const int src = ((cx + t) * GC * GC + jk) * nbc + b;
-          const T m = gq_m<T>(gq, sx, t);
-          const c2<T> v = C[src], u = Cu[src];
-          acc.x += m * v.x;
-          acc.y += m * v.y;
-          accu.x += m * u.x;
-          accu.y += m * u.y;
-        }
-        P[e] = acc;
-        Pu[e] = accu;
-        Pt[e] = mk<T>(0, 0);
-      }
-      for (int jk = tid; jk < GC * GC; jk += nt) {
-        T acc = 0;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) acc += gq_m<T>(gq, sx, t) * D[(cx + t) * GC * GC + jk];
-        Pd[jk] = acc;
-        Pdt[jk] = (T)0;
-      }
-      for (int cy = 0; cy < GT; ++cy) {
-        __syncthreads();
-        // y interpolation for the 5 y nodes of cell cy
-        for (int e = tid; e < AGY * GC * nbc; e += nt) {
-          const int b = e % nbc, yk = e / nbc;
-          const int yh = yk / GC, k = yk % GC;
-          c2<T> acc = mk<T>(0, 0), accu = mk<T>(0, 0);
-#pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            const int src = ((cy + t) * GC + k) * nbc + b;
-            const T m = gq_m<T>(gq, yh, t);
-            const c2<T> v = P[src], u = Pu[src];
-            acc.x += m * v.x;
-            acc.y += m * v.y;
-            accu.x += m * u.x;
-            accu.y += m * u.y;
-          }
-          Q[e] = acc;
-          Qu[e] = accu;
-        }
-        for (int yk = tid; yk < AGY * GC; yk += nt) {
-          const int yh = yk / GC, k = yk % GC;
-          T acc = 0;
-#pragma unroll
-          for (int t = 0; t < 4; ++t) acc += gq_m<T>(gq, yh, t) * Pd[(cy + t) * GC + k];
-          Qd[yk] = acc;
-        }
-        __syncthreads();
-        // z interpolation to the 100 nodes of this (x node, y cell) slice
-        for (int e = tid; e < AGK * nbc; e += nt) {
-          const int b = e % nbc, node = e / nbc;
-          const int yh = node / GN, zn = node % GN, cz = zn / 5, sz = zn % 5;
-          c2<T> acc = mk<T>(0, 0), accu = mk<T>(0, 0);
-#pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            const int src = (yh * GC + cz + t) * nbc + b;
-            const T m = gq_m<T>(gq, sz, t);
-            const c2<T> v = Q[src], u = Qu[src];
-            acc.x += m * v.x;
-            acc.y += m * v.y;
-            accu.x += m * u.x;
-            accu.y += m * u.y;
-          }
-          A[b * AGRS + lds_pos<true>(node)] = acc;
-          Au[b * AGRS + lds_pos<true>(node)] = accu;
-        }
-        for (int node = tid; node < AGK; node += nt) {
-          const int yh = node / GN, zn = node % GN, cz = zn / 5, sz = zn % 5;
-          T acc = 0;
-#pragma unroll
-          for (int t = 0; t < 4; ++t) acc += gq_m<T>(gq, sz, t) * Qd[yh * GC + cz + t];
-          const T wq = gq_w<T>(gq, sx) * gq_w<T>(gq, yh) * gq_w<T>(gq, sz);
-          W[node] = acc * wq;
-          Wq[node] = wq;
-        }
-        __syncthreads();
-        // per node: F (this chunk's bins) and the sources S_b = w delta_B conj(U~_b), over A
-        for (int node = tid; node < AGK; node += nt) {
-          const int zp = lds_pos<true>(node);
-          const T wv = W[node];
-          T f = 0;
-          for (int b = 0; b < nbc; ++b) {
-            const c2<T> a = A[b * AGRS + zp], u = Au[b * AGRS + zp];
-            f += a.x * u.x + a.y * u.y;
-            A[b * AGRS + zp] = mk<T>(wv * u.x, -wv * u.y);
-          }
-          Fn[node] = Wq[node] * f;
-        }
-        __syncthreads();
-        // transposed z
-        for (int e = tid; e < AGY * GC * nbc; e += nt) {
-          const int b = e % nbc, yk = e / nbc;
-          const int yh = yk / GC, kz = yk % GC;
-          c2<T> acc = mk<T>(0, 0);
-#pragma unroll
-          for (int tz = 0; tz < 4; ++tz) {
-            const int cz = kz - tz;
-            if (cz < 0 || cz >= GT) continue;
-#pragma unroll
-            for (int sz = 0; sz < 5; ++sz) {
-              const c2<T> v = A[b * AGRS + lds_pos<true>(yh * GN + 5 * cz + sz)];
-              const T m = gq_m<T>(gq, sz, tz);
-              acc.x += m * v.x;
-              acc.y += m * v.y;
-            }
-          }
-          Qt[e] = acc;
-        }
-        for (int yk = tid; yk < AGY * GC; yk += nt) {
-          const int yh = yk / GC, kz = yk % GC;
-          T acc = 0;
-#pragma unroll
-          for (int tz = 0; tz < 4; ++tz) {
-            const int cz = kz - tz;
-            if (cz < 0 || cz >= GT) continue;
-#pragma unroll
-            for (int sz = 0; sz < 5; ++sz) acc += gq_m<T>(gq, sz, tz) * Fn[yh * GN + 5 * cz + sz];
-          }
-          Qdt[yk] = acc;
-        }
-        __syncthreads();
-        // transposed y
-        for (int e = tid; e < 4 * GC * nbc; e += nt) {
-          const int b = e % nbc, tk = e / nbc;
-          const int tyy = tk / GC, kz = tk % GC;
-          c2<T> acc = mk<T>(0, 0);
-#pragma unroll
-          for (int yh = 0; yh < AGY; ++yh) {
-            const c2<T> v = Qt[(yh * GC + kz) * nbc + b];
-            const T m = gq_m<T>(gq, yh, tyy);
-            acc.x += m * v.x;
-            acc.y += m * v.y;
-          }
-          c2<T>& o = Pt[((cy + tyy) * GC + kz) * nbc + b];
-          o.x += acc.x;
-          o.y += acc.y;
-        }
-        for (int tk = tid; tk < 4 * GC; tk += nt) {
-          const int tyy = tk / GC, kz = tk % GC;
-          T acc = 0;
-#pragma unroll
-          for (int yh = 0; yh < AGY; ++yh) acc += gq_m<T>(gq, yh, tyy) * Qdt[yh * GC + kz];
-          Pdt[(cy + tyy) * GC + kz] += acc;
-        }
-      }
-      __syncthreads();
-      // transposed x
-      for (int e = tid; e < 4 * GC * GC * nbc; e += nt) {
-        const int b = e % nbc, r = e / nbc;
-        const int txx = r / (GC * GC), jk = r % (GC * GC);
-        const c2<T> v = Pt[jk * nbc + b];
-        const T m = gq_m<T>(gq, sx, txx);
-        c2<T>& o = Ct[((cx + txx) * GC * GC + jk) * nbc + b];
-        o.x += m * v.x;
-        o.y += m * v.y;
-      }
-      for (int r = tid; r < 4 * GC * GC; r += nt) {
-        const int txx = r / (GC * GC), jk = r % (GC * GC);
-        Dt[(cx + txx) * GC * GC + jk] += gq_m<T>(gq, sx, txx) * Pdt[jk];
-      }
-    }
-    __syncthreads();
-    // fold the tile into the grid (neighbouring tiles share coefficients)
-    for (int e = tid; e < NC * nbc; e += nt) {
-      const int b = e % nbc, c = e / nbc;
-      const int i = c / (GC * GC), j = (c / GC) % GC, k = c % GC;
-      const long long cell = ((long long)wrapi(x0 + i, n) * n + wrapi(y0 + j, n)) * n + wrapi(z0 + k, n);
-      c2<T>* o = cm + (long long)(b0 + b) * n3 + cell;
-      atomicAdd(&o->x, Ct[e].x);
-      atomicAdd(&o->y, Ct[e].y);
-    }
-    for (int c = tid; c < NC; c += nt) {
-      const int i = c / (GC * GC), j = (c / GC) % GC, k = c % GC;
-      atomicAdd(&rm[((long long)wrapi(x0 + i, n) * n + wrapi(y0 + j, n)) * n + wrapi(z0 + k, n)], wm * Dt[c]);
-    }
-  }
-}
-
 // zeta[mock][l][g(i)][g(j)] += scale sum_w partials[mock][w][i][j] for the local
 // pairs (i, j) of a chunk-pair contraction that this pass owns: the cross
 // block always, the diagonal block of the first chunk when own_a, of the
@@ -3186,6 +2415,24 @@ hipError_t zpass_store_t(const ZpassArgs& a, void* out, hipStream_t st) {
   return hipSuccess;
 }
 
+template <int N, typename T>
+hipError_t zpass_load_t(const ZpassArgs& a, const void* in, void* fields, hipStream_t st) {
+  const int cb = zpass_store_bins<N, T>(a.nbins);
+  for (int b0 = 0; b0 < a.nbins; b0 += cb) {
+    const int nb = a.nbins - b0 < cb ? a.nbins - b0 : cb;
+    const int threads = zpass_threads<N, VZN>(nb);
+    const size_t lds = (size_t)nb * zrow<N>() * sizeof(CT<T>) + (size_t)N * sizeof(CT<T>);
+    hipError_t e = allow_lds(k_zpass_load<N, T>, lds);
+    if (e != hipSuccess) return e;
+    const dim3 gs(a.nwg, a.batch);
+    k_zpass_load<N, T><<<gs, threads, lds, st>>>(static_cast<const CT<T>*>(in), static_cast<CT<T>*>(fields), nb,
+                                                a.nbins, b0, a.ppw, static_cast<const CT<T>*>(a.tw));
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 // float32 with at most 32 bins contracts on the matrix cores (float32 or
 // BF16-split inputs); otherwise on the vector ALUs
 template <int N, typename T>
@@ -3312,6 +2559,9 @@ hipError_t launch_zpass_nodal(int n, int prec, const ZpassArgs& a, hipStream_t s
 hipError_t launch_zpass_store(int n, int prec, const ZpassArgs& a, void* out, hipStream_t st) {
   MP3_DISPATCH(zpass_store_t, n, prec, a, out, st);
 }
+hipError_t launch_zpass_load(int n, int prec, const ZpassArgs& a, const void* in, void* fields, hipStream_t st) {
+  MP3_DISPATCH(zpass_load_t, n, prec, a, in, fields, st);
+}
 hipError_t launch_zpass_adjoint(int n, int prec, const ZpassArgs& a, hipStream_t st) { MP3_DISPATCH(zpass_adjoint_t, n, prec, a, st); }
 hipError_t launch_zpass_fused(int n, int prec, const ZpassArgs& a, hipStream_t st) { MP3_DISPATCH(zpass_fused_t, n, prec, a, st); }
 
@@ -3364,13 +2614,6 @@ hipError_t launch_fill_i32(int* p, long long count, int value, hipStream_t st) {
 hipError_t launch_fill_f64(double* p, long long count, double value, hipStream_t st) {
   const unsigned g = grid_for(count, 256, 8192);
   k_fill<double><<<g, 256, 0, st>>>(p, count, value);
-  return hipGetLastError();
-}
-
-hipError_t launch_lam_sym(int prec, const double* dzeta, void* lam_s, int nbins, int lmax, int batch, hipStream_t st) {
-  const dim3 gs(lmax + 1, batch);
-  if (prec) k_lam_sym<double><<<gs, 256, 0, st>>>(dzeta, static_cast<double*>(lam_s), nbins, lmax, batch);
-  else k_lam_sym<float><<<gs, 256, 0, st>>>(dzeta, static_cast<float*>(lam_s), nbins, lmax, batch);
   return hipGetLastError();
 }
 
@@ -3640,60 +2883,6 @@ hipError_t launch_fbar_subtract(int prec, const double* P, const void* jtab, int
   return hipGetLastError();
 }
 
-template <typename T, bool MF, bool SPLIT = false, bool QUAD = false>
-hipError_t gamma_contract_t(const void* fields, const void* delta, int n, const BinPair& bp, const GammaQuad& gq,
-                            double* partials, int nwg, int batch, hipStream_t st) {
-  const int threads = 1024;
-  const int nbins = bp.na + bp.nc;
-  size_t lds = GammaLds<T>(nbins).total;
-  const size_t red = Contractor<T, MF, SPLIT, QUAD>::scratch_bytes(threads);
-  if (lds < red) lds = red;
-  hipError_t e = allow_lds(k_gamma_contract<T, MF, SPLIT, QUAD>, lds);
-  if (e != hipSuccess) return e;
-  const dim3 gs(nwg, batch);
-  k_gamma_contract<T, MF, SPLIT, QUAD><<<gs, threads, lds, st>>>(static_cast<const CT<T>*>(fields),
-                                                                static_cast<const T*>(delta), n, nbins, gq, partials,
-                                                                bp.nbt, bp.a0, bp.na, bp.c0);
-  return hipGetLastError();
-}
-
-GammaQuad make_gamma_quad(const double (*m)[4], const double* wq) {
-  GammaQuad gq;
-  for (int s = 0; s < 5; ++s) {
-    for (int t = 0; t < 4; ++t) {
-      gq.m[s][t] = (float)m[s][t];
-      gq.md[s][t] = m[s][t];
-    }
-    gq.wq[s] = (float)wq[s];
-    gq.wqd[s] = wq[s];
-  }
-  return gq;
-}
-
-hipError_t launch_gamma_contract(int prec, bool split, const void* fields, const void* delta, int n,
-                                 const BinPair& bp, const double (*m)[4], const double* wq, double* partials, int nwg,
-                                 int batch, hipStream_t st) {
-  const GammaQuad gq = make_gamma_quad(m, wq);
-  const int nbins = bp.na + bp.nc;
-  if (prec) return gamma_contract_t<double, false>(fields, delta, n, bp, gq, partials, nwg, batch, st);
-  if (nbins <= 32) {
-    if (split) return gamma_contract_t<float, true, true>(fields, delta, n, bp, gq, partials, nwg, batch, st);
-    if (nbins > 16 && nbins <= 20)
-      return gamma_contract_t<float, true, false, true>(fields, delta, n, bp, gq, partials, nwg, batch, st);
-    return gamma_contract_t<float, true>(fields, delta, n, bp, gq, partials, nwg, batch, st);
-  }
-  return gamma_contract_t<float, false>(fields, delta, n, bp, gq, partials, nwg, batch, st);
-}
-
-size_t gamma_lds_need(int prec, int nbins) {
-  // the tile plus the contraction's reduction scratch (1024 threads)
-  const size_t a = prec ? GammaLds<double>(nbins).total : GammaLds<float>(nbins).total;
-  const size_t r = prec ? Contractor<double, false>::scratch_bytes(1024)
-                        : (nbins <= 32 ? Contractor<float, true>::scratch_bytes(1024)
-                                       : Contractor<float, false>::scratch_bytes(1024));
-  return a > r ? a : r;
-}
-
 hipError_t launch_reduce_partials_map(const double* partials, int nwg, const BinPair& bp, double* zeta, int l,
                                       int lmax, double scale, bool own_a, bool own_c, int batch, hipStream_t st) {
   const int nl = bp.na + bp.nc;
@@ -3701,46 +2890,6 @@ hipError_t launch_reduce_partials_map(const double* partials, int nwg, const Bin
   k_reduce_partials_map<<<gs, 256, 0, st>>>(partials, nwg, nl, zeta, l, lmax, scale, bp.nbt, bp.a0, bp.na, bp.c0,
                                             own_a ? 1 : 0, own_c ? 1 : 0);
   return hipGetLastError();
-}
-
-hipError_t launch_bin_mix(int prec, const void* F, const void* lam_s, void* U, long long n3, int nbins, int batch,
-                          hipStream_t st) {
-  const size_t lds = (size_t)nbins * nbins * (prec ? 8 : 4);
-  const dim3 gs(grid_for(n3 * nbins, 256, 16384), batch);
-  if (prec)
-    k_bin_mix<double><<<gs, 256, lds, st>>>(static_cast<const double2*>(F), static_cast<const double*>(lam_s),
-                                            static_cast<double2*>(U), n3, nbins);
-  else
-    k_bin_mix<float><<<gs, 256, lds, st>>>(static_cast<const float2*>(F), static_cast<const float*>(lam_s),
-                                           static_cast<float2*>(U), n3, nbins);
-  return hipGetLastError();
-}
-
-template <typename T>
-hipError_t gamma_adjoint_bins_t(const void* fields, const void* U, const void* delta, int n, int nbt, int b0, int nbc,
-                                const GammaQuad& gq, double wm, int nwg, int batch, void* cout, void* direct,
-                                hipStream_t st) {
-  const size_t lds = GammaBinsLds<T>(nbc).total;
-  hipError_t e = allow_lds(k_gamma_adjoint_bins<T>, lds);
-  if (e != hipSuccess) return e;
-  const dim3 gs(nwg, batch);
-  k_gamma_adjoint_bins<T><<<gs, 512, lds, st>>>(static_cast<const CT<T>*>(fields), static_cast<const CT<T>*>(U),
-                                                static_cast<const T*>(delta), n, nbt, b0, nbc, gq, (T)wm,
-                                                static_cast<CT<T>*>(cout), static_cast<T*>(direct));
-  return hipGetLastError();
-}
-
-hipError_t launch_gamma_adjoint_bins(int prec, const void* fields, const void* U, const void* delta, int n, int nbt,
-                                     int b0, int nbc, const double (*m)[4], const double* wq, double wm, int nwg,
-                                     int batch, void* cout, void* direct, hipStream_t st) {
-  const GammaQuad gq = make_gamma_quad(m, wq);
-  if (prec)
-    return gamma_adjoint_bins_t<double>(fields, U, delta, n, nbt, b0, nbc, gq, wm, nwg, batch, cout, direct, st);
-  return gamma_adjoint_bins_t<float>(fields, U, delta, n, nbt, b0, nbc, gq, wm, nwg, batch, cout, direct, st);
-}
-
-size_t gamma_adjoint_bins_lds_need(int prec, int nbc) {
-  return prec ? GammaBinsLds<double>(nbc).total : GammaBinsLds<float>(nbc).total;
 }
 
 hipError_t launch_gather_source(int prec, const void* fields, const int* tcell, const void* twt, const float* w,
@@ -3817,52 +2966,6 @@ hipError_t launch_primary_dw(int prec, const long long* off, int batch, long lon
   if (prec) k_primary_dw<double><<<gr, 256, 0, st>>>(off, batch, np_total, FJ, W, SF, static_cast<double*>(dw));
   else k_primary_dw<float><<<gr, 256, 0, st>>>(off, batch, np_total, FJ, W, SF, static_cast<float*>(dw));
   return hipGetLastError();
-}
-
-template <typename T, bool FUSED, bool MF, bool QUAD>
-hipError_t gamma_adjoint_v(const void* fields, const void* delta, const void* lam_s, int n, int nbins,
-                           const GammaQuad& gq, double wm, int nwg, int batch, void* cout, void* direct,
-                           double* partials, hipStream_t st) {
-  const int threads = sizeof(T) == 4 ? 1024 : 512;
-  size_t lds = GammaAdjLds<T>(nbins).total;
-  if (FUSED) {
-    const size_t red = Contractor<T, MF, false, QUAD>::scratch_bytes(threads);
-    if (lds < red) lds = red;
-  }
-  hipError_t e = allow_lds(k_gamma_adjoint<T, FUSED, MF, QUAD>, lds);
-  if (e != hipSuccess) return e;
-  const dim3 gs(nwg, batch);
-  k_gamma_adjoint<T, FUSED, MF, QUAD><<<gs, threads, lds, st>>>(
-      static_cast<const CT<T>*>(fields), static_cast<const T*>(delta), static_cast<const T*>(lam_s), n, nbins, gq, (T)wm,
-      static_cast<CT<T>*>(cout), static_cast<T*>(direct), partials);
-  return hipGetLastError();
-}
-
-hipError_t launch_gamma_adjoint(int prec, const void* fields, const void* delta, const void* lam_s, int n, int nbins,
-                                const double (*m)[4], const double* wq, double wm, int nwg, int batch, void* cout,
-                                void* direct, double* partials, hipStream_t st) {
-  GammaQuad gq;
-  for (int s = 0; s < 5; ++s) {
-    for (int t = 0; t < 4; ++t) {
-      gq.m[s][t] = (float)m[s][t];
-      gq.md[s][t] = m[s][t];
-    }
-    gq.wq[s] = (float)wq[s];
-    gq.wqd[s] = wq[s];
-  }
-  if (nbins > AGP * AGH) return hipErrorInvalidValue;
-#define MP3_GAMMA_ADJ(T, F, M, Q) \
-  gamma_adjoint_v<T, F, M, Q>(fields, delta, lam_s, n, nbins, gq, wm, nwg, batch, cout, direct, partials, st)
-  // partials != NULL: also contract for zeta (float32 on the matrix cores)
-  if (prec) return partials ? MP3_GAMMA_ADJ(double, true, false, false) : MP3_GAMMA_ADJ(double, false, false, false);
-  if (!partials) return MP3_GAMMA_ADJ(float, false, false, false);
-  return nbins > 16 ? MP3_GAMMA_ADJ(float, true, true, true) : MP3_GAMMA_ADJ(float, true, true, false);
-#undef MP3_GAMMA_ADJ
-}
-
-size_t gamma_adjoint_lds_need(int prec, int nbins) {
-  if (nbins > AGP * AGH) return (size_t)1 << 40;
-  return prec ? GammaAdjLds<double>(nbins).total : GammaAdjLds<float>(nbins).total;
 }
 
 }  // namespace mp3

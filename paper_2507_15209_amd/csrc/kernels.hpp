@@ -94,46 +94,30 @@ struct BinPair {
   int nbt, a0, na, c0, nc;
 };
 
-// grid summation with connection coefficients (5-point Gauss-Legendre per cell);
-// m[s][t] = B3(xi_s + 1 - t), wq[s] node weights on [0, 1]; partials over the
-// pair's (na + nc)^2 local bin pairs
-hipError_t launch_gamma_contract(int prec, bool split, const void* fields, const void* delta, int n,
-                                 const BinPair& bp, const double (*m)[4], const double* wq, double* partials, int nwg,
-                                 int batch, hipStream_t st);
-// LDS bytes of a contraction tile holding nbins bins
-size_t gamma_lds_need(int prec, int nbins);
+// The grid summation with connection coefficients along one axis as points:
+//   sum_{s,t} gamma(s, t) p(x) f(x + s) g(x + t), summed over x, =
+//   sum_x sum_k (P_k p)(x) (F_k f)(x) (F_k g)(x),
+// (F_k f)(x) = sum_t f[k][t] f(x + off + t), (P_k p)(x) = sum_t p[k][t] p(x + off + t) (the point's
+// weight inside), and as the band g[d][j] = gamma(-(j - halo), -(j - halo) - d), d = 0 .. halo.
+struct BandRule {
+  int q, taps, off, halo;
+  double f[5][5], p[5][5], g[4][7];
+};
+constexpr int kBandBins = 32;   // bins of one contraction launch (more: pairs of chunks)
+// forward partials [batch][nwg][nl^2] over the pair's local bins, fields bin-interleaved (band.hip)
+hipError_t launch_band_contract(int prec, const void* fields, const void* prim, int n, const BinPair& bp,
+                                const BandRule& rule, double* partials, int nwg, int batch, hipStream_t st);
+// adjoint sources of fields in the cotangent's eigenbasis (eigenvalues lam_d [batch][nbt]) added to
+// out [batch][N^3][nbt] (zeroed by the caller), wm times the primary's share added to direct
+hipError_t launch_band_adjoint(int prec, const void* fields, const void* prim, const void* lam_d, int n, int nbt,
+                               const BandRule& rule, double wm, int batch, void* out, void* direct, hipStream_t st);
 // zeta += the pair's partials at their stored-bin positions (cross block always,
 // diagonal blocks when owned)
 hipError_t launch_reduce_partials_map(const double* partials, int nwg, const BinPair& bp, double* zeta, int l,
                                       int lmax, double scale, bool own_a, bool own_c, int batch, hipStream_t st);
-// U[x][b] = sum_b' lam_s[b][b'] F[x][b'] over bin-interleaved fields
-hipError_t launch_bin_mix(int prec, const void* F, const void* lam_s, void* U, long long n3, int nbins, int batch,
-                          hipStream_t st);
-// grid-Gamma adjoint of stored bins b0 .. b0 + nbc - 1 from the fields and
-// their mix U: sources into cout, wm times the chunk's primary share into direct
-hipError_t launch_gamma_adjoint_bins(int prec, const void* fields, const void* U, const void* delta, int n, int nbt,
-                                     int b0, int nbc, const double (*m)[4], const double* wq, double wm, int nwg,
-                                     int batch, void* cout, void* direct, hipStream_t st);
-size_t gamma_adjoint_bins_lds_need(int prec, int nbc);
-
-// grid summation with connection coefficients as a stencil over the shifts
-// -halo .. halo per axis (stencil.hip): gamma(s, t) at g[s + 3][t + 3];
-// halo 2 (Daubechies-4, support 3) or 3 (cubic B-spline, support 4)
-struct StencilGamma {
-  double g[7][7];
-  int halo;
-};
-// partials over the pair's local bins, as launch_gamma_contract
-hipError_t launch_stencil_contract(int prec, const void* fields, const void* delta, int n, const BinPair& bp,
-                                   const StencilGamma& sg, double* partials, int nwg, int batch, hipStream_t st);
-size_t stencil_lds_need(int prec, int halo, int nl);
-// adjoint of stored bins b0 .. b0 + nbc - 1 from the fields and their mix U: sources
-// into cout (per-bin layout), wm times the primary's share into direct
-hipError_t launch_stencil_adjoint(int prec, const void* fields, const void* U, const void* delta, int n, int nbt,
-                                  int b0, int nbc, const StencilGamma& sg, double wm, int nwg, int batch, void* cout,
-                                  void* direct, hipStream_t st);
-size_t stencil_adjoint_lds_need(int prec, int halo, int nbc);
 hipError_t launch_zpass_store(int n, int prec, const ZpassArgs& a, void* out, hipStream_t st);
+// z transform of bin-interleaved sources [batch][N^3][nbins] into fields [batch][nbins][N^3]
+hipError_t launch_zpass_load(int n, int prec, const ZpassArgs& a, const void* in, void* fields, hipStream_t st);
 // counting sort of the particles by (2^shift)^3-cell tile of their mock; offs
 // gets batch * (n >> shift)^3 + 1 exclusive tile offsets
 hipError_t launch_tile_sort(const float* pos, const long long* off, int batch, long long np_total, int n, double sc,
@@ -168,8 +152,6 @@ size_t zpass_fused_lds_need(int n, int prec, int nbins);
 hipError_t launch_fill(int prec, void* p, long long count, double value, hipStream_t st);
 hipError_t launch_fill_f64(double* p, long long count, double value, hipStream_t st);
 hipError_t launch_fill_i32(int* p, long long count, int value, hipStream_t st);
-// lam_s[l][batch][nbins^2] for every l <= lmax
-hipError_t launch_lam_sym(int prec, const double* dzeta, void* lam_s, int nbins, int lmax, int batch, hipStream_t st);
 // eigen-decomposition of every symmetrised cotangent (float64 Jacobi, nbins <= 64): eigenvalues
 // lam_d[l][batch][nbins] at the plan precision, eigenvectors evec[l][batch][nbins][nbins] (columns)
 hipError_t launch_lam_eig(int prec, const double* dzeta, void* lam_d, double* evec, int nbins, int lmax, int batch,
@@ -203,15 +185,6 @@ hipError_t launch_tap_records(int prec, const float* pos, const int* perm, long 
 hipError_t launch_fbar_adjoint(int prec, const double* dzeta, const void* jtab, int nq2, int nbp, int nbins, int lmax,
                                const void* dhat, int n, double scale, double* h, void* G, int batch, const void* phi,
                                const Acf& acf, hipStream_t st);
-// grid-Gamma adjoint for one (l, m): adds the transposed-quadrature sources
-// into cout ([batch][nbins][N^3], zeroed by the caller) and wm times the
-// primary's share into direct; fields bin-interleaved, at most 20 bins.
-// partials != NULL: also writes the forward contraction's partials
-// ([batch][nwg][nbins^2], as launch_gamma_contract) from the same node values
-hipError_t launch_gamma_adjoint(int prec, const void* fields, const void* delta, const void* lam_s, int n, int nbins,
-                                const double (*m)[4], const double* wq, double wm, int nwg, int batch, void* cout,
-                                void* direct, double* partials, hipStream_t st);
-size_t gamma_adjoint_lds_need(int prec, int nbins);
 hipError_t launch_primary_dw(int prec, const long long* off, int batch, long long np_total, const double* FJ,
                              const double* W, const double* SF, void* dw, hipStream_t st);
 hipError_t launch_normalise(int prec, void* eps, const double* W, long long n3, int batch, hipStream_t st);

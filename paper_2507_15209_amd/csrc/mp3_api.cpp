@@ -23,8 +23,6 @@ struct mp3_plan_s {
   void* tw = nullptr;    // [n] complex
   size_t elt = 4, celt = 8;
   int device = 0;
-  double gm[5][4] = {{0}};   // grid-Gamma quadrature: B3 tap weights at the nodes
-  double gw[5] = {0};        // and node weights
   int tune[MP3_NTUNE] = {4096, 4096, 0, 8, 2048, 0, 0, 0};   // launch-shape knobs (mp3_tune_knob)
   int basis = 0, binning = 0;
   unsigned kflags = 0;
@@ -32,7 +30,7 @@ struct mp3_plan_s {
   void* phi = nullptr;      // [n] real per-axis phi-hat factors when MP3_KF_PHI_HAT
   double* btab = nullptr;   // Daubechies-4 basis: phi at the dyadic points (NULL for the B-spline)
   mp3::Acf acf{{2416.0 / 5040.0, 1191.0 / 5040.0, 120.0 / 5040.0, 1.0 / 5040.0}};   // basis autocorrelation
-  mp3::StencilGamma sgam{};  // Daubechies-4 connection coefficients (grid summation as a stencil)
+  mp3::BandRule band{};      // the basis' connection coefficients as points and as a band (grid summation)
   std::vector<mp3::ItemRec> items;   // every (l, m >= 0) of the plan, index l (l + 1) / 2 + m
   mp3::ItemRec* items_dev = nullptr; // the same table on the device
   // optional per-pass HIP event timing
@@ -70,8 +68,8 @@ constexpr size_t kLdsLimit = 160 * 1024;
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct Layout {
-  size_t dprim, flag, pplain, aux, xib, fields_u, counter;
-  size_t evec, jrot;   // nodal gradient: the cotangents' eigenvectors and the rotated radial tables
+  size_t dprim, flag, pplain, aux, xib, counter;
+  size_t evec, jrot;   // gradients: the cotangents' eigenvectors and the rotated radial tables
   int group;   // (l, m) items per launch of the one-sweep nodal passes
   size_t off, W, S, dhat, fields, partials, G, direct, lam, fields_i, perm, counts, offs, cursor, power;
   size_t src, fj, hq, SF, tcell, twt;
@@ -121,11 +119,8 @@ int item_group(const mp3_plan_s* p) {
   return g < total ? g : total;
 }
 
-// the grid-Gamma adjoint as the shift stencil (Daubechies-4 always; the
-// B-spline unless the node-quadrature kernel is selected)
-bool gamma_stencil_adjoint(const mp3_plan_s* p) {
-  return p->basis == MP3_BASIS_DAUBECHIES4 || p->tune[MP3_TUNE_GAMMA_ADJOINT] == 0;
-}
+// whether the gradient's radial tables are rotated into the cotangent's eigenbasis
+bool rotated_tables(const mp3_plan_s* p) { return p->summation != MP3_SUM_GRID_GAMMA || p->nbins > 1; }
 
 Layout layout(const mp3_plan_s* p, long long np_total = 0) {
   Layout L{};
@@ -159,8 +154,9 @@ Layout layout(const mp3_plan_s* p, long long np_total = 0) {
   L.direct = take(B * n3 * p->elt);
   L.lam = take((size_t)(p->lmax + 1) * B * nb2 * p->elt);
   L.counter = take(sizeof(int));
-  if (p->summation == MP3_SUM_NODAL || p->summation == MP3_SUM_PARTICLE) {
-    L.evec = take((size_t)(p->lmax + 1) * B * nb2 * sizeof(double));
+  L.evec = take((size_t)(p->lmax + 1) * B * nb2 * sizeof(double));
+  // one bin: the eigenbasis is the bin itself, the plan's own table serves (rotated_tables)
+  if (rotated_tables(p)) {
     L.jrot = take((size_t)(p->lmax + 1) * B * (size_t)p->nq2 * p->nbp * p->elt);
   }
   // primary vertex filtered by the top-hat window (grid forms with smoothing)
@@ -171,10 +167,6 @@ Layout layout(const mp3_plan_s* p, long long np_total = 0) {
   L.aux = take((size_t)2 * kMaxAux * sizeof(double));
   L.xib = take(B * (size_t)p->nbins * sizeof(double));
   if (p->summation != MP3_SUM_NODAL) L.fields_i = take(B * (size_t)p->nbins * n3 * p->celt);
-  // grid-Gamma adjoint by bin chunks: the bin mix U of the fields
-  if (p->summation == MP3_SUM_GRID_GAMMA &&
-      (gamma_stencil_adjoint(p) || mp3::gamma_adjoint_lds_need(p->prec, p->nbins) > kLdsLimit))
-    L.fields_u = take(B * (size_t)p->nbins * n3 * p->celt);
   if (p->summation == MP3_SUM_PARTICLE) {
     const size_t nt = (size_t)(p->n / 4) * (p->n / 4) * (p->n / 4) * B + 1;
     L.perm = take((size_t)(np_total > 0 ? np_total : 1) * sizeof(int));
@@ -207,6 +199,51 @@ Layout layout(const mp3_plan_s* p, long long np_total = 0) {
 bool pow2_supported(int n) { return n == 16 || n == 32 || n == 64 || n == 128 || n == 256 || n == 512; }
 
 constexpr unsigned kKnownFlags = MP3_KF_PHI_HAT | MP3_KF_CHECK_FINITE;
+
+void band_coefficients(const double (*g)[7], mp3::BandRule& r) {
+  for (int d = 0; d <= r.halo; ++d)
+    for (int j = -r.halo; j <= r.halo; ++j) {
+      const int s = -j, t = -j - d;
+      r.g[d][j + r.halo] = t >= -3 && t <= 3 ? g[s + 3][t + 3] : 0.0;
+    }
+}
+
+void b3_band(mp3::BandRule& r) {
+  r = mp3::BandRule{};
+  r.q = 4;
+  r.taps = 4;
+  r.off = -1;
+  r.halo = 3;
+  double xi[4], w[4];
+  mp3::spline_points(xi, w);
+  for (int s = 0; s < 4; ++s)
+    for (int t = 0; t < 4; ++t) {
+      r.f[s][t] = mp3::bspline3(xi[s] + 1.0 - t);
+      r.p[s][t] = w[s] * r.f[s][t];
+    }
+  double g[7][7];
+  mp3::b3_gamma(g);
+  band_coefficients(g, r);
+}
+
+void d4_band(mp3::BandRule& r) {
+  r = mp3::BandRule{};
+  r.q = 5;
+  r.taps = 5;
+  r.off = -2;
+  r.halo = 2;
+  double g5[5][5], val[5], vec[5][5], g[7][7] = {{0}};
+  mp3::d4_gamma(g5);
+  mp3::symmetric_eigen5(g5, val, vec);
+  for (int s = 0; s < 5; ++s) {
+    for (int t = 0; t < 5; ++t) {
+      r.f[s][t] = vec[t][s];
+      g[s + 1][t + 1] = g5[s][t];
+    }
+    r.p[s][2] = val[s];
+  }
+  band_coefficients(g, r);
+}
 
 // checks shared by mp3_plan_create and mp3_window_table
 int validate_desc(const mp3_plan_desc* d) {
@@ -334,29 +371,19 @@ int forward_dft(const mp3_plan_s* p, const void* delta, void* ws, const Layout& 
 
 int item_index(int l, int m) { return l * (l + 1) / 2 + m; }
 
-// the symmetrised cotangent of multipole l: [batch][nbins^2] real
-void* lam_at(const mp3_plan_s* p, void* ws, const Layout& L, int l) {
-  return at(ws, L.lam + (size_t)l * p->batch * p->nbins * p->nbins * p->elt);
-}
-
 // the cotangent's eigenvalues of multipole l after lam_eig_all: [batch][nbins] real
 void* lam_d_at(const mp3_plan_s* p, void* ws, const Layout& L, int l) {
   return at(ws, L.lam + (size_t)l * p->batch * p->nbins * p->elt);
 }
 
-// symmetrised cotangents of every l into the workspace (one launch)
-int lam_all(const mp3_plan_s* p, const double* dzeta, void* ws, const Layout& L, hipStream_t st) {
-  MP3_HIP(mp3::launch_lam_sym(p->prec, dzeta, at(ws, L.lam), p->nbins, p->lmax, p->batch, st), "lambda");
-  return MP3_OK;
-}
-
-// The nodal gradient runs in the eigenbasis of each symmetrised cotangent
+// The gradients run in the eigenbasis of each symmetrised cotangent
 // lam_s = V diag(d) V^T (per l and mock): the eigenvalues d into the lambda
 // slot, V into L.evec, and the radial tables rotated by V into L.jrot.
 int lam_eig_all(const mp3_plan_s* p, const double* dzeta, void* ws, const Layout& L, hipStream_t st) {
   double* evec = reinterpret_cast<double*>(at(ws, L.evec));
   MP3_HIP(mp3::launch_lam_eig(p->prec, dzeta, at(ws, L.lam), evec, p->nbins, p->lmax, p->batch, st),
           "cotangent eigenbasis");
+  if (!rotated_tables(p)) return MP3_OK;
   MP3_HIP(mp3::launch_rotate_jtab(p->prec, p->jtab, at(ws, L.jrot), evec, p->nq2, p->nbins, p->nbp, p->lmax,
                                   p->batch, st),
           "rotated radial tables");
@@ -502,7 +529,6 @@ int mp3_plan_create(const mp3_plan_desc* d, mp3_plan_t* out) {
   p->edges.assign(d->edges, d->edges + d->nbins + 1);
   p->nq2 = mp3::nq2_count(p->n);
   p->nbp = (p->nbins + 3) / 4 * 4;
-  mp3::gamma_quadrature(p->gm, p->gw);
   p->elt = p->prec ? sizeof(double) : sizeof(float);
   p->celt = 2 * p->elt;
   hipGetDevice(&p->device);
@@ -557,21 +583,14 @@ int mp3_plan_create(const mp3_plan_desc* d, mp3_plan_t* out) {
     }
   }
   const size_t ib = p->items.size() * sizeof(mp3::ItemRec);
-  if (p->basis == MP3_BASIS_BSPLINE3) {
-    mp3::b3_gamma(p->sgam.g);
-    p->sgam.halo = 3;
-  }
+  if (p->basis == MP3_BASIS_BSPLINE3) b3_band(p->band);
   hipError_t e4 = hipMalloc(&p->items_dev, ib);
   if (e4 == hipSuccess) e4 = hipMemcpy(p->items_dev, p->items.data(), ib, hipMemcpyHostToDevice);
   if (p->basis == MP3_BASIS_DAUBECHIES4 && e4 == hipSuccess) {
     std::vector<double> tab;
     mp3::d4_table(mp3::kD4Level, tab);
     mp3::d4_autocorr(tab, mp3::kD4Level, p->acf.a);
-    double g5[5][5];
-    mp3::d4_gamma(g5);
-    for (int s = 0; s < 5; ++s)
-      for (int t = 0; t < 5; ++t) p->sgam.g[s + 1][t + 1] = g5[s][t];
-    p->sgam.halo = 2;
+    d4_band(p->band);
     e4 = hipMalloc(&p->btab, tab.size() * sizeof(double));
     if (e4 == hipSuccess) e4 = hipMemcpy(p->btab, tab.data(), tab.size() * sizeof(double), hipMemcpyHostToDevice);
   }
@@ -743,28 +762,22 @@ int mp3_multipole_fields(mp3_plan_t p, const void* delta, int32_t l, int32_t m, 
 
 namespace {
 
-// The grid-Gamma contraction's bin pairs: every bin in one tile when the LDS
-// holds them, else the bins in chunks and one contraction per pair of
-// chunks, each diagonal block owned by exactly one pair.
+// The grid-Gamma contraction's bin pairs: every bin at once up to kBandBins,
+// else the bins in chunks and one contraction per pair of chunks, each
+// diagonal block owned by exactly one pair.
 struct GammaPass {
   mp3::BinPair bp;
   bool own_a, own_c;
 };
 
-// LDS bytes of the forward contraction tile holding nl local bins (the basis' kernel)
-size_t contract_lds_need(const mp3_plan_s* p, int nl) {
-  return p->basis == MP3_BASIS_DAUBECHIES4 ? mp3::stencil_lds_need(p->prec, 2, nl) : mp3::gamma_lds_need(p->prec, nl);
-}
-
 std::vector<GammaPass> gamma_passes(const mp3_plan_s* p) {
   const int nb = p->nbins;
   std::vector<GammaPass> out;
-  if (contract_lds_need(p, nb) <= kLdsLimit) {
+  if (nb <= mp3::kBandBins) {
     out.push_back({{nb, 0, nb, 0, 0}, true, true});
     return out;
   }
-  int cs = nb / 2;
-  while (cs > 1 && contract_lds_need(p, 2 * cs) > kLdsLimit) --cs;
+  const int cs = mp3::kBandBins / 2;
   const int k = (nb + cs - 1) / cs;
   for (int i = 0; i < k; ++i) {
     for (int j = i + 1; j < k; ++j) {
@@ -775,27 +788,12 @@ std::vector<GammaPass> gamma_passes(const mp3_plan_s* p) {
   return out;
 }
 
-// bins per chunk of the chunked grid-Gamma adjoint
-int gamma_adjoint_chunk(const mp3_plan_s* p) {
-  int c = p->nbins;
-  if (gamma_stencil_adjoint(p)) {
-    while (c > 1 && mp3::stencil_adjoint_lds_need(p->prec, p->sgam.halo, c) > kLdsLimit) --c;
-    return c;
-  }
-  while (c > 1 && mp3::gamma_adjoint_bins_lds_need(p->prec, c) > kLdsLimit) --c;
-  return c;
-}
-
 // the contraction of the stored bin-interleaved fields of one (l, m), all passes, into zeta
 int gamma_contract_all(const mp3_plan_s* p, const void* Fi, const void* prim, double* partials, int gwg, double* zeta,
                        int l, double scale, hipStream_t st) {
   for (const GammaPass& g : gamma_passes(p)) {
     MP3_HIP(timed(p, MP3_PASS_GAMMA, st, [&] {
-              if (p->basis == MP3_BASIS_DAUBECHIES4)
-                return mp3::launch_stencil_contract(p->prec, Fi, prim, p->n, g.bp, p->sgam, partials, gwg, p->batch,
-                                                    st);
-              return mp3::launch_gamma_contract(p->prec, p->split, Fi, prim, p->n, g.bp, p->gm, p->gw, partials, gwg,
-                                                p->batch, st);
+              return mp3::launch_band_contract(p->prec, Fi, prim, p->n, g.bp, p->band, partials, gwg, p->batch, st);
             }),
             "grid-Gamma contraction");
     MP3_HIP(mp3::launch_reduce_partials_map(partials, gwg, g.bp, zeta, l, p->lmax, scale, g.own_a, g.own_c, p->batch,
@@ -897,18 +895,21 @@ int zeta_particle(mp3_plan_t p, const float* pos, const float* w, const int64_t*
   return MP3_OK;
 }
 
+// workgroups per mock of the grid-Gamma contraction: at most one per column of cells
+int gamma_wgs(const mp3_plan_s* p) {
+  const long long cols = (long long)(p->n / 2) * (p->n / 4) * 8;
+  const long long g = (long long)contract_wgs(p);
+  return (int)(g < cols ? g : cols);
+}
+
 // grid summation with connection coefficients:
 // zeta_l = (4 pi / N^3) int delta_B sum_m atilde_b1 conj(atilde_b2) d^3u
 int zeta_gamma(mp3_plan_t p, const void* delta, double* zeta, void* ws, const Layout& L, hipStream_t st) {
-  const int nb2 = p->nbins * p->nbins;
   const double n3 = (double)p->n * p->n * p->n;
   void* F = at(ws, L.fields);
   void* Fi = at(ws, L.fields_i);
   double* partials = reinterpret_cast<double*>(at(ws, L.partials));
-  const long long tiles = (long long)(p->n / 4) * (p->n / 4) * (p->n / 4);
-  long long gwg = (long long)contract_wgs(p);
-  if (gwg < 1) gwg = 1;
-  if (gwg > tiles) gwg = tiles;
+  const int gwg = gamma_wgs(p);
   for (int l = 0; l <= p->lmax; ++l) {
     for (int m = 0; m <= l; ++m) {
       if (int s = fields_xy(p, ws, L, F, item_index(l, m), 1, st)) return s;
@@ -921,7 +922,7 @@ int zeta_gamma(mp3_plan_t p, const void* delta, double* zeta, void* ws, const La
       z.batch = p->batch;
       MP3_HIP(timed(p, MP3_PASS_Z_STORE, st, [&] { return mp3::launch_zpass_store(p->n, p->prec, z, Fi, st); }), "z pass (store)");
       const double wm = m == 0 ? 1.0 : 2.0;
-      if (int s = gamma_contract_all(p, Fi, delta, partials, (int)gwg, zeta, l, wm * kFourPi / n3, st)) return s;
+      if (int s = gamma_contract_all(p, Fi, delta, partials, gwg, zeta, l, wm * kFourPi / n3, st)) return s;
     }
   }
   return MP3_OK;
@@ -1073,11 +1074,6 @@ int backward_particle(mp3_plan_t p, const void* delta, const double* dzeta, void
   return MP3_OK;
 }
 
-// Adjoint of the grid summation with connection coefficients: the nodal
-// adjoint with the primary's weight delta_x and the pointwise products
-// replaced by the quadrature of the B-spline reconstructions (k_gamma_adjoint
-// produces c_b and the direct term per (l, m)); the same adjoint transforms
-// and deposit chain rule follow.
 // One sweep of the particle form: the forward's and the adjoint's per-call
 // steps run once, and per (l, m) the stored fields feed both the contraction
 // (gather_contract) and the adjoint sources (gather_source).
@@ -1199,14 +1195,15 @@ int value_and_grad_particle(mp3_plan_t p, const void* delta, const double* dzeta
   return MP3_OK;
 }
 
-// zeta != NULL: one sweep, the adjoint kernel also contracts the node values
-// for zeta (float32 or float64 inputs, not the BF16-split option)
+// Adjoint of the grid summation with connection coefficients: the nodal
+// adjoint with the primary's weight delta_x and the pointwise products
+// replaced by the trilinear form (k_band_adjoint adds c_b and the direct term
+// per (l, m), from the fields in the cotangent's eigenbasis); the same adjoint
+// transforms and deposit chain rule follow.  zeta != NULL: one sweep, the
+// stored fields are also contracted and the value is turned back to the bins.
 int backward_gamma(mp3_plan_t p, const void* delta, const double* dzeta, void* ddelta, const float* pos,
                    const float* w, const int64_t* np_off, void* dw, void* ws, size_t wsb, void* stream,
                    double* zeta = nullptr) {
-  // tiles that do not hold every bin: the adjoint by bin chunks (and, for
-  // zeta, the contraction by pairs of chunks)
-  const bool chunked = gamma_stencil_adjoint(p) || mp3::gamma_adjoint_lds_need(p->prec, p->nbins) > kLdsLimit;
   long long np_total = 0, np_max = 0;
   if (dw) {
     if (int s = check_offsets(p, np_off, &np_total, &np_max)) return s;
@@ -1218,7 +1215,7 @@ int backward_gamma(mp3_plan_t p, const void* delta, const double* dzeta, void* d
   const long long n3 = (long long)p->n * p->n * p->n;
   if (int s = check_finite(p, ws, L.flag, st, delta, n3 * p->batch, p->prec)) return s;
   if (int s = forward_dft(p, delta, ws, L, st)) return s;
-  if (int s = lam_all(p, dzeta, ws, L, st)) return s;
+  if (int s = lam_eig_all(p, dzeta, ws, L, st)) return s;
   int ps = MP3_OK;
   const void* prim = primary_field(p, delta, ws, L, st, &ps);
   if (ps) return ps;
@@ -1231,14 +1228,12 @@ int backward_gamma(mp3_plan_t p, const void* delta, const double* dzeta, void* d
   if (zeta) MP3_HIP(mp3::launch_fill_f64(zeta, (long long)p->batch * (p->lmax + 1) * nb2, 0.0, st), "zero zeta");
   MP3_HIP(mp3::launch_fill(p->prec, G, 2 * n3 * p->batch, 0.0, st), "zero G");
   MP3_HIP(mp3::launch_fill(p->prec, direct, n3 * p->batch, 0.0, st), "zero direct");
-  const long long tiles = (long long)(p->n / 4) * (p->n / 4) * (p->n / 4);
-  long long gwg = (long long)contract_wgs(p);
-  if (gwg < 1) gwg = 1;
-  if (gwg > tiles) gwg = tiles;
+  const int gwg = gamma_wgs(p);
+  const bool rotated = rotated_tables(p);
   for (int l = 0; l <= p->lmax; ++l) {
     for (int m = 0; m <= l; ++m) {
       const double wm = m == 0 ? 1.0 : 2.0;
-      if (int s = fields_xy(p, ws, L, F, item_index(l, m), 1, st)) return s;
+      if (int s = fields_xy(p, ws, L, F, item_index(l, m), 1, st, rotated)) return s;
       mp3::ZpassArgs z{};
       z.fields = F;
       z.tw = p->tw;
@@ -1247,44 +1242,28 @@ int backward_gamma(mp3_plan_t p, const void* delta, const double* dzeta, void* d
       z.ppw = L.ppw;
       z.batch = p->batch;
       MP3_HIP(timed(p, MP3_PASS_Z_STORE, st, [&] { return mp3::launch_zpass_store(p->n, p->prec, z, Fi, st); }), "z pass (store)");
+      if (zeta)
+        if (int s = gamma_contract_all(p, Fi, prim, partials, gwg, zeta, l, wm * kFourPi / (double)n3, st)) return s;
+      // bin-interleaved sources into F (free once stored), their transform into Fi
       MP3_HIP(mp3::launch_fill(p->prec, F, 2 * n3 * p->batch * p->nbins, 0.0, st), "zero sources");
-      if (chunked) {
-        if (zeta)
-          if (int s = gamma_contract_all(p, Fi, prim, partials, (int)gwg, zeta, l, wm * kFourPi / (double)n3, st))
-            return s;
-        void* U = at(ws, L.fields_u);
-        MP3_HIP(mp3::launch_bin_mix(p->prec, Fi, lam_at(p, ws, L, l), U, n3, p->nbins, p->batch, st), "bin mix");
-        const int cb = gamma_adjoint_chunk(p);
-        for (int b0 = 0; b0 < p->nbins; b0 += cb) {
-          const int nbc = std::min(cb, p->nbins - b0);
-          MP3_HIP(timed(p, MP3_PASS_GAMMA, st, [&] {
-                    if (gamma_stencil_adjoint(p))
-                      return mp3::launch_stencil_adjoint(p->prec, Fi, U, prim, p->n, p->nbins, b0, nbc, p->sgam, wm,
-                                                         (int)gwg, p->batch, F, direct, st);
-                    return mp3::launch_gamma_adjoint_bins(p->prec, Fi, U, prim, p->n, p->nbins, b0, nbc, p->gm, p->gw,
-                                                          wm, (int)gwg, p->batch, F, direct, st);
-                  }),
-                  "grid-Gamma adjoint (bin chunk)");
-        }
-      } else {
-        MP3_HIP(timed(p, MP3_PASS_GAMMA, st, [&] {
-                  return mp3::launch_gamma_adjoint(p->prec, Fi, prim, lam_at(p, ws, L, l), p->n, p->nbins, p->gm, p->gw, wm,
-                                                   (int)gwg, p->batch, F, direct, partials, st);
-                }),
-                "grid-Gamma adjoint");
-        if (zeta)
-          MP3_HIP(mp3::launch_reduce_partials(partials, (int)gwg, nb2, zeta, l, p->lmax, wm * kFourPi / (double)n3,
-                                              p->batch, st),
-                  "reduce");
-      }
-      MP3_HIP(timed(p, MP3_PASS_Z_ADJOINT, st, [&] { return mp3::launch_fft_z(p->n, p->prec, +1, F, F, p->batch * p->nbins, p->tw, st); }),
+      MP3_HIP(timed(p, MP3_PASS_GAMMA, st, [&] {
+                return mp3::launch_band_adjoint(p->prec, Fi, prim, lam_d_at(p, ws, L, l), p->n, p->nbins, p->band, wm,
+                                                p->batch, F, direct, st);
+              }),
+              "grid-Gamma adjoint");
+      MP3_HIP(timed(p, MP3_PASS_Z_ADJOINT, st, [&] { return mp3::launch_zpass_load(p->n, p->prec, z, F, Fi, st); }),
               "adjoint z pass");
-      MP3_HIP(timed(p, MP3_PASS_X, st, [&] { return mp3::launch_fft_x(p->n, p->prec, +1, F, p->batch * p->nbins, p->tw, p->tune[MP3_TUNE_FFT_X_PLAN], st); }),
+      MP3_HIP(timed(p, MP3_PASS_X, st, [&] { return mp3::launch_fft_x(p->n, p->prec, +1, Fi, p->batch * p->nbins, p->tw, p->tune[MP3_TUNE_FFT_X_PLAN], st); }),
               "adjoint x pass");
-      mp3::FilterArgs a = filter_args(p, ws, L, F, G, item_index(l, m), 1);
+      mp3::FilterArgs a = filter_args(p, ws, L, Fi, G, item_index(l, m), 1, rotated);
       MP3_HIP(timed(p, MP3_PASS_ADJOINT, st, [&] { return mp3::launch_adjoint_y(p->n, p->prec, a, st); }), "adjoint window pass");
     }
   }
+  // the value was summed over the rotated fields: back to the bins
+  if (zeta && rotated)
+    MP3_HIP(mp3::launch_rotate_zeta(zeta, reinterpret_cast<const double*>(at(ws, L.evec)), p->nbins, p->lmax, p->batch,
+                                    st),
+            "zeta out of the eigenbasis");
   MP3_HIP(timed(p, MP3_PASS_DFT, st, [&] { return mp3::launch_fft3d(p->n, p->prec, -1, false, G, G, p->batch, p->tw, st); }), "adjoint final FFT");
   if (int s = filter_direct(p, direct, ws, L, st)) return s;
   MP3_HIP(mp3::launch_grad_combine(p->prec, direct, G, ddelta, n3 * p->batch, kFourPi / (double)n3, st), "combine");
@@ -1352,7 +1331,7 @@ int mp3_zeta_value_and_grad(mp3_plan_t p, const void* delta, const double* dzeta
   if (p->summation == MP3_SUM_PARTICLE)
     return value_and_grad_particle(p, delta, dzeta, zeta, ddelta, pos, w, np_off, dw, ws, wsb,
                                    static_cast<hipStream_t>(stream));
-  if (p->summation == MP3_SUM_GRID_GAMMA && !p->split)
+  if (p->summation == MP3_SUM_GRID_GAMMA)
     return backward_gamma(p, delta, dzeta, ddelta, pos, w, np_off, dw, ws, wsb, stream, zeta);
   const int storage = p->prec;
   const bool one_sweep = p->summation == MP3_SUM_NODAL && !p->split && p->nbins <= 32 &&

@@ -333,14 +333,62 @@ double bspline3(double u) {
   return 0.0;
 }
 
-void gamma_quadrature(double m[5][4], double wq[5]) {
-  std::vector<double> x, w;
-  gauss_legendre(5, x, w);
-  for (int s = 0; s < 5; ++s) {
-    const double xi = 0.5 * (x[s] + 1.0);
-    wq[s] = 0.5 * w[s];
-    for (int t = 0; t < 4; ++t) m[s][t] = bspline3(xi + 1.0 - t);
+void spline_points(double xi[4], double w[4]) {
+  // The rule on [0, 1], repeated on every unit cell, that integrates every
+  // spline of degree 9 with two continuous derivatives at the knots over the
+  // line: on one cell its error may be c (p'(1) - p'(0)), which telescopes.
+  // A symmetric rule is then left with the even powers 0 .. 8 of the distance
+  // from the centre, five equations for two nodes, two weights and c
+  // (c = -0.00111577849...); the product of three cubic B-spline sums is such
+  // a spline.  Solved to 20 digits (one solution with both nodes inside).
+  const double a = 0.1494769255865451373286, b = 0.4036169140199854453879;
+  const double u = 0.2909893942748533416796, v = 0.2090106057251466583204;
+  xi[0] = 0.5 - b;
+  xi[1] = 0.5 - a;
+  xi[2] = 0.5 + a;
+  xi[3] = 0.5 + b;
+  w[0] = w[3] = v;
+  w[1] = w[2] = u;
+}
+
+void symmetric_eigen5(const double a[5][5], double val[5], double vec[5][5]) {
+  // cyclic Jacobi
+  double m[5][5];
+  for (int i = 0; i < 5; ++i)
+    for (int j = 0; j < 5; ++j) {
+      m[i][j] = 0.5 * (a[i][j] + a[j][i]);
+      vec[i][j] = i == j ? 1.0 : 0.0;
+    }
+  for (int sweep = 0; sweep < 60; ++sweep) {
+    double off = 0.0;
+    for (int p = 0; p < 5; ++p)
+      for (int q = p + 1; q < 5; ++q) off += m[p][q] * m[p][q];
+    if (off == 0.0) break;
+    for (int p = 0; p < 5; ++p)
+      for (int q = p + 1; q < 5; ++q) {
+        if (m[p][q] == 0.0) continue;
+        const double th = (m[q][q] - m[p][p]) / (2.0 * m[p][q]);
+        const double t = (th >= 0.0 ? 1.0 : -1.0) / (std::fabs(th) + std::sqrt(th * th + 1.0));
+        const double c = 1.0 / std::sqrt(t * t + 1.0), s = t * c;
+        for (int k = 0; k < 5; ++k) {
+          const double x = m[k][p], y = m[k][q];
+          m[k][p] = c * x - s * y;
+          m[k][q] = s * x + c * y;
+        }
+        for (int k = 0; k < 5; ++k) {
+          const double x = m[p][k], y = m[q][k];
+          m[p][k] = c * x - s * y;
+          m[q][k] = s * x + c * y;
+        }
+        m[p][q] = m[q][p] = 0.0;
+        for (int k = 0; k < 5; ++k) {
+          const double x = vec[k][p], y = vec[k][q];
+          vec[k][p] = c * x - s * y;
+          vec[k][q] = s * x + c * y;
+        }
+      }
   }
+  for (int i = 0; i < 5; ++i) val[i] = m[i][i];
 }
 
 double ylm_norm(int l, int m) {

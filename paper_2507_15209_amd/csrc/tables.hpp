@@ -31,7 +31,9 @@ void b3_gamma(double g[7][7]);
 double ylm_norm(int l, int m);
 // centred cubic B-spline
 double bspline3(double u);
-// 5-point Gauss-Legendre nodes xi_s on [0, 1]: m[s][t] = B3(xi_s + 1 - t), weights wq[s]
-void gamma_quadrature(double m[5][4], double wq[5]);
+// the 4-point rule on [0, 1] that is exact for splines of degree 9 with two continuous derivatives
+void spline_points(double xi[4], double w[4]);
+// eigenvalues and eigenvectors (columns) of a symmetric 5x5 matrix
+void symmetric_eigen5(const double a[5][5], double val[5], double vec[5][5]);
 
 }  // namespace mp3
