@@ -27,7 +27,7 @@ DEVICE = [f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang", "-p
 def commands() -> list[list[str]]:
     objs = []
     cmds = []
-    for src, dev in (("kernels.hip", True), ("stats.hip", True), ("band.hip", True), ("static_scratch.hip", True),
+    for src, dev in (("kernels.hip", True), ("stats.hip", True), ("band.hip", True), ("scatter.hip", True), ("static_scratch.hip", True),
                      ("mp3_api.cpp", False),
                      ("tables.cpp", False)):
         obj = os.path.join(BUILD, src + ".o")

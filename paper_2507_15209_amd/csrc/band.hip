@@ -15,6 +15,7 @@
 // quarter of the contraction's products and half of the interpolation.
 #include "fft_core.hpp"
 #include "kernels.hpp"
+#include "mfma.hpp"
 
 #include <hip/hip_runtime.h>
 
@@ -23,25 +24,6 @@
 namespace mp3 {
 
 namespace {
-
-typedef float band_f4 __attribute__((ext_vector_type(4)));
-typedef double band_d4 __attribute__((ext_vector_type(4)));
-
-template <typename T> struct acc4;
-template <> struct acc4<float> { using type = band_f4; };
-template <> struct acc4<double> { using type = band_d4; };
-
-// D += A B over four k: lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16]
-__device__ __forceinline__ band_f4 mfma16(float a, float b, band_f4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ band_d4 mfma16(double a, double b, band_d4 c) {
-  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
-// row of D register i of lane l (column l % 16)
-template <typename T> __device__ __forceinline__ int mfma_row(int lane, int i);
-template <> __device__ __forceinline__ int mfma_row<float>(int lane, int i) { return 4 * (lane >> 4) + i; }
-template <> __device__ __forceinline__ int mfma_row<double>(int lane, int i) { return 4 * i + (lane >> 4); }
 
 // BandRule in the working precision (kernel argument)
 template <typename T, int Q, int TP, int H>
@@ -63,10 +45,6 @@ RuleT<T, Q, TP, H> rule_of(const BandRule& r) {
 }
 
 __device__ __forceinline__ int wrap_n(int i, int n) { return i & (n - 1); }   // n is a power of two
-
-// consecutive tasks on one XCD (workgroups are dealt to the 8 XCDs in turn), so that
-// neighbouring tiles find each other's halo in that XCD's L2
-__device__ __forceinline__ int xcd_order(int i, int n) { return n % 8 == 0 ? (i & 7) * (n / 8) + (i >> 3) : i; }
 
 template <typename T, int Q, int TP, int TY, int NH>
 struct ContractLds {

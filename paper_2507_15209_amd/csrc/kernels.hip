@@ -962,6 +962,16 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(MF ? 4
 // ---------------------------------------------------------------------------
 // particle summation
 // ---------------------------------------------------------------------------
+// the next (z, bin) of a thread walking a pencil's [z][bin] elements by blockDim
+__device__ __forceinline__ void next_element(int& z, int& b, int dz, int db, int nbins) {
+  z += dz;
+  b += db;
+  if (b >= nbins) {
+    b -= nbins;
+    ++z;
+  }
+}
+
 // z pass that stores the fields bin-interleaved, out[mock][cell][b], so that a
 // B-spline tap reads all bins of a node contiguously.  One launch handles bins
 // b0 .. b0 + nbins - 1 of nbt (the pencil of those bins is held in LDS).
@@ -980,6 +990,8 @@ __global__ void __launch_bounds__(512) k_zpass_store(const c2<T>* fields, c2<T>*
   const int p1 = min(p0 + ppw, N * N);
   const c2<T>* fmock = fields + (mock * nbt + b0) * N3;
   c2<T>* omock = out + mock * nbt * N3;
+  // the thread's first (z, bin) of a pencil and its step, without a division per element
+  const int zt = threadIdx.x / nbins, bt = threadIdx.x % nbins, dz = blockDim.x / nbins, db = blockDim.x % nbins;
   c2<T> vpre[prefetch_rounds<N, VZN>()][F::RMAX];
   if (p0 < p1) prefetch_pencil<N, T, VZN>(fmock + (long long)p0 * N, N3, nbins, vpre);
   for (int p = p0; p < p1; ++p) {
@@ -993,16 +1005,17 @@ __global__ void __launch_bounds__(512) k_zpass_store(const c2<T>* fields, c2<T>*
     transform_pencil_bins<N, T, VZN>(fmock + (long long)p * N, N3, nbins, A, tws, vcur);
     __syncthreads();
     c2<T>* dst = omock + (long long)p * N * nbt + b0;
+    int z = zt, b = bt;
     for (int idx = threadIdx.x; idx < N * nbins; idx += blockDim.x) {
-      const int z = idx / nbins, b = idx - z * nbins;
       dst[(long long)z * nbt + b] = A[b * RS + lds_pos<true>(z)];
+      next_element(z, b, dz, db, nbins);
     }
   }
 }
 
 // The adjoint's first axis from bin-interleaved sources: the transpose of
 // k_zpass_store.  A pencil of every bin is read in one contiguous run, turned
-// into LDS rows and z-transformed from there into [b][x][y][qz].
+// into LDS rows and z-transformed from there into [b][x][y][qz].  Bound by HBM.
 template <int N, typename T>
 __global__ void __launch_bounds__(512) k_zpass_load(const c2<T>* in, c2<T>* fields, int nbins, int nbt, int b0,
                                                      int ppw, const c2<T>* tw) {
@@ -1020,12 +1033,15 @@ __global__ void __launch_bounds__(512) k_zpass_load(const c2<T>* in, c2<T>* fiel
   c2<T>* fmock = fields + (mock * nbt + b0) * N3;
   const int nbc = blockDim.x / F::TPC;
   const int rounds = pencil_rounds<N, VZN>(nbins);
+  const int zt = threadIdx.x / nbins, bt = threadIdx.x % nbins, dz = blockDim.x / nbins, db = blockDim.x % nbins;
   for (int p = p0; p < p1; ++p) {
     const c2<T>* src = imock + (long long)p * N * nbt + b0;
     __syncthreads();
+    int z = zt, b = bt;
+#pragma unroll 4
     for (int idx = threadIdx.x; idx < N * nbins; idx += blockDim.x) {
-      const int z = idx / nbins, b = idx - z * nbins;
       A[b * RS + lds_pos<true>(z)] = src[(long long)z * nbt + b];
+      next_element(z, b, dz, db, nbins);
     }
     __syncthreads();
     for (int rr = 0; rr < rounds; ++rr) {
@@ -1895,218 +1911,6 @@ __global__ void __launch_bounds__(256) k_gather_source(const c2<T>* fields, cons
   }
 }
 
-// Adjoint source on the grid, c_b(x) = sum_i B3(u_i - x) s_b(i), by pulling:
-// a workgroup owns an 8^3-node tile and BC bins, and every thread owns two of
-// its nodes with BC complex accumulators in registers (no atomics on values).
-// Candidates are the particles of the 4^3-cell sort tiles covering cells
-// x0 - 4 .. x0 + 11 per axis, taken 256 at a time through a prefix sum over
-// the 64 tiles' counts.  The ones whose stencil reaches the tile (first tap
-// at local offset -3 .. 7 per axis) are staged in LDS with their tap weights
-// and sources, bucketed by first-tap cell (11^3 buckets, counting sort), and
-// each node then visits the 4^3 buckets that can reach it.  Batches of up to
-// SCQ particles keep the LDS bounded in dense regions.  Every node has one
-// owner: the tile is written once, empty tiles as zeros.
-__device__ __forceinline__ int tap_offset(int base, int o, int n) {
-  int r = (base - o) % n;
-  return r < 0 ? r + n : r;
-}
-
-constexpr int SCT = 8;                    // owner tile side (nodes)
-constexpr int SCB = (SCT + 3) * (SCT + 3) * (SCT + 3);   // first-tap buckets
-// bins per owner workgroup: float32 8, or 10 where that saves a pass over the
-// candidates (17..20 bins: two passes instead of three, 23 % faster at 512^3);
-// float64 4 up to 8 bins, 10 beyond (scatter_bc_f64)
-template <typename T> constexpr int scatter_bc() { return sizeof(T) == 4 ? 8 : 4; }
-inline int scatter_bc_f32(int nbins) { return (nbins + 9) / 10 < (nbins + 7) / 8 ? 10 : 8; }
-// float64 beyond 8 bins: 10 bins per workgroup (two workgroups per CU by LDS)
-// instead of 4, so that 20 bins take two passes over the candidates, not five
-inline int scatter_bc_f64(int nbins) { return nbins > 8 ? 10 : 4; }
-template <typename T> constexpr int scatter_q() { return sizeof(T) == 4 ? 256 : 256; }
-
-template <typename T, int BC>
-struct ScatterLds {
-  size_t key, wt, sv, cnt, ord, total;
-  __host__ __device__ ScatterLds() {
-    constexpr int Q = scatter_q<T>();
-    size_t o = 0;
-    auto take = [&](size_t b) { size_t r = o; o = (o + b + 15) & ~(size_t)15; return r; };
-    key = take((size_t)Q * sizeof(int));
-    wt = take((size_t)Q * 12 * sizeof(T));
-    sv = take((size_t)Q * BC * sizeof(c2<T>));
-    cnt = take((size_t)(SCB + 1) * sizeof(int));
-    ord = take((size_t)Q * sizeof(int));
-    total = o;
-  }
-};
-
-template <typename T, int BC>
-__global__ void __launch_bounds__(256) k_scatter_source(const int* tcell, const T* twt, const int* toff,
-                                                         const c2<T>* src, int n, int nbins, int nchunk, c2<T>* out) {
-  constexpr int TO = SCT, TB = SCT + 3;
-  constexpr int NODES = TO * TO * TO;
-  constexpr int Q = scatter_q<T>();
-  extern __shared__ __align__(16) char smem[];
-  const ScatterLds<T, BC> L;
-  int* qkey = reinterpret_cast<int*>(smem + L.key);          // bucket of each staged particle
-  T* qwt = reinterpret_cast<T*>(smem + L.wt);                // [q][3][4] tap weights
-  c2<T>* qsv = reinterpret_cast<c2<T>*>(smem + L.sv);        // [q][BC] sources
-  int* cnt = reinterpret_cast<int*>(smem + L.cnt);           // bucket counts, then starts
-  int* ord = reinterpret_cast<int*>(smem + L.ord);           // staged particles in bucket order
-  __shared__ int pre[65];
-  __shared__ int cbase[64];
-  __shared__ int qn;
-  __shared__ int wsum[4];
-  const int tid = threadIdx.x;
-  const int no = n / TO;
-  const int ot = blockIdx.x;
-  const int oxi = ot / (no * no), oyi = (ot / no) % no, ozi = ot % no;
-  const int o0[3] = {oxi * TO, oyi * TO, ozi * TO};
-  const int mock = blockIdx.y / nchunk, b0 = (blockIdx.y % nchunk) * BC;
-  const int nbc = min(BC, nbins - b0);
-  const int ntd = n / 4;
-  const long long ns = (long long)ntd * ntd * ntd;
-  if (tid < 64) {
-    const int sx = wrapi(2 * oxi - 1 + tid / 16, ntd), sy = wrapi(2 * oyi - 1 + (tid / 4) % 4, ntd);
-    const int sz = wrapi(2 * ozi - 1 + tid % 4, ntd);
-    const long long tile = mock * ns + ((long long)sx * ntd + sy) * ntd + sz;
-    const int a = toff[tile];
-    cbase[tid] = a;
-    pre[tid + 1] = toff[tile + 1] - a;
-  }
-  if (tid == 0) qn = 0;
-  __syncthreads();
-  if (tid == 0) {
-    pre[0] = 0;
-    for (int c = 1; c <= 64; ++c) pre[c] += pre[c - 1];
-  }
-  __syncthreads();
-  const int total = pre[64];
-  // owned nodes: tid and tid + 256
-  c2<T> acc[2][BC];
-#pragma unroll
-  for (int h = 0; h < 2; ++h)
-#pragma unroll
-    for (int bb = 0; bb < BC; ++bb) acc[h][bb] = mk<T>(0, 0);
-  for (int t0 = 0; t0 <= total; t0 += blockDim.x) {
-    // stage this pass's candidates that reach the tile
-    const int t = t0 + tid;
-    if (t < total) {
-      int lo = 0, hi = 64;                      // pre[lo] <= t < pre[hi]
-      while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (pre[mid] <= t) lo = mid; else hi = mid;
-      }
-      const int k = cbase[lo] + (t - pre[lo]);
-      const int cell = tcell[k];
-      const int cb[3] = {(cell & 1023) - 1, ((cell >> 10) & 1023) - 1, (cell >> 20) - 1};   // first tap per axis
-      int rl[3];
-      bool reach = cell >= 0;
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        const int r = tap_offset(cb[d], o0[d], n);
-        rl[d] = r < TO ? r : r - n;             // -3 .. 7 when the stencil reaches the tile
-        reach = reach && (r < TO || r >= n - 3);
-      }
-      if (reach) {
-        const int q = atomicAdd(&qn, 1);
-        qkey[q] = ((rl[0] + 3) * TB + (rl[1] + 3)) * TB + (rl[2] + 3);
-        const T* wr = twt + (long long)k * 12;
-#pragma unroll
-        for (int e = 0; e < 12; ++e) qwt[q * 12 + e] = wr[e];
-        const c2<T>* sp = src + (long long)k * nbins + b0;
-#pragma unroll
-        for (int bb = 0; bb < BC; ++bb) qsv[q * BC + bb] = bb < nbc ? sp[bb] : mk<T>(0, 0);
-      }
-    }
-    __syncthreads();
-    const int nq = qn;
-    __syncthreads();                              // every thread has read qn before it changes
-    // pull when the next pass might overflow the stage, and at the end
-    if (nq > Q - (int)blockDim.x || t0 + (int)blockDim.x > total) {
-      for (int c = tid; c <= SCB; c += blockDim.x) cnt[c] = 0;
-      __syncthreads();
-      for (int q = tid; q < nq; q += blockDim.x) atomicAdd(&cnt[qkey[q] + 1], 1);
-      __syncthreads();
-      // exclusive starts: cnt[c] = first slot of bucket c (c = 0 .. SCB)
-      {
-        constexpr int PER = (SCB + 1 + 255) / 256;
-        int loc[PER];
-        int run = 0;
-#pragma unroll
-        for (int e = 0; e < PER; ++e) {
-          const int c = tid * PER + e;
-          loc[e] = c <= SCB ? cnt[c] : 0;
-          run += loc[e];
-        }
-        // block-wide exclusive scan of the per-thread sums
-        int incl = run;
-        for (int o = 1; o < 64; o <<= 1) {
-          const int v = __shfl_up(incl, o, 64);
-          if ((tid & 63) >= o) incl += v;
-        }
-        if ((tid & 63) == 63) wsum[tid >> 6] = incl;
-        __syncthreads();
-        int woff = 0;
-        for (int w = 0; w < (tid >> 6); ++w) woff += wsum[w];
-        int ex = woff + incl - run;
-#pragma unroll
-        for (int e = 0; e < PER; ++e) {
-          const int c = tid * PER + e;
-          ex += loc[e];
-          if (c <= SCB) cnt[c] = ex;              // sum of the counts of buckets 0 .. c - 1
-        }
-      }
-      __syncthreads();
-      // cnt[c] is now the start of bucket c (counts were stored at c + 1)
-      for (int q = tid; q < nq; q += blockDim.x) {
-        const int slot = atomicAdd(&cnt[qkey[q]], 1);
-        ord[slot] = q;
-      }
-      __syncthreads();
-      // after the fill cnt[c] is the end of bucket c = start of bucket c + 1;
-      // bucket c spans [c == 0 ? 0 : cnt[c - 1], cnt[c])
-      // the 4 buckets (z taps c = 0..3) of one (a, b) row are consecutive keys,
-      // so their particles form one contiguous range of ord
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int node = tid + h * 256;
-        const int i = node / (TO * TO), j = (node / TO) % TO, kz = node % TO;
-        for (int a = 0; a < 4; ++a) {
-          for (int b = 0; b < 4; ++b) {
-            const int rowc = ((i - a + 3) * TB + (j - b + 3)) * TB + 3 + kz;   // key of tap c = 0
-            const int k0 = rowc - 3;
-            const int e0 = k0 == 0 ? 0 : cnt[k0 - 1], e1 = cnt[rowc];
-            for (int e = e0; e < e1; ++e) {
-              const int q = ord[e];
-              const int c = rowc - qkey[q];
-              const T w = qwt[(q * 3 + 0) * 4 + a] * qwt[(q * 3 + 1) * 4 + b] * qwt[(q * 3 + 2) * 4 + c];
-#pragma unroll
-              for (int bb = 0; bb < BC; ++bb) {
-                const c2<T> v = qsv[q * BC + bb];
-                acc[h][bb].x += w * v.x;
-                acc[h][bb].y += w * v.y;
-              }
-            }
-          }
-        }
-      }
-      __syncthreads();
-      if (tid == 0) qn = 0;
-      __syncthreads();
-    }
-  }
-  const long long n3 = (long long)n * n * n;
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int node = tid + h * 256;
-    const int i = node / (TO * TO), j = (node / TO) % TO, k = node % TO;
-    const long long cell = ((long long)(o0[0] + i) * n + o0[1] + j) * n + o0[2] + k;
-#pragma unroll
-    for (int bb = 0; bb < BC; ++bb)
-      if (bb < nbc) out[((long long)mock * nbins + b0 + bb) * n3 + cell] = acc[h][bb];
-  }
-}
-
 // zeta[mock][l][g(i)][g(j)] += scale sum_w partials[mock][w][i][j] for the local
 // pairs (i, j) of a chunk-pair contraction that this pass owns: the cross
 // block always, the diagonal block of the first chunk when own_a, of the
@@ -2907,30 +2711,6 @@ hipError_t launch_gather_source(int prec, const void* fields, const int* tcell, 
                                                static_cast<const float*>(lam_d), n, nbins, (float)wm, FJ,
                                                static_cast<float2*>(src));
   return hipGetLastError();
-}
-
-template <typename T, int BC>
-hipError_t scatter_source_t(const int* tcell, const void* twt, const int* toff, const void* src, int n, int nbins,
-                            int batch, void* out, hipStream_t st) {
-  const int no = n / SCT;
-  const int nchunk = (nbins + BC - 1) / BC;
-  const size_t lds = ScatterLds<T, BC>().total;
-  hipError_t e = allow_lds(k_scatter_source<T, BC>, lds);
-  if (e != hipSuccess) return e;
-  const dim3 gs(no * no * no, batch * nchunk);
-  k_scatter_source<T, BC><<<gs, 256, lds, st>>>(tcell, static_cast<const T*>(twt), toff, static_cast<const CT<T>*>(src),
-                                                n, nbins, nchunk, static_cast<CT<T>*>(out));
-  return hipGetLastError();
-}
-
-hipError_t launch_scatter_source(int prec, const int* tcell, const void* twt, const int* toff, const void* src, int n,
-                                 int nbins, int batch, void* out, hipStream_t st) {
-  if (prec) {
-    if (scatter_bc_f64(nbins) == 10) return scatter_source_t<double, 10>(tcell, twt, toff, src, n, nbins, batch, out, st);
-    return scatter_source_t<double, scatter_bc<double>()>(tcell, twt, toff, src, n, nbins, batch, out, st);
-  }
-  if (scatter_bc_f32(nbins) == 10) return scatter_source_t<float, 10>(tcell, twt, toff, src, n, nbins, batch, out, st);
-  return scatter_source_t<float, 8>(tcell, twt, toff, src, n, nbins, batch, out, st);
 }
 
 hipError_t launch_tap_records(int prec, const float* pos, const int* perm, long long np_total, int n, double sc,
