@@ -148,11 +148,18 @@ def _source_digest():
     return hashlib.sha256(src).hexdigest()[:16]
 
 
+def _zpass_mode(name):
+    """The MODE argument of a k_zpass<N, T, MAXNB, MODE, ...> kernel name (0 adjoint, 1 one sweep, 2 forward)."""
+    if "k_zpass<" not in name:
+        return None
+    return int(name.split("k_zpass<")[1].split(",")[3])
+
+
 # kernels whose traffic is summarised: pass name -> kernel-name test
 PMC_KERNELS = {"x": lambda k: "k_fft_strided" in k, "filter": lambda k: "k_filter_y" in k,
-               "z_nodal": lambda k: "k_zpass_nodal" in k,
-               "z_adjoint": lambda k: "k_zpass_adjoint" in k and "false, false, false>" in k,
-               "z_fused": lambda k: "k_zpass_adjoint" in k and ", true," in k.split(">")[0],
+               "z_nodal": lambda k: _zpass_mode(k) == 2,
+               "z_adjoint": lambda k: _zpass_mode(k) == 0,
+               "z_fused": lambda k: _zpass_mode(k) == 1,
                "adjoint": lambda k: "k_adjoint_y" in k}
 
 

@@ -19,6 +19,7 @@
 // the 512 KB-strided x axis is left to the one-field-per-tile plain pass.
 #include "fft_core.hpp"
 #include "kernels.hpp"
+#include "mfma.hpp"
 
 #include <hip/hip_runtime.h>
 
@@ -568,19 +569,20 @@ __device__ __forceinline__ void transform_pencil_bins(const c2<T>* src, long lon
   }
 }
 
-typedef float mp3_f4 __attribute__((ext_vector_type(4)));
+typedef mfma_f4 mp3_f4;
 
 // Nodal contraction on the matrix cores (float32, nbins <= 32): per pair of z,
 // one v_mfma_f32_16x16x4f32 per upper-triangular 16x16 block of (b1, b2),
 // k = (z, re/im):  A[b1][k] = delta_z c_k(a_b1(z)),  B[k][b2] = c_k(a_b2(z)).
 // Lane l supplies A[l%16][l/16] and B[l/16][l%16]; D register i of lane l is
 // C[4 (l/16) + i][l%16].
-struct MfmaAcc {
-  mp3_f4 c00, c01, c11;
+template <typename T> struct MfmaAcc {
+  typename acc4<T>::type c00, c01, c11;
 };
 
-__device__ __forceinline__ void mfma_contract_pencil(const float2* A, const float* dl, int nbins, int RS, int N,
-                                                     MfmaAcc& acc) {
+template <typename T>
+__device__ __forceinline__ void mfma_contract_pencil(const c2<T>* A, const T* dl, int nbins, int RS, int N,
+                                                     MfmaAcc<T>& acc) {
   const int lane = threadIdx.x & 63;
   const int w = threadIdx.x >> 6;
   const int nw = blockDim.x >> 6;
@@ -590,25 +592,26 @@ __device__ __forceinline__ void mfma_contract_pencil(const float2* A, const floa
   const bool ok0 = col < nbins, ok1 = 16 + col < nbins;
   // lanes of bins beyond nbins read row 0 (finite values): they only feed
   // entries of P that the reduction drops, and the loads need no mask
-  const float* r0 = reinterpret_cast<const float*>(A + (ok0 ? col : 0) * RS) + comp;
-  const float* r1 = reinterpret_cast<const float*>(A + (ok1 ? 16 + col : 0) * RS) + comp;
+  const T* r0 = reinterpret_cast<const T*>(A + (ok0 ? col : 0) * RS) + comp;
+  const T* r1 = reinterpret_cast<const T*>(A + (ok1 ? 16 + col : 0) * RS) + comp;
   for (int zp = w; zp < N / 2; zp += nw) {
     const int z = 2 * zp + zz;
     const int off = 2 * lds_pos<true>(z);
-    const float d = dl[z];
-    const float v0 = r0[off];
-    acc.c00 = __builtin_amdgcn_mfma_f32_16x16x4f32(d * v0, v0, acc.c00, 0, 0, 0);
+    const T d = dl[z];
+    const T v0 = r0[off];
+    acc.c00 = mfma16(d * v0, v0, acc.c00);
     if (two) {
-      const float v1 = r1[off];
-      acc.c01 = __builtin_amdgcn_mfma_f32_16x16x4f32(d * v0, v1, acc.c01, 0, 0, 0);
-      acc.c11 = __builtin_amdgcn_mfma_f32_16x16x4f32(d * v1, v1, acc.c11, 0, 0, 0);
+      const T v1 = r1[off];
+      acc.c01 = mfma16(d * v0, v1, acc.c01);
+      acc.c11 = mfma16(d * v1, v1, acc.c11);
     }
   }
 }
 
 // the same for z in [z0, z1) (even bounds), all by the calling wave
-__device__ __forceinline__ void mfma_contract_pencil_range(const float2* A, const float* dl, int nbins, int RS, int z0,
-                                                           int z1, MfmaAcc& acc) {
+template <typename T>
+__device__ __forceinline__ void mfma_contract_pencil_range(const c2<T>* A, const T* dl, int nbins, int RS, int z0,
+                                                           int z1, MfmaAcc<T>& acc) {
   const int lane = threadIdx.x & 63;
   const int col = lane & 15, kq = lane >> 4;
   const int zz = kq >> 1, comp = kq & 1;
@@ -616,19 +619,19 @@ __device__ __forceinline__ void mfma_contract_pencil_range(const float2* A, cons
   const bool ok0 = col < nbins, ok1 = 16 + col < nbins;
   // lanes of bins beyond nbins read row 0 (finite values): they only feed
   // entries of P that the reduction drops, and the loads need no mask
-  const float* r0 = reinterpret_cast<const float*>(A + (ok0 ? col : 0) * RS) + comp;
-  const float* r1 = reinterpret_cast<const float*>(A + (ok1 ? 16 + col : 0) * RS) + comp;
+  const T* r0 = reinterpret_cast<const T*>(A + (ok0 ? col : 0) * RS) + comp;
+  const T* r1 = reinterpret_cast<const T*>(A + (ok1 ? 16 + col : 0) * RS) + comp;
 #pragma unroll 8
   for (int zp = z0 / 2; zp < z1 / 2; ++zp) {
     const int z = 2 * zp + zz;
     const int off = 2 * lds_pos<true>(z);
-    const float d = dl[z];
-    const float v0 = r0[off];
-    acc.c00 = __builtin_amdgcn_mfma_f32_16x16x4f32(d * v0, v0, acc.c00, 0, 0, 0);
+    const T d = dl[z];
+    const T v0 = r0[off];
+    acc.c00 = mfma16(d * v0, v0, acc.c00);
     if (two) {
-      const float v1 = r1[off];
-      acc.c01 = __builtin_amdgcn_mfma_f32_16x16x4f32(d * v0, v1, acc.c01, 0, 0, 0);
-      acc.c11 = __builtin_amdgcn_mfma_f32_16x16x4f32(d * v1, v1, acc.c11, 0, 0, 0);
+      const T v1 = r1[off];
+      acc.c01 = mfma16(d * v0, v1, acc.c01);
+      acc.c11 = mfma16(d * v1, v1, acc.c11);
     }
   }
 }
@@ -648,7 +651,7 @@ __device__ __forceinline__ void pair_group(int beta, int& g1, int& g2) {
 }
 
 __device__ __forceinline__ void mfma_contract_4x4(const float2* A, const float* dl, int nbins, int RS, int K,
-                                                  MfmaAcc& acc) {
+                                                  MfmaAcc<float>& acc) {
   const int lane = threadIdx.x & 63;
   const int w = threadIdx.x >> 6;
   const int nw = blockDim.x >> 6;
@@ -675,7 +678,7 @@ __device__ __forceinline__ void mfma_contract_4x4(const float2* A, const float* 
 
 // the same for z in [z0, z1) (even bounds), all by the calling wave
 __device__ __forceinline__ void mfma_contract_4x4_range(const float2* A, const float* dl, int nbins, int RS, int z0,
-                                                        int z1, MfmaAcc& acc) {
+                                                        int z1, MfmaAcc<float>& acc) {
   const int lane = threadIdx.x & 63;
   const int beta = lane >> 2, i = lane & 3;
   int g1 = 0, g2 = 0;
@@ -731,7 +734,7 @@ __device__ __forceinline__ mp3_f4 mfma3(const mp3_s4& ah, const mp3_s4& al, cons
 // K must be a multiple of 8.  Lane l supplies A[l%16][4 (l/16) + j] and
 // B[4 (l/16) + j][l%16], j = 0..3: k = 2 (z - z0) + comp over z = z0 + 2 (l/16) + {0, 1}.
 __device__ __forceinline__ void mfma_contract_bf16x3(const float2* A, const float* dl, int nbins, int RS, int K,
-                                                     MfmaAcc& acc) {
+                                                     MfmaAcc<float>& acc) {
   const int lane = threadIdx.x & 63;
   const int w = threadIdx.x >> 6;
   const int nw = blockDim.x >> 6;
@@ -778,7 +781,7 @@ struct Contractor {
   int bb1 = 0, bb2 = 0, zc = 0;
   bool has_item = false;
   T acc[MF ? 1 : 16];
-  MfmaAcc macc;
+  MfmaAcc<T> macc;
 
   __device__ void init(int nbins) {
     pb.init(nbins, blockDim.x);
@@ -789,7 +792,7 @@ struct Contractor {
     }
 #pragma unroll
     for (int i = 0; i < (MF ? 1 : 16); ++i) acc[i] = (T)0;
-    macc.c00 = mp3_f4{0.f, 0.f, 0.f, 0.f};
+    macc.c00 = typename acc4<T>::type{0, 0, 0, 0};
     macc.c01 = macc.c00;
     macc.c11 = macc.c00;
   }
@@ -801,7 +804,7 @@ struct Contractor {
     } else if constexpr (MF && QUAD) {
       mfma_contract_4x4(reinterpret_cast<const float2*>(A), reinterpret_cast<const float*>(w), nbins, RS, K, macc);
     } else if constexpr (MF) {
-      mfma_contract_pencil(reinterpret_cast<const float2*>(A), reinterpret_cast<const float*>(w), nbins, RS, K, macc);
+      mfma_contract_pencil<T>(A, w, nbins, RS, K, macc);
     } else if (has_item) {
       const int b1o = 4 * bb1, b2o = 4 * bb2;
       for (int z = zc; z < K; z += pb.zch) {
@@ -824,13 +827,12 @@ struct Contractor {
 
   // matrix-core forms only: z in [z0, z1) by the calling wave alone
   __device__ void add_range(const c2<T>* A, const T* w, int nbins, int RS, int z0, int z1) {
-    static_assert(MF && !SPLIT, "range contraction: matrix-core float32 forms");
+    static_assert(MF && !SPLIT, "range contraction: matrix-core forms with full inputs");
     if constexpr (QUAD)
       mfma_contract_4x4_range(reinterpret_cast<const float2*>(A), reinterpret_cast<const float*>(w), nbins, RS, z0, z1,
                               macc);
     else
-      mfma_contract_pencil_range(reinterpret_cast<const float2*>(A), reinterpret_cast<const float*>(w), nbins, RS, z0,
-                                 z1, macc);
+      mfma_contract_pencil_range<T>(A, w, nbins, RS, z0, z1, macc);
   }
 
   // LDS bytes finish() needs as scratch
@@ -867,7 +869,7 @@ struct Contractor {
       const int lane = tid & 63, w = tid >> 6, nw = blockDim.x >> 6;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int row = 4 * (lane >> 4) + i, col = lane & 15;
+        const int row = mfma_row<T>(lane, i), col = lane & 15;
         red[((w * 3 + 0) * 16 + row) * 16 + col] = (double)macc.c00[i];
         red[((w * 3 + 1) * 16 + row) * 16 + col] = (double)macc.c01[i];
         red[((w * 3 + 2) * 16 + row) * 16 + col] = (double)macc.c11[i];
@@ -906,58 +908,6 @@ struct Contractor {
     }
   }
 };
-
-template <int N, typename T, bool MF, bool SPLIT = false, bool QUAD = false>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(MF ? 4 : 1))) k_zpass_nodal(
-    const c2<T>* fields, const T* delta, double* partials, int nbins, int ppw, const c2<T>* tw) {
-  using F = Fft<N, VZN>;
-  constexpr int RS = zrow<N>();
-  constexpr long long N3 = (long long)N * N * N;
-  extern __shared__ __align__(16) char smem[];
-  c2<T>* A = reinterpret_cast<c2<T>*>(smem);
-  c2<T>* tws = A + nbins * RS;
-  T* dl = reinterpret_cast<T*>(tws + N);
-  const int tid = threadIdx.x;
-  const long long mock = blockIdx.y;
-  stage_twiddles<N, T>(tw, tws);
-  Contractor<T, MF, SPLIT, QUAD> ctr;
-  ctr.init(nbins);
-  const int p0 = blockIdx.x * ppw;
-  const int p1 = min(p0 + ppw, N * N);
-  const c2<T>* fmock = fields + mock * nbins * N3;
-  c2<T> vpre[prefetch_rounds<N, VZN>()][F::RMAX];
-  T dpre[DPRE];
-  const T* dmock = delta + mock * N3;
-  if (p0 < p1) {
-    prefetch_pencil<N, T, VZN>(fmock + (long long)p0 * N, N3, nbins, vpre);
-    prefetch_delta<N, T>(dmock + (long long)p0 * N, dpre);
-  }
-  for (int p = p0; p < p1; ++p) {
-    // this pencil's data moves to vcur; the next pencil's loads are issued
-    // before the transform so they stay in flight for the whole iteration
-    c2<T> vcur[prefetch_rounds<N, VZN>()][F::RMAX];
-#pragma unroll
-    for (int q = 0; q < prefetch_rounds<N, VZN>(); ++q)
-#pragma unroll
-      for (int r = 0; r < F::RMAX; ++r) vcur[q][r] = vpre[q][r];
-#pragma unroll
-    for (int k = 0; k < DPRE; ++k) {
-      const int z = tid + k * blockDim.x;
-      if (z < N) dl[z] = dpre[k];
-    }
-    if (p + 1 < p1) {
-      prefetch_pencil<N, T, VZN>(fmock + (long long)(p + 1) * N, N3, nbins, vpre);
-      prefetch_delta<N, T>(dmock + (long long)(p + 1) * N, dpre);
-    }
-    __syncthreads();
-    transform_pencil_bins<N, T, VZN>(fmock + (long long)p * N, N3, nbins, A, tws, vcur);
-    __syncthreads();
-    ctr.add(A, dl, nbins, RS, N);
-    __syncthreads();
-  }
-  ctr.finish(reinterpret_cast<double*>(smem), partials + ((long long)mock * gridDim.x + blockIdx.x) * nbins * nbins,
-             nbins);
-}
 
 // ---------------------------------------------------------------------------
 // particle summation
@@ -1130,6 +1080,39 @@ __global__ void k_tile_scatter(const float* pos, const long long* off, int batch
   }
 }
 
+// Order of the particles within each 4^3-cell tile: by cell, z fastest, one wave
+// per tile (counting sort over the 64 cells in LDS), perm -> out.  Neighbours
+// in this order share most of their taps, so the gather finds them in L1 rather
+// than in L2.
+__global__ void __launch_bounds__(256) k_tile_order(const float* pos, const int* perm, const int* toff, long long ntiles,
+                                                    int n, double sc, int* out) {
+  __shared__ int hist[4][64];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const long long tile = blockIdx.x * 4LL + wv;
+  const int a0 = tile < ntiles ? toff[tile] : 0, a1 = tile < ntiles ? toff[tile + 1] : 0;
+  auto key = [&](int i) {
+    const int c = tile_of(pos + 3 * (long long)i, n, sc, n, 0);   // (x n + y) n + z of the cell
+    return ((c / (n * n)) & 3) * 16 + ((c / n) & 3) * 4 + (c & 3);
+  };
+  hist[wv][lane] = 0;
+  __syncthreads();
+  for (int k = a0 + lane; k < a1; k += 64) atomicAdd(&hist[wv][key(perm[k])], 1);
+  __syncthreads();
+  const int c = hist[wv][lane];
+  int incl = c;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int v = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += v;
+  }
+  hist[wv][lane] = a0 + incl - c;
+  __syncthreads();
+  for (int k = a0 + lane; k < a1; k += 64) {
+    const int i = perm[k];
+    out[atomicAdd(&hist[wv][key(i)], 1)] = i;
+  }
+}
+
 // Per-particle stencil records in sorted order, computed once per call by
 // make_taps: the cell (floor of x n / box per axis, packed 10 bits each; -1
 // for a position that is not finite) and the 12 tap weights in the working
@@ -1139,11 +1122,14 @@ __device__ __forceinline__ int pack_cell(const Taps& t) {
   return t.ok ? ((t.base[0] + 1) | ((t.base[1] + 1) << 10) | ((t.base[2] + 1) << 20)) : -1;
 }
 
+// On entry tcell holds the particles' final order (k_tile_order), which moves to perm.
 template <typename T>
-__global__ void k_tap_records(const float* pos, const int* perm, long long np_total, int n, double sc, int* tcell,
+__global__ void k_tap_records(const float* pos, int* perm, long long np_total, int n, double sc, int* tcell,
                               T* twt, const double* btab) {
   for (long long k = blockIdx.x * (long long)blockDim.x + threadIdx.x; k < np_total; k += (long long)gridDim.x * blockDim.x) {
-    const Taps t = make_taps(pos + 3 * (long long)perm[k], n, sc, btab);
+    const int i = tcell[k];
+    perm[k] = i;
+    const Taps t = make_taps(pos + 3 * (long long)i, n, sc, btab);
     tcell[k] = pack_cell(t);
 #pragma unroll
     for (int d = 0; d < 3; ++d)
@@ -1157,8 +1143,17 @@ __global__ void k_tap_records(const float* pos, const int* perm, long long np_to
 // (x, y) row with the z weights, the rows with the y weights, then x.  A row
 // whose z taps do not wrap is read at one base address plus multiples of the
 // node stride.
-template <typename T>
-__device__ __forceinline__ c2<T> gather_record(const c2<T>* fm, int cell, const T* wt, int n, int nbins, int b) {
+// W consecutive bins of a node (float32: two in one 16-byte load, which needs 4-byte alignment only)
+template <typename T, int W> struct BinRun;
+template <> struct BinRun<float, 1> { typedef float2 type; };
+template <> struct BinRun<double, 1> { typedef double2 type; };
+typedef float mp3_f4u __attribute__((ext_vector_type(4), aligned(8)));
+template <> struct BinRun<float, 2> { typedef mp3_f4u type; };
+
+// W = 2: bins b and b + 1 in one lane (float32)
+template <typename T, int W>
+__device__ __forceinline__ void gather_record(const c2<T>* fm, int cell, const T* wt, int n, int nbins, int b, c2<T>* out) {
+  using V = typename BinRun<T, W>::type;
   const int cx = cell & 1023, cy = (cell >> 10) & 1023, cz = cell >> 20;
   T w[8];                                               // y and z weights (x weights read per row)
 #pragma unroll
@@ -1169,38 +1164,49 @@ __device__ __forceinline__ c2<T> gather_record(const c2<T>* fm, int cell, const 
   long long oz[4];
 #pragma unroll
   for (int az = 0; az < 4; ++az) oz[az] = (long long)(zin ? cz - 1 + az : wrapi(cz - 1 + az, n)) * nbins + b;
-  c2<T> acc = mk<T>(0, 0);
-  // all four x rows unrolled: the 64 loads of a record are in flight together
+  T acc[2 * W];
 #pragma unroll
+  for (int e = 0; e < 2 * W; ++e) acc[e] = 0;
+  // as many x rows unrolled as 128 registers of loads in flight hold
+#pragma unroll(W == 2 ? 2 : 4)
   for (int ax = 0; ax < 4; ++ax) {
     const c2<T>* px = fm + wrapi(cx - 1 + ax, n) * rowx;
-    c2<T> sy = mk<T>(0, 0);
+    T sy[2 * W];
+#pragma unroll
+    for (int e = 0; e < 2 * W; ++e) sy[e] = 0;
 #pragma unroll
     for (int ay = 0; ay < 4; ++ay) {
       const c2<T>* py = px + wrapi(cy - 1 + ay, n) * rowy;
-      c2<T> v[4];
+      V v[4];
       if (zin) {
         const c2<T>* q = py + oz[0];
 #pragma unroll
-        for (int az = 0; az < 4; ++az) v[az] = q[az * nbins];
+        for (int az = 0; az < 4; ++az) v[az] = *reinterpret_cast<const V*>(q + az * nbins);
       } else {
 #pragma unroll
-        for (int az = 0; az < 4; ++az) v[az] = py[oz[az]];
+        for (int az = 0; az < 4; ++az) v[az] = *reinterpret_cast<const V*>(py + oz[az]);
       }
-      c2<T> sz = mk<T>(0, 0);
+      T sz[2 * W];
+#pragma unroll
+      for (int e = 0; e < 2 * W; ++e) sz[e] = 0;
 #pragma unroll
       for (int az = 0; az < 4; ++az) {
-        sz.x += w[4 + az] * v[az].x;
-        sz.y += w[4 + az] * v[az].y;
+        sz[0] += w[4 + az] * v[az].x;
+        sz[1] += w[4 + az] * v[az].y;
+        if constexpr (W == 2) {
+          sz[2] += w[4 + az] * v[az].z;
+          sz[3] += w[4 + az] * v[az].w;
+        }
       }
-      sy.x += w[ay] * sz.x;
-      sy.y += w[ay] * sz.y;
+#pragma unroll
+      for (int e = 0; e < 2 * W; ++e) sy[e] += w[ay] * sz[e];
     }
     const T wx = wt[ax];
-    acc.x += wx * sy.x;
-    acc.y += wx * sy.y;
+#pragma unroll
+    for (int e = 0; e < 2 * W; ++e) acc[e] += wx * sy[e];
   }
-  return acc;
+#pragma unroll
+  for (int i = 0; i < W; ++i) out[i] = mk<T>(acc[2 * i], acc[2 * i + 1]);
 }
 
 // particle slots of one contraction slice of the gather (LDS rows of nbins x slots)
@@ -1214,7 +1220,7 @@ constexpr int kGatherSlots = 256;
 // of the cotangent, lam_d its eigenvalues): per lane v_b = d_b conj(atilde_b),
 // src = N^3 (w_i / W) v_b, and wm sum_b d_b |atilde_b|^2 added to F_J(u_i),
 // all at gather time.
-template <typename T, bool MF, bool SPLIT = false, bool QUAD = false, bool SRC = false>
+template <typename T, bool MF, bool SPLIT, bool QUAD, bool SRC, int WB>
 __global__ void __launch_bounds__(256) k_gather_contract(const c2<T>* fields, const int* tcell, const T* twt,
                                                           const float* w, const int* perm, const long long* off,
                                                           const double* W, int n, int nbins, double* partials,
@@ -1232,11 +1238,12 @@ __global__ void __launch_bounds__(256) k_gather_contract(const c2<T>* fields, co
   const long long per = (a1 - a0 + gridDim.x - 1) / gridDim.x;
   const long long s0 = a0 + per * blockIdx.x, s1 = min(a1, s0 + per);
   const double invW = 1.0 / W[mock];
-  // nbins lanes per particle, 64 / nbins particles per wave (the rest idle)
+  // nl = nbins / WB lanes per particle, 64 / nl particles per wave (the rest idle)
+  const int nl = (nbins + WB - 1) / WB;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
   // slots per slice: a multiple of the particles per pass and of 8 (fewer
   // particles per wave where no multiple fits the slice)
-  int ppw = 64 / nbins;
+  int ppw = 64 / nl;
   if (ppw * nw > K) ppw = K / nw;
   int kcount = 0;
   for (;;) {
@@ -1246,12 +1253,16 @@ __global__ void __launch_bounds__(256) k_gather_contract(const c2<T>* fields, co
     if (kcount > 0 || ppw == 1) break;
     --ppw;
   }
-  const int pw = lane / nbins, b = lane - pw * nbins;
+  const int pw = lane / nl, bl = lane - pw * nl;
+  // an odd last bin: its lane takes the one before it too (written twice, the same values)
+  const int b = WB == 2 ? min(2 * bl, nbins - 2) : bl;
   const bool lane_ok = pw < ppw;
   const int ppp = nw * ppw;                             // particles per pass
   const c2<T>* fm = fields + mock * n3 * nbins;
   const double fw = (double)n3 / W[mock];
-  const T dl = (SRC && lane_ok) ? lam_d[mock * nbins + b] : (T)0;
+  T dl[WB];
+#pragma unroll
+  for (int i = 0; i < WB; ++i) dl[i] = (SRC && lane_ok) ? lam_d[mock * nbins + b + i] : (T)0;
   if constexpr (SRC) {
     for (int t = threadIdx.x; t < nbins; t += blockDim.x) lam[t] = lam_d[mock * nbins + t];
   }
@@ -1261,24 +1272,27 @@ __global__ void __launch_bounds__(256) k_gather_contract(const c2<T>* fields, co
     for (int k0 = 0; k0 < kcount; k0 += ppp) {
       const int k = k0 + wv * ppw + pw;
       const long long si = c0 + k;
-      c2<T> acc = mk<T>(0, 0);
+      c2<T> acc[WB];
+#pragma unroll
+      for (int e = 0; e < WB; ++e) acc[e] = mk<T>(0, 0);
       T wgt = 0;
       int i = -1;
       if (lane_ok && si < s1) {
         i = perm[si];
         const int cell = tcell[si];
-        if (cell >= 0) acc = gather_record<T>(fm, cell, twt + si * 12, n, nbins, b);
+        if (cell >= 0) gather_record<T, WB>(fm, cell, twt + si * 12, n, nbins, b, acc);
         const double wi = w ? (double)w[i] : 1.0;
         wgt = (T)(wi * invW);
         if constexpr (SRC) {
-          const T e = dl * acc.x, f2 = dl * acc.y;
           const T f = (T)(fw * wi);
-          src[si * nbins + b] = mk<T>(f * e, -(f * f2));
+#pragma unroll
+          for (int e = 0; e < WB; ++e) src[si * nbins + b + e] = mk<T>(f * (dl[e] * acc[e].x), -(f * (dl[e] * acc[e].y)));
         }
       }
       if (lane_ok) {
-        A[b * RS + lds_pos<true>(k)] = acc;
-        if (b == 0) {
+#pragma unroll
+        for (int e = 0; e < WB; ++e) A[(b + e) * RS + lds_pos<true>(k)] = acc[e];
+        if (bl == 0) {
           wk[k] = wgt;
           if constexpr (SRC) pk[k] = i;
         }
@@ -1390,22 +1404,29 @@ __global__ void k_reduce_partials(const double* partials, int nwg, int nb2, doub
 }
 
 // ---------------------------------------------------------------------------
-// backward pass z: recompute a_b on the pencil, then per z (one thread owns a
-// z column, so no atomics and no read/write hazards)
-//   u_b = sum_b' lam_s[b,b'] conj(a_b'),  direct += wm Re(sum_b a_b u_b),
-//   c_b = delta u_b,
-// and z-transform every c_b (the adjoint's first axis), written over the field.
-// lam_s is read with wave-uniform indices (scalar loads).
-// FUSED: the same sweep also contracts the pencil for zeta (the partials of
-// k_zpass_nodal), so that value and gradient share one computation of the
-// fields when dJ/dzeta is fixed before the forward (J linear in zeta).
+// z passes over a group of items: z-transform every bin of a pencil into LDS
+// rows, then by MODE
+//   forward   contract it, P[b1,b2] += sum_z delta_z Re(a_b1 conj(a_b2));
+//   adjoint   per z (one thread owns a z column, so no atomics and no
+//             read/write hazards), in the cotangent's eigenbasis,
+//             direct += wm sum_b d_b |a_b|^2,  c_b = delta d_b conj(a_b),
+//             and z-transform every c_b (the adjoint's first axis), written
+//             over the field;
+//   one sweep both, so that value and gradient share one computation of the
+//             fields when dJ/dzeta is fixed before the forward (J linear in zeta).
+// The forward shares this kernel because it hides latency by several small
+// workgroups per CU rather than by a pencil of prefetch registers: 256^3, 11
+// bins 0.865 -> 0.482 ms per (l, m), 20 bins 1.40 -> 0.89 ms.
 // ---------------------------------------------------------------------------
-template <int N, typename T, int MAXNB, bool FUSED = false, bool MF = false, bool QUAD = false>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(FUSED && MF ? 3 : 1)))
-k_zpass_adjoint(c2<T>* fields, const T* delta, const T* __restrict__ lam_d, T* direct, int nbins, int ppw,
+// MODE: what the pass does with the transformed pencil
+constexpr int Z_ADJOINT = 0, Z_FUSED = 1, Z_FORWARD = 2;
+template <int N, typename T, int MAXNB, int MODE, bool MF, bool QUAD, bool SPLIT>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(MODE != Z_ADJOINT && MF ? 3 : 1)))
+k_zpass(c2<T>* fields, const T* delta, const T* __restrict__ lam_d, T* direct, int nbins, int ppw,
                 const c2<T>* tw, double* partials, const ItemRec* items, int item0, int nitems, int batch, int nwg,
                 int* counter) {
   using F = Fft<N, VZA<T>>;
+  constexpr bool FUSED = MODE != Z_ADJOINT, GRAD = MODE != Z_FORWARD;
   constexpr int RS = zrow<N>();
   constexpr int NBP = (MAXNB + 3) / 4 * 4;
   constexpr long long N3 = (long long)N * N * N;
@@ -1414,7 +1435,7 @@ k_zpass_adjoint(c2<T>* fields, const T* delta, const T* __restrict__ lam_d, T* d
   c2<T>* A = reinterpret_cast<c2<T>*>(smem);
   c2<T>* tws = A + nbins * RS;
   T* lam = reinterpret_cast<T*>(tws + N);             // [NBP] eigenvalues of the cotangent, zero padded
-  T* dl = lam + NBP;                                  // FUSED: delta of the pencil
+  T* dl = lam + (GRAD ? NBP : 0);                     // FUSED: delta of the pencil
   const int tid = threadIdx.x;
   const int nbc = blockDim.x / F::TPC;
   const int nb2 = nbins * nbins;
@@ -1439,10 +1460,12 @@ k_zpass_adjoint(c2<T>* fields, const T* delta, const T* __restrict__ lam_d, T* d
     const ItemRec& it = items[item0 + g];
     const T wm = (T)it.wm;
     stage_twiddles<N, T>(tw, tws);
-    const T* ls = lam_d + ((long long)it.l * batch + mock) * nbins;
-    for (int t = tid; t < NBP; t += blockDim.x) lam[t] = t < nbins ? ls[t] : (T)0;
+    if constexpr (GRAD) {
+      const T* ls = lam_d + ((long long)it.l * batch + mock) * nbins;
+      for (int t = tid; t < NBP; t += blockDim.x) lam[t] = t < nbins ? ls[t] : (T)0;
+    }
     __syncthreads();
-    Contractor<T, MF, false, QUAD> ctr;
+    Contractor<T, MF, SPLIT, QUAD> ctr;
     if constexpr (FUSED) ctr.init(nbins);
     const int p0 = chunk * ppw;
     const int p1 = min(p0 + ppw, N * N);
@@ -1454,7 +1477,7 @@ k_zpass_adjoint(c2<T>* fields, const T* delta, const T* __restrict__ lam_d, T* d
     if (!NO_PREFETCH && p0 < p1) {
       prefetch_pencil<N, T, VZA<T>>(fmock + (long long)p0 * N, N3, nbins, vpre);
       prefetch_delta<N, T>(dmock + (long long)p0 * N, dpre);
-      prefetch_delta<N, T>(rmock + (long long)p0 * N, rpre);
+      if constexpr (GRAD) prefetch_delta<N, T>(rmock + (long long)p0 * N, rpre);
     }
     for (int p = p0; p < p1; ++p) {
       c2<T>* fbase = fmock + (long long)p * N;
@@ -1462,7 +1485,7 @@ k_zpass_adjoint(c2<T>* fields, const T* delta, const T* __restrict__ lam_d, T* d
       T dcur[DPRE], rcur[DPRE];
       if constexpr (NO_PREFETCH) {
         prefetch_delta<N, T>(dmock + (long long)p * N, dcur);
-        prefetch_delta<N, T>(rmock + (long long)p * N, rcur);
+        if constexpr (GRAD) prefetch_delta<N, T>(rmock + (long long)p * N, rcur);
       } else {
 #pragma unroll
         for (int q = 0; q < prefetch_rounds<N, VZA<T>>(); ++q)
@@ -1471,13 +1494,13 @@ k_zpass_adjoint(c2<T>* fields, const T* delta, const T* __restrict__ lam_d, T* d
 #pragma unroll
         for (int k = 0; k < DPRE; ++k) {
           dcur[k] = dpre[k];
-          rcur[k] = rpre[k];
+          if constexpr (GRAD) rcur[k] = rpre[k];
         }
       }
       if (!NO_PREFETCH && p + 1 < p1) {
         prefetch_pencil<N, T, VZA<T>>(fbase + N, N3, nbins, vpre);
         prefetch_delta<N, T>(dmock + (long long)(p + 1) * N, dpre);
-        prefetch_delta<N, T>(rmock + (long long)(p + 1) * N, rpre);
+        if constexpr (GRAD) prefetch_delta<N, T>(rmock + (long long)(p + 1) * N, rpre);
       }
       if constexpr (FUSED) {
 #pragma unroll
@@ -1501,7 +1524,7 @@ k_zpass_adjoint(c2<T>* fields, const T* delta, const T* __restrict__ lam_d, T* d
         // contraction of the fields before the sources overwrite them.  On the
         // matrix cores each wave contracts the 64 z columns whose sources its
         // own threads form next, so no barrier separates the two steps.
-        if constexpr (MF) {
+        if constexpr (MF && !SPLIT) {
           const int z0 = 64 * (tid >> 6);
           if (z0 < N) ctr.add_range(A, dl, nbins, RS, z0, z0 + 64 < N ? z0 + 64 : N);
         } else {
@@ -1509,6 +1532,7 @@ k_zpass_adjoint(c2<T>* fields, const T* delta, const T* __restrict__ lam_d, T* d
           __syncthreads();
         }
       }
+      if constexpr (GRAD) {
 #pragma unroll
       for (int k = 0; k < DPRE; ++k) {
         const int z = tid + k * blockDim.x;
@@ -1555,6 +1579,7 @@ k_zpass_adjoint(c2<T>* fields, const T* delta, const T* __restrict__ lam_d, T* d
 #pragma unroll
           for (int e = 0; e < F::RMAX; ++e) fbase[b * N3 + F::out_index(j, e)] = v[e];
         }
+      }
       }
       __syncthreads();
     }
@@ -1765,7 +1790,8 @@ __global__ void __launch_bounds__(256) k_rotate_zeta(double* zeta, const double*
 // ---------------------------------------------------------------------------
 // float32: four waves per SIMD (128 registers; the angular factors wait in
 // LDS, so the bin loop holds the bin sum, the column and the window values)
-template <int N, typename T>
+// SPLIT: grid.z splits the items of the group, and the shares meet in G atomically
+template <int N, typename T, bool SPLIT>
 __global__ void __launch_bounds__((strided_threads<N, T, VB>())) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 1)))
 k_adjoint_y(const c2<T>* fields, c2<T>* G,
                                                                           const T* jtab, int jmocks, int nq2, int nbins,
@@ -1802,7 +1828,9 @@ k_adjoint_y(const c2<T>* fields, c2<T>* G,
     const int qxs = sfreq(qx, N), qys = sfreq(F::out_index(j, e), N), qzs = sfreq(qz, N);
     q2[e] = qxs * qxs + qys * qys + qzs * qzs;
   }
-  for (int gi = 0; gi < nitems; ++gi) {
+  const int per = SPLIT ? (nitems + gridDim.z - 1) / gridDim.z : nitems;
+  const int g0 = SPLIT ? blockIdx.z * per : 0, g1 = SPLIT ? min(nitems, g0 + per) : nitems;
+  for (int gi = g0; gi < g1; ++gi) {
     const ItemRec& it = items[item0 + gi];
     // one element at a time: the float64 recurrences of the elements do not
     // run side by side (registers)
@@ -1854,7 +1882,13 @@ k_adjoint_y(const c2<T>* fields, c2<T>* G,
 #pragma unroll
       for (int e = 0; e < RMAX; ++e) {
         c2<T>* p = dst + F::out_index(j, e) * N;
-        nt_store(p, cadd<T>(nt_load(p), cmul<T>(acc[e], facs[e * blockDim.x + tid])));
+        const c2<T> v = cmul<T>(acc[e], facs[e * blockDim.x + tid]);
+        if constexpr (SPLIT) {
+          unsafeAtomicAdd(&p->x, v.x);
+          unsafeAtomicAdd(&p->y, v.y);
+        } else {
+          nt_store(p, cadd<T>(nt_load(p), v));
+        }
       }
     }
   }
@@ -1900,7 +1934,7 @@ __global__ void __launch_bounds__(256) k_gather_source(const c2<T>* fields, cons
     if (has && b < nbins) {
       c2<T> acc = mk<T>(0, 0);
       const int cell = tcell[si];
-      if (cell >= 0) acc = gather_record<T>(fm, cell, twt + si * 12, n, nbins, b);
+      if (cell >= 0) gather_record<T, 1>(fm, cell, twt + si * 12, n, nbins, b, &acc);
       const T e = d * acc.x, f2 = d * acc.y;
       fj = e * acc.x + f2 * acc.y;
       const T f = (T)(fw * (w ? (double)w[i] : 1.0));
@@ -2132,15 +2166,21 @@ hipError_t adjoint_y_t(const FilterArgs& a, hipStream_t st) {
   constexpr int ZC = zc_of<T>();
   constexpr int G = tiles_per_wg<N, T, VB>();
   constexpr int threads = Fft<N, VB>::TPC * ZC * G;
-  const dim3 gs((N * (N / ZC) + G - 1) / G, a.batch);
+  // items side by side while the tiles alone leave the chip idle (32^3, 15 items: 16 workgroups,
+  // 0.183 -> 0.025 ms); from 128^3 on the tiles fill it and the plain update of G is kept
+  const int tiles = (N * (N / ZC) + G - 1) / G;
+  int split = 512 / (tiles * a.batch);
+  split = split < 1 ? 1 : split > a.nitems ? a.nitems : split;
+  const dim3 gs(tiles, a.batch, split);
   const size_t dyn = (size_t)threads * Fft<N, VB>::RMAX * sizeof(CT<T>);
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_adjoint_y<N, T>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);
+  auto kern = split > 1 ? k_adjoint_y<N, T, true> : k_adjoint_y<N, T, false>;
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     (int)dyn);
   if (e != hipSuccess) return e;
-  k_adjoint_y<N, T><<<gs, threads, dyn, st>>>(static_cast<const CT<T>*>(a.src), static_cast<CT<T>*>(a.dst),
-                                           static_cast<const T*>(a.jtab), a.jmocks, a.nq2, a.nbins, a.nbp, a.items,
-                                           a.item0, a.nitems, a.batch, a.scale, static_cast<const CT<T>*>(a.tw),
-                                           static_cast<const T*>(a.phi));
+  kern<<<gs, threads, dyn, st>>>(static_cast<const CT<T>*>(a.src), static_cast<CT<T>*>(a.dst),
+                                 static_cast<const T*>(a.jtab), a.jmocks, a.nq2, a.nbins, a.nbp, a.items, a.item0,
+                                 a.nitems, a.batch, a.scale, static_cast<const CT<T>*>(a.tw),
+                                 static_cast<const T*>(a.phi));
   return hipGetLastError();
 }
 
@@ -2176,21 +2216,6 @@ template <int N, typename T> inline size_t zpass_adjoint_lds(int nbins) {
 template <typename K> hipError_t allow_lds(K kernel, size_t bytes) {
   if (bytes <= 65536) return hipSuccess;
   return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-}
-
-template <int N, typename T, bool MF, bool SPLIT = false, bool QUAD = false>
-hipError_t zpass_nodal_mf(const ZpassArgs& a, hipStream_t st) {
-  const int threads = zpass_threads<N, VZN>(a.nbins);
-  size_t lds = zpass_nodal_lds<N, T>(a.nbins, threads);
-  const size_t red = Contractor<T, MF, SPLIT, QUAD>::scratch_bytes(threads);
-  if (lds < red) lds = red;
-  hipError_t e = allow_lds(k_zpass_nodal<N, T, MF, SPLIT, QUAD>, lds);
-  if (e != hipSuccess) return e;
-  const dim3 gs(a.nwg, a.batch);
-  k_zpass_nodal<N, T, MF, SPLIT, QUAD><<<gs, threads, lds, st>>>(static_cast<const CT<T>*>(a.fields),
-                                                                static_cast<const T*>(a.delta), a.partials, a.nbins,
-                                                                a.ppw, static_cast<const CT<T>*>(a.tw));
-  return hipGetLastError();
 }
 
 // bins per launch of the store pass: as many as the LDS holds
@@ -2237,20 +2262,6 @@ hipError_t zpass_load_t(const ZpassArgs& a, const void* in, void* fields, hipStr
   return hipSuccess;
 }
 
-// float32 with at most 32 bins contracts on the matrix cores (float32 or
-// BF16-split inputs); otherwise on the vector ALUs
-template <int N, typename T>
-hipError_t zpass_nodal_t(const ZpassArgs& a, hipStream_t st) {
-  if constexpr (std::is_same<T, float>::value) {
-    if (a.nbins <= 32 && zpass_threads<N, VZN>(a.nbins) % 64 == 0) {
-      if (a.split) return zpass_nodal_mf<N, T, true, true>(a, st);
-      if (a.nbins > 16 && a.nbins <= 20) return zpass_nodal_mf<N, T, true, false, true>(a, st);
-      return zpass_nodal_mf<N, T, true>(a, st);
-    }
-  }
-  return zpass_nodal_mf<N, T, false>(a, st);
-}
-
 // fused sweeps round the workgroup up to whole waves (the matrix-core
 // contractions split the work by wave); the extra threads hold no column
 template <int N, typename T> inline int zpass_fused_threads(int nbins, int waves = 0) {
@@ -2274,48 +2285,70 @@ template <int N, typename T> inline size_t zpass_fused_lds(int nbins, int thread
 // kZpassResident workgroups take units from the counter (zeroed here first)
 constexpr int kZpassResident = 2048;
 
-template <int N, typename T, int MAXNB, bool FUSED = false, bool MF = false, bool QUAD = false>
-hipError_t zpass_adjoint_nb(const ZpassArgs& a, hipStream_t st) {
-  const int threads = FUSED ? zpass_fused_threads<N, T>(a.nbins, a.waves) : zpass_threads<N, VZA<T>>(a.nbins);
-  const size_t lds = FUSED ? zpass_fused_lds<N, T>(a.nbins, threads,
-                                                    Contractor<T, MF, false, QUAD>::scratch_bytes(threads))
-                           : zpass_adjoint_lds<N, T>(a.nbins);
-  hipError_t e = allow_lds(k_zpass_adjoint<N, T, MAXNB, FUSED, MF, QUAD>, lds);
+template <int N, typename T, int MAXNB, int MODE, bool MF, bool QUAD = false, bool SPLIT = false>
+hipError_t zpass_mode(const ZpassArgs& a, hipStream_t st) {
+  // the forward takes the fewest whole waves with a thread per z point; on the vector ALUs the 4x4 pair
+  // blocks (136 at 64 bins) need a thread each
+  const int threads = MODE == Z_FUSED     ? zpass_fused_threads<N, T>(a.nbins, a.waves)
+                      : MODE == Z_FORWARD ? zpass_fused_threads<N, T>(a.nbins, MF ? 1 : 4)
+                                          : zpass_threads<N, VZA<T>>(a.nbins);
+  const size_t scratch = MODE == Z_ADJOINT ? 0 : Contractor<T, MF, SPLIT, QUAD>::scratch_bytes(threads);
+  size_t lds = MODE == Z_ADJOINT ? zpass_adjoint_lds<N, T>(a.nbins)
+               : MODE == Z_FUSED ? zpass_fused_lds<N, T>(a.nbins, threads, scratch)
+                                 : zpass_nodal_lds<N, T>(a.nbins, 0);
+  if (lds < scratch) lds = scratch;
+  auto kern = k_zpass<N, T, MAXNB, MODE, MF, QUAD, SPLIT>;
+  hipError_t e = allow_lds(kern, lds);
   if (e != hipSuccess) return e;
   k_fill<int><<<1, 64, 0, st>>>(a.counter, 1, 0);
   const long long units = (long long)a.nitems * a.batch * a.nwg;
   const unsigned grid = (unsigned)(units < kZpassResident ? units : kZpassResident);
-  k_zpass_adjoint<N, T, MAXNB, FUSED, MF, QUAD><<<grid, threads, lds, st>>>(
+  kern<<<grid, threads, lds, st>>>(
       static_cast<CT<T>*>(const_cast<void*>(a.fields)), static_cast<const T*>(a.delta), static_cast<const T*>(a.lam),
       static_cast<T*>(a.direct), a.nbins, a.ppw, static_cast<const CT<T>*>(a.tw), a.partials, a.items, a.item0,
       a.nitems, a.batch, a.nwg, a.counter);
   return hipGetLastError();
 }
 
-// value-and-gradient sweep, <= 32 bins: float32 contracts on the matrix cores
-// (4x4 blocks at 17..20 bins), float64 on the vector ALUs
+// Contraction of the z passes on the matrix cores: float32 up to 32 bins; float64 up to 16, where one
+// 16x16 block serves (128^3, 15 bins: one sweep 0.374 -> 0.315 ms, forward 0.215 -> 0.180 ms per (l, m)),
+// beyond it three blocks spend more than the vector ALUs' upper-triangle 4x4 blocks (24 bins: 0.89 against 0.82 ms)
+template <typename T> constexpr int mf_bins() { return std::is_same<T, float>::value ? 32 : 16; }
+
+// value-and-gradient sweep, <= 32 bins (float32: 4x4 matrix blocks at 17..20 bins)
 template <int N, typename T>
 hipError_t zpass_fused_t(const ZpassArgs& a, hipStream_t st) {
   if (a.nbins > 32) return hipErrorInvalidValue;
-  constexpr bool MF = std::is_same<T, float>::value;
-  if (a.nbins <= 8) return zpass_adjoint_nb<N, T, 8, true, MF, false>(a, st);
-  if (a.nbins <= 12) return zpass_adjoint_nb<N, T, 12, true, MF, false>(a, st);
-  if (a.nbins <= 16) return zpass_adjoint_nb<N, T, 16, true, MF, false>(a, st);
-  if (a.nbins <= 20) return zpass_adjoint_nb<N, T, 20, true, MF, MF>(a, st);
-  if (a.nbins <= 24) return zpass_adjoint_nb<N, T, 24, true, MF, false>(a, st);
-  return zpass_adjoint_nb<N, T, 32, true, MF, false>(a, st);
+  constexpr bool F32 = std::is_same<T, float>::value;
+  if (a.nbins <= 8) return zpass_mode<N, T, 8, Z_FUSED, true>(a, st);
+  if (a.nbins <= 12) return zpass_mode<N, T, 12, Z_FUSED, true>(a, st);
+  if (a.nbins <= 16) return zpass_mode<N, T, 16, Z_FUSED, true>(a, st);
+  if (a.nbins <= 20) return zpass_mode<N, T, 20, Z_FUSED, F32, F32>(a, st);
+  if (a.nbins <= 24) return zpass_mode<N, T, 24, Z_FUSED, F32>(a, st);
+  return zpass_mode<N, T, 32, Z_FUSED, F32>(a, st);
+}
+
+// forward contraction (float32: also with BF16-split inputs)
+template <int N, typename T>
+hipError_t zpass_nodal_t(const ZpassArgs& a, hipStream_t st) {
+  if (a.nbins > mf_bins<T>()) return zpass_mode<N, T, 4, Z_FORWARD, false>(a, st);
+  if constexpr (std::is_same<T, float>::value) {
+    if (a.split) return zpass_mode<N, T, 4, Z_FORWARD, true, false, true>(a, st);
+    if (a.nbins > 16 && a.nbins <= 20) return zpass_mode<N, T, 4, Z_FORWARD, true, true>(a, st);
+  }
+  return zpass_mode<N, T, 4, Z_FORWARD, true>(a, st);
 }
 
 template <int N, typename T>
 hipError_t zpass_adjoint_t(const ZpassArgs& a, hipStream_t st) {
-  if (a.nbins <= 8) return zpass_adjoint_nb<N, T, 8>(a, st);
-  if (a.nbins <= 12) return zpass_adjoint_nb<N, T, 12>(a, st);
-  if (a.nbins <= 16) return zpass_adjoint_nb<N, T, 16>(a, st);
-  if (a.nbins <= 20) return zpass_adjoint_nb<N, T, 20>(a, st);
-  if (a.nbins <= 24) return zpass_adjoint_nb<N, T, 24>(a, st);
-  if (a.nbins <= 32) return zpass_adjoint_nb<N, T, 32>(a, st);
-  if (a.nbins <= 48) return zpass_adjoint_nb<N, T, 48>(a, st);
-  return zpass_adjoint_nb<N, T, 64>(a, st);
+  if (a.nbins <= 8) return zpass_mode<N, T, 8, Z_ADJOINT, false>(a, st);
+  if (a.nbins <= 12) return zpass_mode<N, T, 12, Z_ADJOINT, false>(a, st);
+  if (a.nbins <= 16) return zpass_mode<N, T, 16, Z_ADJOINT, false>(a, st);
+  if (a.nbins <= 20) return zpass_mode<N, T, 20, Z_ADJOINT, false>(a, st);
+  if (a.nbins <= 24) return zpass_mode<N, T, 24, Z_ADJOINT, false>(a, st);
+  if (a.nbins <= 32) return zpass_mode<N, T, 32, Z_ADJOINT, false>(a, st);
+  if (a.nbins <= 48) return zpass_mode<N, T, 48, Z_ADJOINT, false>(a, st);
+  return zpass_mode<N, T, 64, Z_ADJOINT, false>(a, st);
 }
 
 template <int N, typename T> size_t zpass_lds_need_t(int nbins) {
@@ -2372,10 +2405,9 @@ hipError_t launch_zpass_fused(int n, int prec, const ZpassArgs& a, hipStream_t s
 template <int N, typename T> size_t zpass_fused_lds_need_t(int nbins) {
   if (nbins > 32) return (size_t)1 << 40;
   const int threads = 512;   // the largest workgroup any waves setting gives
-  constexpr bool MF = std::is_same<T, float>::value;
-  const size_t red = nbins > 16 && nbins <= 20 ? Contractor<T, MF, false, MF>::scratch_bytes(threads)
-                                                : Contractor<T, MF, false, false>::scratch_bytes(threads);
-  return zpass_fused_lds<N, T>(nbins, threads, red);
+  return zpass_fused_lds<N, T>(nbins, threads,
+                               nbins <= mf_bins<T>() ? Contractor<T, true>::scratch_bytes(threads)
+                                                     : Contractor<T, false>::scratch_bytes(threads));
 }
 
 size_t zpass_fused_lds_need(int n, int prec, int nbins) {
@@ -2633,7 +2665,7 @@ hipError_t launch_deposit_tiled(int prec, int tside, const float* pos, const flo
                                 btab, st);
 }
 
-template <typename T, bool MF, bool SPLIT, bool QUAD, bool SRC>
+template <typename T, bool MF, bool SPLIT, bool QUAD, bool SRC, int W>
 hipError_t gather_contract_v(const GatherArgs& a, hipStream_t st) {
   constexpr int K = kGatherSlots;
   const size_t rs = K + K / 16 + 1;
@@ -2641,19 +2673,26 @@ hipError_t gather_contract_v(const GatherArgs& a, hipStream_t st) {
   if (SRC) lds += K * sizeof(int) + (size_t)a.nbins * sizeof(T);
   const size_t red = Contractor<T, MF, SPLIT, QUAD>::scratch_bytes(256);
   if (lds < red) lds = red;
-  hipError_t e = allow_lds(k_gather_contract<T, MF, SPLIT, QUAD, SRC>, lds);
+  hipError_t e = allow_lds(k_gather_contract<T, MF, SPLIT, QUAD, SRC, W>, lds);
   if (e != hipSuccess) return e;
   const dim3 gs(a.nwg, a.batch);
-  k_gather_contract<T, MF, SPLIT, QUAD, SRC><<<gs, 256, lds, st>>>(
+  k_gather_contract<T, MF, SPLIT, QUAD, SRC, W><<<gs, 256, lds, st>>>(
       static_cast<const CT<T>*>(a.fields), a.tcell, static_cast<const T*>(a.twt), a.w, a.perm, a.off, a.W, a.n, a.nbins,
       a.partials, static_cast<const T*>(a.lam), (T)a.wm, a.FJ, static_cast<CT<T>*>(a.src));
   return hipGetLastError();
 }
 
+// float32 reads two bins per lane in 16-byte loads (half the load instructions: 512^3, 20 bins
+// 42.0 -> 35.5 ms; 128^3, 15 bins 0.66 -> 0.51 ms); float64 bins are 16 bytes each
 template <typename T, bool MF, bool SPLIT = false, bool QUAD = false>
 hipError_t gather_contract_t(const GatherArgs& a, hipStream_t st) {
-  if (a.src) return gather_contract_v<T, MF, SPLIT, QUAD, true>(a, st);
-  return gather_contract_v<T, MF, SPLIT, QUAD, false>(a, st);
+  if constexpr (std::is_same<T, float>::value) {
+    if (a.nbins > 1)
+      return a.src ? gather_contract_v<T, MF, SPLIT, QUAD, true, 2>(a, st)
+                   : gather_contract_v<T, MF, SPLIT, QUAD, false, 2>(a, st);
+  }
+  if (a.src) return gather_contract_v<T, MF, SPLIT, QUAD, true, 1>(a, st);
+  return gather_contract_v<T, MF, SPLIT, QUAD, false, 1>(a, st);
 }
 
 hipError_t launch_gather_contract(int prec, const GatherArgs& a, hipStream_t st) {
@@ -2713,8 +2752,10 @@ hipError_t launch_gather_source(int prec, const void* fields, const int* tcell, 
   return hipGetLastError();
 }
 
-hipError_t launch_tap_records(int prec, const float* pos, const int* perm, long long np_total, int n, double sc,
-                              int* tcell, void* twt, const double* btab, hipStream_t st) {
+hipError_t launch_tap_records(int prec, const float* pos, int* perm, const int* toff, long long ntiles,
+                              long long np_total, int n, double sc, int* tcell, void* twt, const double* btab,
+                              hipStream_t st) {
+  k_tile_order<<<(unsigned)((ntiles + 3) / 4), 256, 0, st>>>(pos, perm, toff, ntiles, n, sc, tcell);
   const unsigned g = grid_for(np_total, 256, 16384);
   if (prec)
     k_tap_records<double><<<g, 256, 0, st>>>(pos, perm, np_total, n, sc, tcell, static_cast<double*>(twt), btab);

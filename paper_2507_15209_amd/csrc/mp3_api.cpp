@@ -96,6 +96,12 @@ size_t contract_wgs(const mp3_plan_s* p) {
   return (size_t)(g > 1 ? g : 1);
 }
 
+// 4^3-cell tiles of the particle sort, all mocks
+long long sort_tiles(const mp3_plan_s* p) {
+  const long long t = p->n / 4;
+  return t * t * t * p->batch;
+}
+
 size_t deposit_tiles(const mp3_plan_s* p) {
   const size_t t = (size_t)(p->n / p->tune[MP3_TUNE_DEPOSIT_TILE]);
   return t * t * t * (size_t)p->batch;
@@ -422,8 +428,12 @@ mp3::ZpassArgs adjoint_zargs(const mp3_plan_s* p, void* ws, const Layout& L, voi
   z.direct = direct;
   z.tw = p->tw;
   z.nbins = p->nbins;
-  z.nwg = L.nwg;
-  z.ppw = L.ppw;
+  // the launch's workgroups over all of its items: several pencils each rather than a partial sum
+  // (and its reduction) per pencil on small grids
+  const int per = p->tune[MP3_TUNE_ZPASS_WGS] / (p->batch * nitems);
+  const int pencils = p->n * p->n, nwg = per < 1 ? 1 : per < L.nwg ? per : L.nwg;
+  z.ppw = (pencils + nwg - 1) / nwg;
+  z.nwg = (pencils + z.ppw - 1) / z.ppw;
   z.batch = p->batch;
   z.lmax = p->lmax;
   z.items = p->items_dev;
@@ -808,26 +818,17 @@ int zeta_nodal(mp3_plan_t p, const void* delta, double* zeta, void* ws, const La
   const double n3 = (double)p->n * p->n * p->n;
   void* F = at(ws, L.fields);
   double* partials = reinterpret_cast<double*>(at(ws, L.partials));
-  for (int l = 0; l <= p->lmax; ++l) {
-    for (int m = 0; m <= l; ++m) {
-      if (int s = fields_xy(p, ws, L, F, item_index(l, m), 1, st)) return s;
-      mp3::ZpassArgs z{};
-      z.fields = F;
-      z.delta = delta;
-      z.partials = partials;
-      z.tw = p->tw;
-      z.nbins = p->nbins;
-      z.nwg = L.nwg;
-      z.ppw = L.ppw;
-      z.batch = p->batch;
-      z.l = l;
-      z.lmax = p->lmax;
-      z.split = p->split;
-      MP3_HIP(timed(p, MP3_PASS_Z_NODAL, st, [&] { return mp3::launch_zpass_nodal(p->n, p->prec, z, st); }), "z pass (contraction)");
-      const double wm = m == 0 ? 1.0 : 2.0;
-      MP3_HIP(mp3::launch_reduce_partials(partials, L.nwg, nb2, zeta, l, p->lmax, wm * kFourPi / n3, p->batch, st),
-              "reduce");
-    }
+  const int nitems_all = (int)p->items.size();
+  for (int item0 = 0; item0 < nitems_all; item0 += L.group) {
+    const int ni = std::min(L.group, nitems_all - item0);
+    if (int s = fields_xy(p, ws, L, F, item0, ni, st)) return s;
+    mp3::ZpassArgs z = adjoint_zargs(p, ws, L, F, delta, nullptr, nullptr, item0, ni);
+    z.partials = partials;
+    z.split = p->split;
+    MP3_HIP(timed(p, MP3_PASS_Z_NODAL, st, [&] { return mp3::launch_zpass_nodal(p->n, p->prec, z, st); }), "z pass (contraction)");
+    MP3_HIP(mp3::launch_reduce_items(partials, z.nwg, nb2, zeta, p->lmax, kFourPi / n3, p->items_dev, item0, ni,
+                                     p->batch, st),
+            "reduce");
   }
   return MP3_OK;
 }
@@ -849,7 +850,7 @@ int zeta_particle(mp3_plan_t p, const float* pos, const float* w, const int64_t*
           "tile sort");
   int* tcell = reinterpret_cast<int*>(at(ws, L.tcell));
   void* twt = at(ws, L.twt);
-  MP3_HIP(mp3::launch_tap_records(p->prec, pos, perm, np_total, p->n, sc, tcell, twt, p->btab, st), "stencil records");
+  MP3_HIP(mp3::launch_tap_records(p->prec, pos, perm, reinterpret_cast<const int*>(at(ws, L.offs)), sort_tiles(p), np_total, p->n, sc, tcell, twt, p->btab, st), "stencil records");
   double* P = reinterpret_cast<double*>(at(ws, L.power));
   const int nq2 = mp3::nq2_count(p->n);
   MP3_HIP(mp3::launch_fill_f64(P, (long long)p->batch * nq2, 0.0, st), "zero power");
@@ -1015,7 +1016,7 @@ int backward_particle(mp3_plan_t p, const void* delta, const double* dzeta, void
           "tile sort");
   int* tcell = reinterpret_cast<int*>(at(ws, L.tcell));
   void* twt = at(ws, L.twt);
-  MP3_HIP(mp3::launch_tap_records(p->prec, pos, perm, np_total, p->n, sc, tcell, twt, p->btab, st), "stencil records");
+  MP3_HIP(mp3::launch_tap_records(p->prec, pos, perm, reinterpret_cast<const int*>(at(ws, L.offs)), sort_tiles(p), np_total, p->n, sc, tcell, twt, p->btab, st), "stencil records");
   void* F = at(ws, L.fields);
   void* Fi = at(ws, L.fields_i);
   void* G = at(ws, L.G);
@@ -1106,7 +1107,7 @@ int value_and_grad_particle(mp3_plan_t p, const void* delta, const double* dzeta
           "tile sort");
   int* tcell = reinterpret_cast<int*>(at(ws, L.tcell));
   void* twt = at(ws, L.twt);
-  MP3_HIP(mp3::launch_tap_records(p->prec, pos, perm, np_total, p->n, sc, tcell, twt, p->btab, st), "stencil records");
+  MP3_HIP(mp3::launch_tap_records(p->prec, pos, perm, reinterpret_cast<const int*>(at(ws, L.offs)), sort_tiles(p), np_total, p->n, sc, tcell, twt, p->btab, st), "stencil records");
   double* P = reinterpret_cast<double*>(at(ws, L.power));
   const int nq2 = mp3::nq2_count(p->n);
   MP3_HIP(mp3::launch_fill_f64(P, (long long)p->batch * nq2, 0.0, st), "zero power");
@@ -1372,7 +1373,7 @@ int mp3_zeta_value_and_grad(mp3_plan_t p, const void* delta, const double* dzeta
     z.waves = p->tune[MP3_TUNE_FUSED_WAVES];
     MP3_HIP(timed(p, MP3_PASS_Z_FUSED, st, [&] { return mp3::launch_zpass_fused(p->n, p->prec, z, st); }),
             "z pass (contraction and adjoint)");
-    MP3_HIP(mp3::launch_reduce_items(partials, L.nwg, nb2, zeta, p->lmax, kFourPi / (double)n3, p->items_dev, item0, ni,
+    MP3_HIP(mp3::launch_reduce_items(partials, z.nwg, nb2, zeta, p->lmax, kFourPi / (double)n3, p->items_dev, item0, ni,
                                      p->batch, st),
             "reduce");
     MP3_HIP(timed(p, MP3_PASS_X, st, [&] { return mp3::launch_fft_x(p->n, p->prec, +1, F, ni * p->batch * p->nbins, p->tw, p->tune[MP3_TUNE_FFT_X_PLAN], st); }), "adjoint x pass");

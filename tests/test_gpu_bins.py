@@ -1,0 +1,59 @@
+"""GPU: values at the bin counts where the contractions change form -- one and two 16-bin matrix blocks,
+4x4 blocks at 17..20 bins, the vector ALUs beyond (float64 from 17, float32 from 33 bins), one or two bins
+per gather lane -- on grids whose items share a launch, against the oracle; the one sweep's and the two
+calls' gradients against each other.
+
+Bars: float64 1.1e-11 (1e5 terms x 2^-53); float32 1.9e-5 (20 operations x 2^-24 x 16, the largest sum of
+interpolation weights); gradients of the two ways agree to twice that."""
+import functools
+
+import numpy as np
+import pytest
+
+from mockgen import lognormal_catalogue
+from oracle import basis as B
+from oracle import estimator as E
+from tests._common import assert_zeta_close
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+TOL = {"f64": 1.1e-11, "f32": 1.9e-5}
+LMAX = 2
+
+
+@functools.lru_cache(maxsize=None)
+def _case(n, nb, form):
+    box = 10.0 * n
+    edges = np.linspace(0.1 * box, 0.35 * box, nb + 1)
+    pos, w = lognormal_catalogue(n, box, 1500, 0.05 * box, 601, 602, 603, (0.5, 1.5))
+    op = E.Plan(n, box, LMAX, edges)
+    if form == "particle":
+        return box, edges, pos, w, E.zeta_particle(op, pos, w)
+    delta = B.density_contrast(B.deposit(pos, w, n, box), float(np.sum(w.astype(np.float64))))
+    return box, edges, pos, w, E.zeta_nodal(op, delta)
+
+
+@pytest.mark.parametrize("form,n,nb", [("nodal", 16, 1), ("nodal", 16, 16), ("nodal", 16, 17), ("nodal", 16, 32),
+                                       ("nodal", 16, 33), ("nodal", 16, 50), ("nodal", 32, 15), ("nodal", 32, 20),
+                                       ("particle", 16, 1), ("particle", 16, 2), ("particle", 16, 3),
+                                       ("particle", 16, 20), ("particle", 16, 33)])
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+def test_bin_counts(prec, form, n, nb):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2507_15209_amd as mp3
+    print("[case] bin counts", prec, form, n, nb, flush=True)
+    box, edges, pos, w, ref = _case(n, nb, form)
+    plan = mp3.Plan(n, box, LMAX, edges, precision=prec, summation=form)
+    pt, wt = torch.as_tensor(pos, device="cuda"), torch.as_tensor(w, device="cuda")
+    delta = plan.deposit(pt, wt)
+    cat = (pt, wt) if form == "particle" else ()
+    lam = torch.as_tensor(np.random.default_rng(604).standard_normal((1, LMAX + 1, nb, nb)), device="cuda")
+    assert_zeta_close(plan.zeta(delta, *cat).cpu().numpy()[0], ref, TOL[prec])
+    z, g, dw = plan.zeta_value_and_grad(delta, lam, pt, wt)
+    assert_zeta_close(z.cpu().numpy()[0], ref, TOL[prec])
+    g2, dw2 = plan.zeta_backward(delta, lam, pt, wt)
+    for a, b in ((g, g2), (dw, dw2)):
+        a, b = a.double().cpu().numpy(), b.double().cpu().numpy()
+        assert np.abs(a - b).max() <= 2 * TOL[prec] * np.abs(b).max()
