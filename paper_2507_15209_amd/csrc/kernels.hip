@@ -390,7 +390,9 @@ __global__ void __launch_bounds__((contig_pencils<N, T>() * Fft<N>::TPC)) k_fft_
 // first pass of the forward: window K_{lm,b} on the k-space tile, all bins,
 // transform along y
 // ---------------------------------------------------------------------------
-template <int N, typename T>
+// PAIR: items of two real fields (m = 0 of multipoles l and l2), window K_l + i K_l2: one pair costs
+// 1.5 ms at 256^3, 20 bins against 2 x 0.79 ms here, and the passes after it run once instead of twice
+template <int N, typename T, bool PAIR>
 __global__ void __launch_bounds__((strided_threads<N, T, VB>())) k_filter_y(const c2<T>* dhat, c2<T>* fields,
                                                                          const T* jtab, int jmocks, int nq2, int nbins,
                                                                          int nbp, const ItemRec* items, int item0,
@@ -418,7 +420,7 @@ __global__ void __launch_bounds__((strided_threads<N, T, VB>())) k_filter_y(cons
   const ItemRec& it = items[item0 + gi];
   stage_twiddles<N, T>(tw, tws);
   __syncthreads();
-  c2<T> v0[RMAX];
+  c2<T> v0[RMAX], v1[PAIR ? RMAX : 1];
   int q2[RMAX];
 #pragma unroll
   for (int r = 0; r < RMAX; ++r) {
@@ -426,16 +428,25 @@ __global__ void __launch_bounds__((strided_threads<N, T, VB>())) k_filter_y(cons
     const c2<T> d = active ? nt_load(&dhat[mock * N3 + ((long long)qx * N + qy) * N + qz]) : mk<T>(0, 0);
     const c2<T> f = window_angular<T>(qx, qy, qz, N, it.l, it.m, it.norm, scale, it.yr, q2[r], phi);
     v0[r] = cmul<T>(d, f);
+    if constexpr (PAIR) {
+      const c2<T> f2 = window_angular<T>(qx, qy, qz, N, it.l2, 0, it.norm2, scale, it.yr2, q2[r], phi);
+      v1[r] = mul_i<+1, T>(cmul<T>(d, f2));
+    }
   }
   // radial window of this thread's elements, four bins per load, one quad
   // ahead (jmocks tables per l: one, or one per mock in the cotangent's eigenbasis)
   const T* jl = jtab + ((long long)it.l * jmocks + mock % jmocks) * nq2 * nbp;
+  const T* jl2 = PAIR ? jtab + ((long long)it.l2 * jmocks + mock % jmocks) * nq2 * nbp : nullptr;
   T jq[RMAX][4];
 #pragma unroll
   for (int r = 0; r < RMAX; ++r) load_quad<T>(jl + (long long)q2[r] * nbp, jq[r]);
   c2<T>* fbase = fields + ((long long)gi * batch + mock) * nbins * N3 + (long long)qx * N * N + qz;
   for (int bq = 0; bq < nbins; bq += 4) {
-    T jn[RMAX][4];
+    T jn[RMAX][4], j2[PAIR ? RMAX : 1][4];
+    if constexpr (PAIR) {
+#pragma unroll
+      for (int r = 0; r < RMAX; ++r) load_quad<T>(jl2 + (long long)q2[r] * nbp + bq, j2[r]);
+    }
     if (bq + 4 < nbins) {
 #pragma unroll
       for (int r = 0; r < RMAX; ++r) load_quad<T>(jl + (long long)q2[r] * nbp + bq + 4, jn[r]);
@@ -445,7 +456,10 @@ __global__ void __launch_bounds__((strided_threads<N, T, VB>())) k_filter_y(cons
       if (bq + k < nbins) {
         c2<T> v[RMAX];
 #pragma unroll
-        for (int r = 0; r < RMAX; ++r) v[r] = cscale<T>(v0[r], jq[r][k]);
+        for (int r = 0; r < RMAX; ++r) {
+          v[r] = cscale<T>(v0[r], jq[r][k]);
+          if constexpr (PAIR) v[r] = cadd<T>(v[r], cscale<T>(v1[r], j2[r][k]));
+        }
         int jj = j;
         asm volatile("" : "+v"(jj));
         fft_column<N, +1, T, false, VB>(v, lds + g * N * ZC + cc, ZC, jj, tws, active);
@@ -571,15 +585,33 @@ __device__ __forceinline__ void transform_pencil_bins(const c2<T>* src, long lon
 
 typedef mfma_f4 mp3_f4;
 
-// Nodal contraction on the matrix cores (float32, nbins <= 32): per pair of z,
-// one v_mfma_f32_16x16x4f32 per upper-triangular 16x16 block of (b1, b2),
-// k = (z, re/im):  A[b1][k] = delta_z c_k(a_b1(z)),  B[k][b2] = c_k(a_b2(z)).
-// Lane l supplies A[l%16][l/16] and B[l/16][l%16]; D register i of lane l is
-// C[4 (l/16) + i][l%16].
+// Nodal contraction on the matrix cores (nbins <= 32): per four z, one
+// 16x16x4 instruction per upper-triangular 16x16 block of (b1, b2) and part,
+// k = z:  A[b1][k] = delta_z re(a_b1(z)),  B[k][b2] = re(a_b2(z)), then im.
+// Lane l supplies A[l%16][l/16] and B[l/16][l%16].
+// the products of the real and of the imaginary parts apart: a pair item's parts belong to two multipoles
 template <typename T> struct MfmaAcc {
-  typename acc4<T>::type c00, c01, c11;
+  typename acc4<T>::type r00, r01, r11, i00, i01, i11;
 };
 
+template <typename T>
+__device__ __forceinline__ void mfma_contract_step(const c2<T>* r0, const c2<T>* r1, const T* dl, int z, bool two,
+                                                   MfmaAcc<T>& acc) {
+  const int off = lds_pos<true>(z);
+  const T d = dl[z];
+  const c2<T> v0 = r0[off];
+  acc.r00 = mfma16(d * v0.x, v0.x, acc.r00);
+  acc.i00 = mfma16(d * v0.y, v0.y, acc.i00);
+  if (two) {
+    const c2<T> v1 = r1[off];
+    acc.r01 = mfma16(d * v0.x, v1.x, acc.r01);
+    acc.i01 = mfma16(d * v0.y, v1.y, acc.i01);
+    acc.r11 = mfma16(d * v1.x, v1.x, acc.r11);
+    acc.i11 = mfma16(d * v1.y, v1.y, acc.i11);
+  }
+}
+
+// N a multiple of 4
 template <typename T>
 __device__ __forceinline__ void mfma_contract_pencil(const c2<T>* A, const T* dl, int nbins, int RS, int N,
                                                      MfmaAcc<T>& acc) {
@@ -587,53 +619,23 @@ __device__ __forceinline__ void mfma_contract_pencil(const c2<T>* A, const T* dl
   const int w = threadIdx.x >> 6;
   const int nw = blockDim.x >> 6;
   const int col = lane & 15, kq = lane >> 4;
-  const int zz = kq >> 1, comp = kq & 1;
-  const bool two = nbins > 16;
-  const bool ok0 = col < nbins, ok1 = 16 + col < nbins;
   // lanes of bins beyond nbins read row 0 (finite values): they only feed
   // entries of P that the reduction drops, and the loads need no mask
-  const T* r0 = reinterpret_cast<const T*>(A + (ok0 ? col : 0) * RS) + comp;
-  const T* r1 = reinterpret_cast<const T*>(A + (ok1 ? 16 + col : 0) * RS) + comp;
-  for (int zp = w; zp < N / 2; zp += nw) {
-    const int z = 2 * zp + zz;
-    const int off = 2 * lds_pos<true>(z);
-    const T d = dl[z];
-    const T v0 = r0[off];
-    acc.c00 = mfma16(d * v0, v0, acc.c00);
-    if (two) {
-      const T v1 = r1[off];
-      acc.c01 = mfma16(d * v0, v1, acc.c01);
-      acc.c11 = mfma16(d * v1, v1, acc.c11);
-    }
-  }
+  const c2<T>* r0 = A + (col < nbins ? col : 0) * RS;
+  const c2<T>* r1 = A + (16 + col < nbins ? 16 + col : 0) * RS;
+  for (int z = 4 * w; z < N; z += 4 * nw) mfma_contract_step<T>(r0, r1, dl, z + kq, nbins > 16, acc);
 }
 
-// the same for z in [z0, z1) (even bounds), all by the calling wave
+// the same for z in [z0, z1) (bounds multiples of 4), all by the calling wave
 template <typename T>
 __device__ __forceinline__ void mfma_contract_pencil_range(const c2<T>* A, const T* dl, int nbins, int RS, int z0,
                                                            int z1, MfmaAcc<T>& acc) {
   const int lane = threadIdx.x & 63;
   const int col = lane & 15, kq = lane >> 4;
-  const int zz = kq >> 1, comp = kq & 1;
-  const bool two = nbins > 16;
-  const bool ok0 = col < nbins, ok1 = 16 + col < nbins;
-  // lanes of bins beyond nbins read row 0 (finite values): they only feed
-  // entries of P that the reduction drops, and the loads need no mask
-  const T* r0 = reinterpret_cast<const T*>(A + (ok0 ? col : 0) * RS) + comp;
-  const T* r1 = reinterpret_cast<const T*>(A + (ok1 ? 16 + col : 0) * RS) + comp;
-#pragma unroll 8
-  for (int zp = z0 / 2; zp < z1 / 2; ++zp) {
-    const int z = 2 * zp + zz;
-    const int off = 2 * lds_pos<true>(z);
-    const T d = dl[z];
-    const T v0 = r0[off];
-    acc.c00 = mfma16(d * v0, v0, acc.c00);
-    if (two) {
-      const T v1 = r1[off];
-      acc.c01 = mfma16(d * v0, v1, acc.c01);
-      acc.c11 = mfma16(d * v1, v1, acc.c11);
-    }
-  }
+  const c2<T>* r0 = A + (col < nbins ? col : 0) * RS;
+  const c2<T>* r1 = A + (16 + col < nbins ? 16 + col : 0) * RS;
+#pragma unroll 4
+  for (int z = z0; z < z1; z += 4) mfma_contract_step<T>(r0, r1, dl, z + kq, nbins > 16, acc);
 }
 
 // 17..20 bins: the 15 upper-triangle 4x4 blocks (g1 <= g2 of 5 bin groups)
@@ -664,15 +666,14 @@ __device__ __forceinline__ void mfma_contract_4x4(const float2* A, const float* 
   // they only feed entries of P that the reduction drops, so no load is masked
   const float2* ra = A + (oka ? ba : 0) * RS;
   const float2* rb = A + (okb ? bb : 0) * RS;
-  // three accumulators in rotation keep dependent matrix-core issues apart
   for (int z = 2 * w; z < K; z += 2 * nw) {
     const int zp0 = lds_pos<true>(z), zp1 = lds_pos<true>(z + 1);
     const float d0 = dl[z], d1 = dl[z + 1];
     const float2 u0 = ra[zp0], v0 = rb[zp0], u1 = ra[zp1], v1 = rb[zp1];
-    acc.c00 = __builtin_amdgcn_mfma_f32_4x4x1f32(d0 * u0.x, v0.x, acc.c00, 0, 0, 0);
-    acc.c01 = __builtin_amdgcn_mfma_f32_4x4x1f32(d0 * u0.y, v0.y, acc.c01, 0, 0, 0);
-    acc.c11 = __builtin_amdgcn_mfma_f32_4x4x1f32(d1 * u1.x, v1.x, acc.c11, 0, 0, 0);
-    acc.c00 = __builtin_amdgcn_mfma_f32_4x4x1f32(d1 * u1.y, v1.y, acc.c00, 0, 0, 0);
+    acc.r00 = __builtin_amdgcn_mfma_f32_4x4x1f32(d0 * u0.x, v0.x, acc.r00, 0, 0, 0);
+    acc.i00 = __builtin_amdgcn_mfma_f32_4x4x1f32(d0 * u0.y, v0.y, acc.i00, 0, 0, 0);
+    acc.r01 = __builtin_amdgcn_mfma_f32_4x4x1f32(d1 * u1.x, v1.x, acc.r01, 0, 0, 0);
+    acc.i01 = __builtin_amdgcn_mfma_f32_4x4x1f32(d1 * u1.y, v1.y, acc.i01, 0, 0, 0);
   }
 }
 
@@ -694,10 +695,10 @@ __device__ __forceinline__ void mfma_contract_4x4_range(const float2* A, const f
     const int zp0 = lds_pos<true>(z), zp1 = lds_pos<true>(z + 1);
     const float d0 = dl[z], d1 = dl[z + 1];
     const float2 u0 = ra[zp0], v0 = rb[zp0], u1 = ra[zp1], v1 = rb[zp1];
-    acc.c00 = __builtin_amdgcn_mfma_f32_4x4x1f32(d0 * u0.x, v0.x, acc.c00, 0, 0, 0);
-    acc.c01 = __builtin_amdgcn_mfma_f32_4x4x1f32(d0 * u0.y, v0.y, acc.c01, 0, 0, 0);
-    acc.c11 = __builtin_amdgcn_mfma_f32_4x4x1f32(d1 * u1.x, v1.x, acc.c11, 0, 0, 0);
-    acc.c00 = __builtin_amdgcn_mfma_f32_4x4x1f32(d1 * u1.y, v1.y, acc.c00, 0, 0, 0);
+    acc.r00 = __builtin_amdgcn_mfma_f32_4x4x1f32(d0 * u0.x, v0.x, acc.r00, 0, 0, 0);
+    acc.i00 = __builtin_amdgcn_mfma_f32_4x4x1f32(d0 * u0.y, v0.y, acc.i00, 0, 0, 0);
+    acc.r01 = __builtin_amdgcn_mfma_f32_4x4x1f32(d1 * u1.x, v1.x, acc.r01, 0, 0, 0);
+    acc.i01 = __builtin_amdgcn_mfma_f32_4x4x1f32(d1 * u1.y, v1.y, acc.i01, 0, 0, 0);
   }
 }
 
@@ -754,7 +755,7 @@ __device__ __forceinline__ void mfma_contract_bf16x3(const float2* A, const floa
     mp3_s4 ah, al, bh, bl;
     bf16_split4(xa, ah, al);
     bf16_split4(xb, bh, bl);
-    acc.c00 = mfma3(ah, al, bh, bl, acc.c00);
+    acc.r00 = mfma3(ah, al, bh, bl, acc.r00);
     if (two) {
       u0 = ok1 ? r1[p0] : make_float2(0.f, 0.f);
       u1 = ok1 ? r1[p1] : make_float2(0.f, 0.f);
@@ -763,8 +764,8 @@ __device__ __forceinline__ void mfma_contract_bf16x3(const float2* A, const floa
       mp3_s4 ch, cl, dh, dlo;
       bf16_split4(ya, ch, cl);
       bf16_split4(yb, dh, dlo);
-      acc.c01 = mfma3(ah, al, dh, dlo, acc.c01);
-      acc.c11 = mfma3(ch, cl, dh, dlo, acc.c11);
+      acc.r01 = mfma3(ah, al, dh, dlo, acc.r01);
+      acc.r11 = mfma3(ch, cl, dh, dlo, acc.r11);
     }
   }
 }
@@ -792,9 +793,8 @@ struct Contractor {
     }
 #pragma unroll
     for (int i = 0; i < (MF ? 1 : 16); ++i) acc[i] = (T)0;
-    macc.c00 = typename acc4<T>::type{0, 0, 0, 0};
-    macc.c01 = macc.c00;
-    macc.c11 = macc.c00;
+    macc.r00 = typename acc4<T>::type{0, 0, 0, 0};
+    macc.r01 = macc.r11 = macc.i00 = macc.i01 = macc.i11 = macc.r00;
   }
 
   // K positions (even), weights w[k] in LDS
@@ -840,8 +840,22 @@ struct Contractor {
     return MF ? (size_t)(threads / 64) * 3 * 256 * sizeof(double) : (size_t)threads * 16 * sizeof(double);
   }
 
-  // workgroup reduction through LDS scratch red, symmetric partial to out[nbins^2]
-  __device__ void finish(double* red, double* out, int nbins) {
+  // workgroup reduction through LDS scratch red, symmetric partial to out[nbins^2]; pair (matrix-core
+  // forms): the real parts' sum there and the imaginary parts' behind it
+  __device__ void finish(double* red, double* out, int nbins, bool pair = false) {
+    if constexpr (MF) {
+      if (pair) {
+        finish_part(red, out, nbins, 1.0, 0.0);
+        __syncthreads();
+        finish_part(red, out + nbins * nbins, nbins, 0.0, 1.0);
+        return;
+      }
+    }
+    finish_part(red, out, nbins, 1.0, 1.0);
+  }
+
+  // wr times the real parts' sum plus wi times the imaginary parts'
+  __device__ void finish_part(double* red, double* out, int nbins, double wr, double wi) {
     const int tid = threadIdx.x;
     if constexpr (MF && QUAD) {
       // red[w][beta][row][col] for the 15 (g1, g2) 4x4 blocks
@@ -849,7 +863,7 @@ struct Contractor {
 #pragma unroll
       for (int i = 0; i < 4; ++i)
         red[(w * 16 + (lane >> 2)) * 16 + i * 4 + (lane & 3)] =
-            (double)macc.c00[i] + (double)macc.c01[i] + (double)macc.c11[i];
+            wr * ((double)macc.r00[i] + (double)macc.r01[i]) + wi * ((double)macc.i00[i] + (double)macc.i01[i]);
       __syncthreads();
       for (int t = tid; t < 15 * 16; t += blockDim.x) {
         const int beta = t / 16, row = (t / 4) % 4, col = t % 4;
@@ -870,9 +884,9 @@ struct Contractor {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int row = mfma_row<T>(lane, i), col = lane & 15;
-        red[((w * 3 + 0) * 16 + row) * 16 + col] = (double)macc.c00[i];
-        red[((w * 3 + 1) * 16 + row) * 16 + col] = (double)macc.c01[i];
-        red[((w * 3 + 2) * 16 + row) * 16 + col] = (double)macc.c11[i];
+        red[((w * 3 + 0) * 16 + row) * 16 + col] = wr * (double)macc.r00[i] + wi * (double)macc.i00[i];
+        red[((w * 3 + 1) * 16 + row) * 16 + col] = wr * (double)macc.r01[i] + wi * (double)macc.i01[i];
+        red[((w * 3 + 2) * 16 + row) * 16 + col] = wr * (double)macc.r11[i] + wi * (double)macc.i11[i];
       }
       __syncthreads();
       for (int t = tid; t < 3 * 256; t += blockDim.x) {
@@ -1383,11 +1397,16 @@ __global__ void k_reduce_items(const double* partials, int nwg, int nb2, double*
   const int e = blockIdx.x, j = blockIdx.y;
   for (int g = 0; g < nitems; ++g) {
     const ItemRec& it = items[item0 + g];
-    const double* p = partials + ((long long)g * batch + j) * nwg * nb2 + e;
-    double s = 0.0;
-    for (int w = threadIdx.x; w < nwg; w += blockDim.x) s += p[(long long)w * nb2];
-    s = block_sum(s, sh);
-    if (threadIdx.x == 0) zeta[((long long)j * (lmax + 1) + it.l) * nb2 + e] += scale * it.wm * s;
+    // a pair item's workgroups leave two sums, of multipoles l and l2
+    const int parts = it.l2 >= 0 ? 2 : 1;
+    for (int part = 0; part < parts; ++part) {
+      const double* p = partials + (((long long)g * batch + j) * nwg * parts + part) * nb2 + e;
+      double s = 0.0;
+      for (int w = threadIdx.x; w < nwg; w += blockDim.x) s += p[(long long)w * parts * nb2];
+      s = block_sum(s, sh);
+      if (threadIdx.x == 0) zeta[((long long)j * (lmax + 1) + (part ? it.l2 : it.l)) * nb2 + e] += scale * it.wm * s;
+      __syncthreads();
+    }
   }
 }
 
@@ -1435,7 +1454,8 @@ k_zpass(c2<T>* fields, const T* delta, const T* __restrict__ lam_d, T* direct, i
   c2<T>* A = reinterpret_cast<c2<T>*>(smem);
   c2<T>* tws = A + nbins * RS;
   T* lam = reinterpret_cast<T*>(tws + N);             // [NBP] eigenvalues of the cotangent, zero padded
-  T* dl = lam + (GRAD ? NBP : 0);                     // FUSED: delta of the pencil
+  T* lam2 = lam + (GRAD ? NBP : 0);                   // [NBP] those of a pair item's second multipole
+  T* dl = lam2 + (GRAD ? NBP : 0);                     // FUSED: delta of the pencil
   const int tid = threadIdx.x;
   const int nbc = blockDim.x / F::TPC;
   const int nb2 = nbins * nbins;
@@ -1459,10 +1479,17 @@ k_zpass(c2<T>* fields, const T* delta, const T* __restrict__ lam_d, T* direct, i
     const int chunk = unit % nwg;
     const ItemRec& it = items[item0 + g];
     const T wm = (T)it.wm;
+    // a pair item holds two real fields: their sources are d a (no conjugate), each with its own multipole's d
+    const bool pair = it.l2 >= 0;
+    const T sgn = pair ? (T)1 : (T)-1;
     stage_twiddles<N, T>(tw, tws);
     if constexpr (GRAD) {
       const T* ls = lam_d + ((long long)it.l * batch + mock) * nbins;
-      for (int t = tid; t < NBP; t += blockDim.x) lam[t] = t < nbins ? ls[t] : (T)0;
+      const T* ls2 = pair ? lam_d + ((long long)it.l2 * batch + mock) * nbins : ls;
+      for (int t = tid; t < NBP; t += blockDim.x) {
+        lam[t] = t < nbins ? ls[t] : (T)0;
+        lam2[t] = t < nbins ? ls2[t] : (T)0;
+      }
     }
     __syncthreads();
     Contractor<T, MF, SPLIT, QUAD> ctr;
@@ -1540,20 +1567,21 @@ k_zpass(c2<T>* fields, const T* delta, const T* __restrict__ lam_d, T* direct, i
         const int zp = lds_pos<true>(z);
         // in the eigenbasis of the cotangent the source of field k is
         // d_k conj(a_k) delta and the direct term sum_k d_k |a_k|^2
-        const T d = dcur[k];
+        const T d = dcur[k], ds = sgn * d;
         T dir = 0;
 #pragma unroll
         for (int bq = 0; bq < NBP; bq += 4) {
-          T lq[4];
+          T lq[4], lq2[4];
           load_quad<T>(lam + bq, lq);                // LDS broadcast
+          load_quad<T>(lam2 + bq, lq2);
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             const int b = bq + i;
             if (b < nbins) {
               const c2<T> a = A[b * RS + zp];
-              const T e = lq[i] * a.x, f = lq[i] * a.y;
+              const T e = lq[i] * a.x, f = lq2[i] * a.y;
               dir += e * a.x + f * a.y;
-              A[b * RS + zp] = mk<T>(d * e, -(d * f));
+              A[b * RS + zp] = mk<T>(d * e, ds * f);
             }
           }
         }
@@ -1584,8 +1612,8 @@ k_zpass(c2<T>* fields, const T* delta, const T* __restrict__ lam_d, T* direct, i
       __syncthreads();
     }
     if constexpr (FUSED)
-      ctr.finish(reinterpret_cast<double*>(smem), partials + (((long long)g * batch + mock) * nwg + chunk) * nb2,
-                 nbins);
+      ctr.finish(reinterpret_cast<double*>(smem),
+                 partials + (((long long)g * batch + mock) * nwg + chunk) * nb2 * (pair ? 2 : 1), nbins, pair);
   }
 }
 
@@ -1791,8 +1819,10 @@ __global__ void __launch_bounds__(256) k_rotate_zeta(double* zeta, const double*
 // float32: four waves per SIMD (128 registers; the angular factors wait in
 // LDS, so the bin loop holds the bin sum, the column and the window values)
 // SPLIT: grid.z splits the items of the group, and the shares meet in G atomically
-template <int N, typename T, bool SPLIT>
-__global__ void __launch_bounds__((strided_threads<N, T, VB>())) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 1)))
+// PAIR: sources c = c_l + i c_l2 of two real fields.  K_l ifft(c_l) and the rest are the spectra of real
+// fields, so the window K_l - i K_l2 leaves their sum in the real part of the gradient's transform.
+template <int N, typename T, bool SPLIT, bool PAIR>
+__global__ void __launch_bounds__((strided_threads<N, T, VB>())) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? (PAIR ? 2 : 4) : 1)))
 k_adjoint_y(const c2<T>* fields, c2<T>* G,
                                                                           const T* jtab, int jmocks, int nq2, int nbins,
                                                                           int nbp, const ItemRec* items, int item0,
@@ -1840,10 +1870,14 @@ k_adjoint_y(const c2<T>* fields, c2<T>* G,
       facs[e * blockDim.x + tid] =
           window_angular<T>(qx, F::out_index(j, e), qz, N, it.l, it.m, it.norm, scale * it.wm, it.yr, q2e, phi);
     }
-    c2<T> acc[RMAX];
+    c2<T> acc[RMAX], acc2[PAIR ? RMAX : 1];
 #pragma unroll
-    for (int e = 0; e < RMAX; ++e) acc[e] = mk<T>(0, 0);
+    for (int e = 0; e < RMAX; ++e) {
+      acc[e] = mk<T>(0, 0);
+      if constexpr (PAIR) acc2[e] = mk<T>(0, 0);
+    }
     const T* jl = jtab + ((long long)it.l * jmocks + mock % jmocks) * nq2 * nbp;
+    const T* jl2 = PAIR ? jtab + ((long long)it.l2 * jmocks + mock % jmocks) * nq2 * nbp : nullptr;
     const c2<T>* src = fields + ((long long)gi * batch + mock) * nbins * N3 + (long long)qx * N * N + qz;
     // next bin's column, one bin ahead
     c2<T> vn[RMAX];
@@ -1852,9 +1886,12 @@ k_adjoint_y(const c2<T>* fields, c2<T>* G,
       for (int r = 0; r < RMAX; ++r) vn[r] = nt_load(&src[F::in_index(j, r) * N]);
     }
     for (int bq = 0; bq < nbins; bq += 4) {
-      T jq[RMAX][4];
+      T jq[RMAX][4], j2[PAIR ? RMAX : 1][4];
 #pragma unroll
-      for (int e = 0; e < RMAX; ++e) load_quad<T>(jl + (long long)q2[e] * nbp + bq, jq[e]);
+      for (int e = 0; e < RMAX; ++e) {
+        load_quad<T>(jl + (long long)q2[e] * nbp + bq, jq[e]);
+        if constexpr (PAIR) load_quad<T>(jl2 + (long long)q2[e] * nbp + bq, j2[e]);
+      }
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const int b = bq + k;
@@ -1873,8 +1910,22 @@ k_adjoint_y(const c2<T>* fields, c2<T>* G,
           for (int e = 0; e < RMAX; ++e) {
             acc[e].x += jq[e][k] * v[e].x;
             acc[e].y += jq[e][k] * v[e].y;
+            if constexpr (PAIR) {
+              acc2[e].x += j2[e][k] * v[e].x;
+              acc2[e].y += j2[e][k] * v[e].y;
+            }
           }
         }
+      }
+    }
+    if constexpr (PAIR) {
+#pragma unroll
+      for (int e = 0; e < RMAX; ++e) acc[e] = cmul<T>(acc[e], facs[e * blockDim.x + tid]);
+#pragma unroll 1
+      for (int e = 0; e < RMAX; ++e) {
+        int q2e;
+        facs[e * blockDim.x + tid] =
+            window_angular<T>(qx, F::out_index(j, e), qz, N, it.l2, 0, it.norm2, scale * it.wm, it.yr2, q2e, phi);
       }
     }
     // the window's angular factor is common to every bin: applied once, into G
@@ -1882,7 +1933,9 @@ k_adjoint_y(const c2<T>* fields, c2<T>* G,
 #pragma unroll
       for (int e = 0; e < RMAX; ++e) {
         c2<T>* p = dst + F::out_index(j, e) * N;
-        const c2<T> v = cmul<T>(acc[e], facs[e * blockDim.x + tid]);
+        c2<T> v;
+        if constexpr (PAIR) v = cadd<T>(acc[e], mul_i<-1, T>(cmul<T>(acc2[e], facs[e * blockDim.x + tid])));
+        else v = cmul<T>(acc[e], facs[e * blockDim.x + tid]);
         if constexpr (SPLIT) {
           unsafeAtomicAdd(&p->x, v.x);
           unsafeAtomicAdd(&p->y, v.y);
@@ -2154,10 +2207,10 @@ hipError_t filter_y_t(const FilterArgs& a, hipStream_t st) {
   constexpr int G = tiles_per_wg<N, T, VB>();
   constexpr int threads = Fft<N, VB>::TPC * ZC * G;
   const dim3 gs((N * (N / ZC) + G - 1) / G, a.batch * a.nitems);
-  k_filter_y<N, T><<<gs, threads, 0, st>>>(static_cast<const CT<T>*>(a.src), static_cast<CT<T>*>(a.dst),
-                                          static_cast<const T*>(a.jtab), a.jmocks, a.nq2, a.nbins, a.nbp, a.items,
-                                          a.item0, a.batch, a.scale, static_cast<const CT<T>*>(a.tw),
-                                          static_cast<const T*>(a.phi));
+  auto kern = a.pair ? k_filter_y<N, T, true> : k_filter_y<N, T, false>;
+  kern<<<gs, threads, 0, st>>>(static_cast<const CT<T>*>(a.src), static_cast<CT<T>*>(a.dst),
+                               static_cast<const T*>(a.jtab), a.jmocks, a.nq2, a.nbins, a.nbp, a.items, a.item0,
+                               a.batch, a.scale, static_cast<const CT<T>*>(a.tw), static_cast<const T*>(a.phi));
   return hipGetLastError();
 }
 
@@ -2173,7 +2226,8 @@ hipError_t adjoint_y_t(const FilterArgs& a, hipStream_t st) {
   split = split < 1 ? 1 : split > a.nitems ? a.nitems : split;
   const dim3 gs(tiles, a.batch, split);
   const size_t dyn = (size_t)threads * Fft<N, VB>::RMAX * sizeof(CT<T>);
-  auto kern = split > 1 ? k_adjoint_y<N, T, true> : k_adjoint_y<N, T, false>;
+  auto kern = a.pair ? (split > 1 ? k_adjoint_y<N, T, true, true> : k_adjoint_y<N, T, false, true>)
+                     : (split > 1 ? k_adjoint_y<N, T, true, false> : k_adjoint_y<N, T, false, false>);
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)dyn);
   if (e != hipSuccess) return e;
@@ -2210,7 +2264,7 @@ template <int N, typename T> inline size_t zpass_adjoint_lds(int nbins) {
   // the cotangent's eigenvalues, padded to the largest MAXNB that serves nbins
   const size_t maxnb = nbins <= 8 ? 8 : nbins <= 12 ? 12 : nbins <= 16 ? 16 : nbins <= 20 ? 20 : nbins <= 24 ? 24
                        : nbins <= 32 ? 32 : nbins <= 48 ? 48 : 64;
-  return (size_t)nbins * RS * sizeof(CT<T>) + (size_t)N * sizeof(CT<T>) + maxnb * sizeof(T);
+  return (size_t)nbins * RS * sizeof(CT<T>) + (size_t)N * sizeof(CT<T>) + 2 * maxnb * sizeof(T);
 }
 
 template <typename K> hipError_t allow_lds(K kernel, size_t bytes) {

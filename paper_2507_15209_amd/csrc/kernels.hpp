@@ -30,6 +30,11 @@ struct ItemRec {
   double norm;       // Y_lm normalisation
   double wm;         // m weight of the contraction: 1 for m = 0, 2 otherwise
   YlmRec yr;         // Legendre recurrence of (l, m)
+  // pair item: the field of m = 0 is real, so that one complex transform carries those of two
+  // multipoles, a = a_l + i a_l2 (l2 < 0: none)
+  int l2;
+  double norm2;
+  YlmRec yr2;
 };
 
 // Window passes over a group of nitems consecutive items of the table,
@@ -44,6 +49,7 @@ struct FilterArgs {
   int nq2, nbins, nbp, batch;
   const ItemRec* items;   // device item table
   int item0, nitems;
+  bool pair = false;      // pair items (a launch holds one kind)
   double scale;      // real factor (1/N^3); the adjoint pass also takes each item's m weight
   const void* phi = nullptr;   // [N] per-axis phi-hat factors (real), or NULL for none
 };

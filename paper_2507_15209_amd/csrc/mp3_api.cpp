@@ -31,7 +31,8 @@ struct mp3_plan_s {
   double* btab = nullptr;   // Daubechies-4 basis: phi at the dyadic points (NULL for the B-spline)
   mp3::Acf acf{{2416.0 / 5040.0, 1191.0 / 5040.0, 120.0 / 5040.0, 1.0 / 5040.0}};   // basis autocorrelation
   mp3::BandRule band{};      // the basis' connection coefficients as points and as a band (grid summation)
-  std::vector<mp3::ItemRec> items;   // every (l, m >= 0) of the plan, index l (l + 1) / 2 + m
+  std::vector<mp3::ItemRec> items;   // every (l, m >= 0) of the plan, index l (l + 1) / 2 + m, then the work items
+  int work0 = 0, npairs = 0;         // work items: npairs pairs of m = 0 fields, then the single items
   mp3::ItemRec* items_dev = nullptr; // the same table on the device
   // optional per-pass HIP event timing
   bool profile = false;
@@ -114,7 +115,7 @@ int tile_shift(int side) { return side == 4 ? 2 : (side == 8 ? 3 : 4); }
 constexpr double kGroupBudget = 1073741824.0;
 
 int item_group(const mp3_plan_s* p) {
-  const int total = (int)p->items.size();
+  const int total = p->work0;
   if (p->summation != MP3_SUM_NODAL) return 1;
   int g = p->tune[MP3_TUNE_ITEM_GROUP];
   if (g <= 0) {
@@ -396,6 +397,19 @@ int lam_eig_all(const mp3_plan_s* p, const double* dzeta, void* ws, const Layout
   return MP3_OK;
 }
 
+// whether a call runs the paired items: not where one launch takes every (l, m) (pairs would be a second
+// one: 32^3, 15 items 330 us plain, 412 us paired), nor with a single partial sum per item (pairs leave two)
+bool paired(const mp3_plan_s* p, const Layout& L) { return p->npairs > 0 && L.nwg >= 2 && L.group < p->work0; }
+
+int first_item(const mp3_plan_s* p, const Layout& L) { return paired(p, L) ? p->work0 : 0; }
+
+// work items of the launch that starts at item0: up to the group size, of one kind; 0 at the end
+int group_size(const mp3_plan_s* p, const Layout& L, int item0) {
+  const int pairs_end = p->work0 + p->npairs;
+  const int end = !paired(p, L) ? p->work0 : item0 < pairs_end ? pairs_end : (int)p->items.size();
+  return std::min(L.group, end - item0);
+}
+
 // rotated: the radial tables of the cotangents' eigenbasis (lam_eig_all), one per (l, mock)
 mp3::FilterArgs filter_args(const mp3_plan_s* p, void* ws, const Layout& L, const void* src, void* dst, int item0,
                             int nitems, bool rotated = false) {
@@ -412,6 +426,7 @@ mp3::FilterArgs filter_args(const mp3_plan_s* p, void* ws, const Layout& L, cons
   a.items = p->items_dev;
   a.item0 = item0;
   a.nitems = nitems;
+  a.pair = p->items[item0].l2 >= 0;
   a.scale = 1.0 / ((double)p->n * p->n * p->n);
   a.phi = p->phi;
   return a;
@@ -431,7 +446,9 @@ mp3::ZpassArgs adjoint_zargs(const mp3_plan_s* p, void* ws, const Layout& L, voi
   // the launch's workgroups over all of its items: several pencils each rather than a partial sum
   // (and its reduction) per pencil on small grids
   const int per = p->tune[MP3_TUNE_ZPASS_WGS] / (p->batch * nitems);
-  const int pencils = p->n * p->n, nwg = per < 1 ? 1 : per < L.nwg ? per : L.nwg;
+  // pair items leave two partial sums per workgroup
+  const int most = p->items[item0].l2 >= 0 ? std::max(1, L.nwg / 2) : L.nwg;
+  const int pencils = p->n * p->n, nwg = per < 1 ? 1 : per < most ? per : most;
   z.ppw = (pencils + nwg - 1) / nwg;
   z.nwg = (pencils + z.ppw - 1) / z.ppw;
   z.batch = p->batch;
@@ -583,6 +600,7 @@ int mp3_plan_create(const mp3_plan_desc* d, mp3_plan_t* out) {
       it.m = m;
       it.norm = mp3::ylm_norm(l, m);
       it.wm = m == 0 ? 1.0 : 2.0;
+      it.l2 = -1;
       it.yr.pmm = 1.0;
       for (int k = 1; k <= m; ++k) it.yr.pmm *= -(2.0 * k - 1.0);
       for (int k = 0; k < 21; ++k) {
@@ -592,6 +610,24 @@ int mp3_plan_create(const mp3_plan_desc* d, mp3_plan_t* out) {
       p->items.push_back(it);
     }
   }
+  // work items: the real m = 0 fields of neighbouring multipoles two by two (half their transforms)
+  // where the contraction keeps the parts apart (matrix cores), then everything else
+  p->work0 = (int)p->items.size();
+  const bool pairs = p->summation == MP3_SUM_NODAL && !p->split && p->nbins <= (p->prec ? 16 : 32);
+  if (pairs) {
+    for (int l = 0; l + 1 <= p->lmax; l += 2) {
+      mp3::ItemRec it = p->items[item_index(l, 0)];
+      const mp3::ItemRec& o = p->items[item_index(l + 1, 0)];
+      it.l2 = o.l;
+      it.norm2 = o.norm;
+      it.yr2 = o.yr;
+      p->items.push_back(it);
+      ++p->npairs;
+    }
+  }
+  for (int l = 0; l <= p->lmax; ++l)
+    for (int m = 0; m <= l; ++m)
+      if (m > 0 || l >= 2 * p->npairs) p->items.push_back(mp3::ItemRec(p->items[item_index(l, m)]));
   const size_t ib = p->items.size() * sizeof(mp3::ItemRec);
   if (p->basis == MP3_BASIS_BSPLINE3) b3_band(p->band);
   hipError_t e4 = hipMalloc(&p->items_dev, ib);
@@ -818,9 +854,7 @@ int zeta_nodal(mp3_plan_t p, const void* delta, double* zeta, void* ws, const La
   const double n3 = (double)p->n * p->n * p->n;
   void* F = at(ws, L.fields);
   double* partials = reinterpret_cast<double*>(at(ws, L.partials));
-  const int nitems_all = (int)p->items.size();
-  for (int item0 = 0; item0 < nitems_all; item0 += L.group) {
-    const int ni = std::min(L.group, nitems_all - item0);
+  for (int item0 = first_item(p, L), ni; (ni = group_size(p, L, item0)) > 0; item0 += ni) {
     if (int s = fields_xy(p, ws, L, F, item0, ni, st)) return s;
     mp3::ZpassArgs z = adjoint_zargs(p, ws, L, F, delta, nullptr, nullptr, item0, ni);
     z.partials = partials;
@@ -1311,9 +1345,7 @@ int mp3_zeta_backward(mp3_plan_t p, const void* delta, const double* dzeta, void
   void* direct = at(ws, L.direct);
   MP3_HIP(mp3::launch_fill(p->prec, G, 2 * n3 * p->batch, 0.0, st), "zero G");
   MP3_HIP(mp3::launch_fill(p->prec, direct, n3 * p->batch, 0.0, st), "zero direct");
-  const int nitems_all = (int)p->items.size();
-  for (int item0 = 0; item0 < nitems_all; item0 += L.group) {
-    const int ni = std::min(L.group, nitems_all - item0);
+  for (int item0 = first_item(p, L), ni; (ni = group_size(p, L, item0)) > 0; item0 += ni) {
     if (int s = fields_xy(p, ws, L, F, item0, ni, st, true)) return s;
     mp3::ZpassArgs z = adjoint_zargs(p, ws, L, F, prim, dzeta, direct, item0, ni);
     MP3_HIP(timed(p, MP3_PASS_Z_ADJOINT, st, [&] { return mp3::launch_zpass_adjoint(p->n, p->prec, z, st); }), "z pass (adjoint)");
@@ -1364,9 +1396,7 @@ int mp3_zeta_value_and_grad(mp3_plan_t p, const void* delta, const double* dzeta
   MP3_HIP(mp3::launch_fill_f64(zeta, (long long)p->batch * (p->lmax + 1) * nb2, 0.0, st), "zero zeta");
   MP3_HIP(mp3::launch_fill(p->prec, G, 2 * n3 * p->batch, 0.0, st), "zero G");
   MP3_HIP(mp3::launch_fill(p->prec, direct, n3 * p->batch, 0.0, st), "zero direct");
-  const int nitems_all = (int)p->items.size();
-  for (int item0 = 0; item0 < nitems_all; item0 += L.group) {
-    const int ni = std::min(L.group, nitems_all - item0);
+  for (int item0 = first_item(p, L), ni; (ni = group_size(p, L, item0)) > 0; item0 += ni) {
     if (int s = fields_xy(p, ws, L, F, item0, ni, st, true)) return s;
     mp3::ZpassArgs z = adjoint_zargs(p, ws, L, F, prim, dzeta, direct, item0, ni);
     z.partials = partials;

@@ -57,3 +57,37 @@ def test_bin_counts(prec, form, n, nb):
     for a, b in ((g, g2), (dw, dw2)):
         a, b = a.double().cpu().numpy(), b.double().cpu().numpy()
         assert np.abs(a - b).max() <= 2 * TOL[prec] * np.abs(b).max()
+
+
+@pytest.mark.parametrize("form,lmax,nb", [("nodal", 1, 3), ("nodal", 2, 16), ("nodal", 3, 20), ("gamma", 1, 3),
+                                          ("gamma", 2, 5), ("gamma", 3, 2)])
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+def test_paired_multipoles(prec, form, lmax, nb):
+    """The m = 0 fields of two multipoles in one transform (one (l, m) per launch, so that the nodal form
+    pairs too): value and gradient of mocks with cotangents of their own against the oracle."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2507_15209_amd as mp3
+    from mockgen import random_field
+    from oracle import adjoint as A
+    from tests._common import assert_grad_close
+    print("[case] paired multipoles", prec, form, lmax, nb, flush=True)
+    n, box = 16, 160.0
+    edges = np.linspace(16.0, 56.0, nb + 1)
+    delta = np.stack([random_field(n, 611), random_field(n, 612)]).astype(np.float32).astype(np.float64)
+    lam = np.random.default_rng(613).standard_normal((2, lmax + 1, nb, nb))
+    plan = mp3.Plan(n, box, lmax, edges, precision=prec, summation=form, batch=2)
+    plan.tune_set("item_group", 1)
+    d = torch.as_tensor(delta, dtype=torch.float64 if prec == "f64" else torch.float32, device="cuda")
+    lt = torch.as_tensor(lam, device="cuda")
+    z0 = plan.zeta(d).cpu().numpy()
+    z, g, _ = (t if t is None else t.cpu().numpy() for t in plan.zeta_value_and_grad(d, lt))
+    g2 = plan.zeta_backward(d, lt)[0].cpu().numpy()
+    op = E.Plan(n, box, lmax, edges)
+    for j in range(2):
+        ref = E.zeta_nodal(op, delta[j]) if form == "nodal" else E.zeta_gamma_quadrature(op, delta[j])
+        gref = (A.zeta_nodal_grad if form == "nodal" else A.zeta_gamma_grad)(op, delta[j], lam[j])
+        assert_zeta_close(z0[j], ref, TOL[prec])
+        assert_zeta_close(z[j], ref, TOL[prec])
+        assert_grad_close(g[j], gref, TOL[prec], "one sweep")
+        assert_grad_close(g2[j], gref, TOL[prec], "backward")
