@@ -75,11 +75,11 @@ struct ContractLds {
 // Bound by instruction issue (vector ALU, LDS and matrix products share a wave's
 // issue slots); partial sums are float32 over a wave's march as the fields are,
 // float64 beyond.  Against 5^3 Gauss points per cell interpolated into LDS rows: 256^3, 20
-// bins 160.7 -> 17.8 ms per (l, m); 128^3, 15 bins 14.0 -> 0.85 ms.
+// bins 160.7 -> 17.8 ms per item; 128^3, 15 bins 14.0 -> 0.85 ms.
 template <typename T, int Q, int TP, int H, int TY, int NH>
 __global__ void __launch_bounds__(TY* Q * 64)
     k_band_contract(const c2<T>* fields, const T* prim, int n, int nbt, int a0, int na, int c0, int nl, int off,
-                    RuleT<T, Q, TP, H> rule, int nseg, double* partials) {
+                    RuleT<T, Q, TP, H> rule, int nseg, int pair, double* partials) {
   using L_ = ContractLds<T, Q, TP, TY, NH>;
   constexpr int ZC = L_::ZC, ZG = L_::ZG, YG = L_::YG, NODES = L_::NODES, NT = TY * Q * 64, W = TY * Q;
   constexpr int CELLS = YG * ZG, PF = (CELLS * 16 * NH + NT - 1) / NT, WIN = H + 1;
@@ -114,11 +114,12 @@ __global__ void __launch_bounds__(TY* Q * 64)
   int bc[NH];
 #pragma unroll
   for (int h = 0; h < NH; ++h) bc[h] = 16 * h + bl < nl ? 16 * h + bl : 0;   // absent bins: dropped at the end
-  A4 acc[NH][NH];
+  // the real and the imaginary parts' products apart: the parts of a pair item are two multipoles' fields
+  A4 acc[2][NH][NH];
 #pragma unroll
   for (int i = 0; i < NH; ++i)
 #pragma unroll
-    for (int k = 0; k < NH; ++k) acc[i][k] = A4{0, 0, 0, 0};
+    for (int k = 0; k < NH; ++k) acc[0][i][k] = acc[1][i][k] = A4{0, 0, 0, 0};
 
   const int tz = n / ZC, ty = n / TY, ntask = ty * tz * nseg, seg = n / nseg;
   for (int task0 = blockIdx.x; task0 < ntask; task0 += gridDim.x) {
@@ -251,11 +252,11 @@ __global__ void __launch_bounds__(TY* Q * 64)
 #pragma unroll
                 for (int h1 = 0; h1 < NH; ++h1)
 #pragma unroll
-                  for (int h2 = 0; h2 < NH; ++h2) acc[h1][h2] = mfma16(win[h1][u][s].x, g[h2].x, acc[h1][h2]);
+                  for (int h2 = 0; h2 < NH; ++h2) acc[0][h1][h2] = mfma16(win[h1][u][s].x, g[h2].x, acc[0][h1][h2]);
 #pragma unroll
                 for (int h1 = 0; h1 < NH; ++h1)
 #pragma unroll
-                  for (int h2 = 0; h2 < NH; ++h2) acc[h1][h2] = mfma16(win[h1][u][s].y, g[h2].y, acc[h1][h2]);
+                  for (int h2 = 0; h2 < NH; ++h2) acc[1][h1][h2] = mfma16(win[h1][u][s].y, g[h2].y, acc[1][h1][h2]);
               }
             }
           }
@@ -264,29 +265,35 @@ __global__ void __launch_bounds__(TY* Q * 64)
     }
     __syncthreads();   // the next task refills both planes
   }
-  // T[b1][b2] over the waves in float64, then T + T^T
+  // T[b1][b2] over the waves in float64, then T + T^T; a pair item's parts one after the other
   double* red = reinterpret_cast<double*>(smem);
   double* tt = red + W * 256;   // [NH][NH][16][16]
+  const int parts = pair ? 2 : 1;
+  for (int part = 0; part < parts; ++part) {
 #pragma unroll
-  for (int h1 = 0; h1 < NH; ++h1)
+    for (int h1 = 0; h1 < NH; ++h1)
 #pragma unroll
-    for (int h2 = 0; h2 < NH; ++h2) {
-      __syncthreads();
+      for (int h2 = 0; h2 < NH; ++h2) {
+        __syncthreads();
 #pragma unroll
-      for (int i = 0; i < 4; ++i) red[wave * 256 + mfma_row<T>(lane, i) * 16 + bl] = (double)acc[h1][h2][i];
-      __syncthreads();
-      for (int e = tid; e < 256; e += NT) {
-        double s = 0.0;
-        for (int w = 0; w < W; ++w) s += red[w * 256 + e];
-        tt[(h1 * NH + h2) * 256 + e] = s;
+        for (int i = 0; i < 4; ++i) {
+          const double re = (double)acc[0][h1][h2][i], im = (double)acc[1][h1][h2][i];
+          red[wave * 256 + mfma_row<T>(lane, i) * 16 + bl] = !pair ? re + im : part == 0 ? re : im;
+        }
+        __syncthreads();
+        for (int e = tid; e < 256; e += NT) {
+          double s = 0.0;
+          for (int w = 0; w < W; ++w) s += red[w * 256 + e];
+          tt[(h1 * NH + h2) * 256 + e] = s;
+        }
       }
+    __syncthreads();
+    double* out = partials + (((long long)blockIdx.y * gridDim.x + blockIdx.x) * parts + part) * nl * nl;
+    for (int e = tid; e < nl * nl; e += NT) {
+      const int b1 = e / nl, b2 = e % nl;
+      out[e] = tt[((b1 / 16) * NH + b2 / 16) * 256 + (b1 % 16) * 16 + b2 % 16] +
+               tt[((b2 / 16) * NH + b1 / 16) * 256 + (b2 % 16) * 16 + b1 % 16];
     }
-  __syncthreads();
-  double* out = partials + ((long long)blockIdx.y * gridDim.x + blockIdx.x) * nl * nl;
-  for (int e = tid; e < nl * nl; e += NT) {
-    const int b1 = e / nl, b2 = e % nl;
-    out[e] = tt[((b1 / 16) * NH + b2 / 16) * 256 + (b1 % 16) * 16 + b2 % 16] +
-             tt[((b2 / 16) * NH + b1 / 16) * 256 + (b2 % 16) * 16 + b1 % 16];
   }
 }
 
@@ -368,7 +375,7 @@ struct AdjointLds {
 // bins float32 38 -> 3.3 ms per (l, m) with the contraction apart; 32^3, 6 bins float64 0.46 -> 0.05 ms.
 template <typename T, int Q, int TP, int H, int TY, int PT, int PO>
 __global__ void __launch_bounds__(TY* Q * 64)
-    k_band_adjoint(const c2<T>* fields, const T* prim, const T* lam_d, int n, int nbt, int off,
+    k_band_adjoint(const c2<T>* fields, const T* prim, const T* lam_d, const T* lam_d2, T sgn, int n, int nbt, int off,
                    RuleT<T, Q, TP, H> rule, T wm, int nseg, int nchunk, c2<T>* out, T* direct) {
   using L_ = AdjointLds<T, Q, TP, TY>;
   using A4 = typename acc4<T>::type;
@@ -408,7 +415,10 @@ __global__ void __launch_bounds__(TY* Q * 64)
     const int chunk = task % nchunk, sg = (task / nchunk) % nseg, tile = task / (nchunk * nseg);
     const int b0 = chunk * BB, nbc = nbt - b0 < BB ? nbt - b0 : BB;
     const int y0 = (tile / tz) * TY + off, z0 = (tile % tz) * ZA + off, x0 = sg * seg;
+    // eigenvalues of the real and the imaginary part (a pair item's parts are two multipoles' real fields,
+    // whose sources carry no conjugate: sgn = 1, else -1)
     const T dk = bl < nbc ? lam_d[(long long)mock * nbt + b0 + bl] : (T)0;
+    const T dk2 = bl < nbc ? lam_d2[(long long)mock * nbt + b0 + bl] : (T)0;
     int src[PF];
 #pragma unroll
     for (int i = 0; i < PF; ++i) {
@@ -550,13 +560,14 @@ __global__ void __launch_bounds__(TY* Q * 64)
               const c2<T> f = win[(u + WIN - H) % WIN][s];
               T hx = m[0] * f.x, hy = m[0] * f.y;
               T q[H + 1];
-              q[0] = f.x * f.x + f.y * f.y;
+              const T fx = dk * f.x, fy = dk2 * f.y;
+              q[0] = fx * f.x + fy * f.y;
 #pragma unroll
               for (int d = 1; d <= H; ++d) {
                 const c2<T> lo = win[(u + 2 * WIN - H - d) % WIN][s], hi = win[(u + WIN - H + d) % WIN][s];
                 hx += m[d] * lo.x + mu[d] * hi.x;
                 hy += m[d] * lo.y + mu[d] * hi.y;
-                q[d] = f.x * lo.x + f.y * lo.y;
+                q[d] = fx * lo.x + fy * lo.y;
               }
 #pragma unroll
               for (int t = 0; t < TP; ++t) {
@@ -568,18 +579,18 @@ __global__ void __launch_bounds__(TY* Q * 64)
               for (int d = 0; d <= H; ++d) {
                 const int row4 = std::is_same<T, double>::value ? 4 * d + (s & 3) : 4 * (s & 3) + d;
                 if (s < 4) {
-                  qd[0] = mfma16(z == row4 ? dk : (T)0, q[d], qd[0]);
+                  qd[0] = mfma16(z == row4 ? (T)1 : (T)0, q[d], qd[0]);
                 } else {   // the fifth point, on every lane row
                   const bool mine = std::is_same<T, double>::value ? (z >> 2) == d : (z & 3) == d;
-                  qd[NP - 1] = mfma16(mine ? dk : (T)0, q[d], qd[NP - 1]);
+                  qd[NP - 1] = mfma16(mine ? (T)1 : (T)0, q[d], qd[NP - 1]);
                 }
               }
             }
             T ax, hx, ay, hy;
             row_taps_t<TP, 0, T>(ox, ax, hx);
             row_taps_t<TP, 0, T>(oy, ay, hy);
-            S[(wave * ZG + z) * BB + b] = mk<T>(dk * ax, -(dk * ay));
-            if (z < HL) S[(wave * ZG + 16 + z) * BB + b] = mk<T>(dk * hx, -(dk * hy));
+            S[(wave * ZG + z) * BB + b] = mk<T>(dk * ax, sgn * (dk2 * ay));
+            if (z < HL) S[(wave * ZG + 16 + z) * BB + b] = mk<T>(dk * hx, sgn * (dk2 * hy));
           }
           // the primary's share at plane u - H is complete with plane u
           if (st >= 3 * H) {
@@ -681,7 +692,7 @@ int band_segments(int n, long long tiles, int batch) {
 
 template <typename T, int Q, int TP, int H, int TY, int NH>
 hipError_t contract_t(const void* fields, const void* prim, int n, const BinPair& bp, const BandRule& rule,
-                      double* partials, int nwg, int batch, hipStream_t st) {
+                      double* partials, int nwg, bool pair, int batch, hipStream_t st) {
   const int nl = bp.na + bp.nc;
   const size_t lds = ContractLds<T, Q, TP, TY, NH>(nl).total;
   auto kern = k_band_contract<T, Q, TP, H, TY, NH>;
@@ -690,12 +701,12 @@ hipError_t contract_t(const void* fields, const void* prim, int n, const BinPair
   const int nseg = band_segments(n, (long long)(n / TY) * (n / 4), batch);
   kern<<<dim3(nwg, batch), TY * Q * 64, lds, st>>>(static_cast<const c2<T>*>(fields), static_cast<const T*>(prim), n,
                                                   bp.nbt, bp.a0, bp.na, bp.c0, nl, rule.off,
-                                                  rule_of<T, Q, TP, H>(rule), nseg, partials);
+                                                  rule_of<T, Q, TP, H>(rule), nseg, pair ? 1 : 0, partials);
   return hipGetLastError();
 }
 
 template <typename T, int Q, int TP, int H, int TY, int PT, int PO>
-hipError_t adjoint_t(const void* fields, const void* prim, const void* lam_d, int n, int nbt, const BandRule& rule,
+hipError_t adjoint_t(const void* fields, const void* prim, const void* lam_d, const void* lam_d2, int n, int nbt, const BandRule& rule,
                      double wm, int batch, void* out, void* direct, hipStream_t st) {
   const size_t lds = AdjointLds<T, Q, TP, TY>().total;
   auto kern = k_band_adjoint<T, Q, TP, H, TY, PT, PO>;
@@ -706,7 +717,8 @@ hipError_t adjoint_t(const void* fields, const void* prim, const void* lam_d, in
   const int nseg = band_segments(n, tiles, batch);
   const long long tasks = tiles * nseg;
   kern<<<dim3((unsigned)(tasks < 65536 ? tasks : 65536), batch), TY * Q * 64, lds, st>>>(
-      static_cast<const c2<T>*>(fields), static_cast<const T*>(prim), static_cast<const T*>(lam_d), n, nbt, rule.off,
+      static_cast<const c2<T>*>(fields), static_cast<const T*>(prim), static_cast<const T*>(lam_d),
+      static_cast<const T*>(lam_d2 ? lam_d2 : lam_d), lam_d2 ? (T)1 : (T)-1, n, nbt, rule.off,
       rule_of<T, Q, TP, H>(rule), (T)wm, nseg, nchunk, static_cast<c2<T>*>(out), static_cast<T*>(direct));
   return hipGetLastError();
 }
@@ -714,7 +726,7 @@ hipError_t adjoint_t(const void* fields, const void* prim, const void* lam_d, in
 }  // namespace
 
 hipError_t launch_band_contract(int prec, const void* fields, const void* prim, int n, const BinPair& bp,
-                                const BandRule& rule, double* partials, int nwg, int batch, hipStream_t st) {
+                                const BandRule& rule, double* partials, int nwg, bool pair, int batch, hipStream_t st) {
   const int nl = bp.na + bp.nc;
   if (nl > kBandBins || n % 4) return hipErrorInvalidValue;
   const bool two = nl > 16;
@@ -723,25 +735,25 @@ hipError_t launch_band_contract(int prec, const void* fields, const void* prim, 
   // with 8 waves), as do float64 and the five points of Daubechies-4
   if (rule.q == 4) {
     if (prec) {
-      return two ? contract_t<double, 4, 4, 3, 2, 2>(fields, prim, n, bp, rule, partials, nwg, batch, st)
-                 : contract_t<double, 4, 4, 3, 2, 1>(fields, prim, n, bp, rule, partials, nwg, batch, st);
+      return two ? contract_t<double, 4, 4, 3, 2, 2>(fields, prim, n, bp, rule, partials, nwg, pair, batch, st)
+                 : contract_t<double, 4, 4, 3, 2, 1>(fields, prim, n, bp, rule, partials, nwg, pair, batch, st);
     }
-    return two ? contract_t<float, 4, 4, 3, 2, 2>(fields, prim, n, bp, rule, partials, nwg, batch, st)
-               : contract_t<float, 4, 4, 3, 4, 1>(fields, prim, n, bp, rule, partials, nwg, batch, st);
+    return two ? contract_t<float, 4, 4, 3, 2, 2>(fields, prim, n, bp, rule, partials, nwg, pair, batch, st)
+               : contract_t<float, 4, 4, 3, 4, 1>(fields, prim, n, bp, rule, partials, nwg, pair, batch, st);
   }
   if (rule.q != 5) return hipErrorInvalidValue;
   if (prec) {
-    return two ? contract_t<double, 5, 5, 2, 1, 2>(fields, prim, n, bp, rule, partials, nwg, batch, st)
-               : contract_t<double, 5, 5, 2, 2, 1>(fields, prim, n, bp, rule, partials, nwg, batch, st);
+    return two ? contract_t<double, 5, 5, 2, 1, 2>(fields, prim, n, bp, rule, partials, nwg, pair, batch, st)
+               : contract_t<double, 5, 5, 2, 2, 1>(fields, prim, n, bp, rule, partials, nwg, pair, batch, st);
   }
-  return two ? contract_t<float, 5, 5, 2, 2, 2>(fields, prim, n, bp, rule, partials, nwg, batch, st)
-             : contract_t<float, 5, 5, 2, 2, 1>(fields, prim, n, bp, rule, partials, nwg, batch, st);
+  return two ? contract_t<float, 5, 5, 2, 2, 2>(fields, prim, n, bp, rule, partials, nwg, pair, batch, st)
+             : contract_t<float, 5, 5, 2, 2, 1>(fields, prim, n, bp, rule, partials, nwg, pair, batch, st);
 }
 
-hipError_t launch_band_adjoint(int prec, const void* fields, const void* prim, const void* lam_d, int n, int nbt,
+hipError_t launch_band_adjoint(int prec, const void* fields, const void* prim, const void* lam_d, const void* lam_d2, int n, int nbt,
                                const BandRule& rule, double wm, int batch, void* out, void* direct, hipStream_t st) {
   if (n % ZA) return hipErrorInvalidValue;
-#define BAND_ADJ(...) adjoint_t<__VA_ARGS__>(fields, prim, lam_d, n, nbt, rule, wm, batch, out, direct, st)
+#define BAND_ADJ(...) adjoint_t<__VA_ARGS__>(fields, prim, lam_d, lam_d2, n, nbt, rule, wm, batch, out, direct, st)
   if (rule.q == 4) return prec ? BAND_ADJ(double, 4, 4, 3, 2, 4, 0) : BAND_ADJ(float, 4, 4, 3, 4, 4, 0);
   if (rule.q != 5) return hipErrorInvalidValue;
   return prec ? BAND_ADJ(double, 5, 5, 2, 1, 1, 2) : BAND_ADJ(float, 5, 5, 2, 2, 1, 2);

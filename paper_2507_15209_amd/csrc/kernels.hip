@@ -2002,7 +2002,7 @@ __global__ void __launch_bounds__(256) k_gather_source(const c2<T>* fields, cons
 // pairs (i, j) of a chunk-pair contraction that this pass owns: the cross
 // block always, the diagonal block of the first chunk when own_a, of the
 // second when own_c (local i < na is field bin a0 + i, else c0 + i - na)
-__global__ void k_reduce_partials_map(const double* partials, int nwg, int nl, double* zeta, int l, int lmax,
+__global__ void k_reduce_partials_map(const double* partials, int nwg, int part, int parts, int nl, double* zeta, int l, int lmax,
                                       double scale, int nbt, int a0, int na, int c0, int own_a, int own_c) {
   __shared__ double sh[32];
   const int e = blockIdx.x, mock = blockIdx.y;
@@ -2011,9 +2011,9 @@ __global__ void k_reduce_partials_map(const double* partials, int nwg, int nl, d
   if (ia && ja && !own_a) return;
   if (!ia && !ja && !own_c) return;
   const int nl2 = nl * nl;
-  const double* p = partials + (long long)mock * nwg * nl2 + e;
+  const double* p = partials + ((long long)mock * nwg * parts + part) * nl2 + e;
   double s = 0.0;
-  for (int w = threadIdx.x; w < nwg; w += blockDim.x) s += p[(long long)w * nl2];
+  for (int w = threadIdx.x; w < nwg; w += blockDim.x) s += p[(long long)w * parts * nl2];
   s = block_sum(s, sh);
   const int gi = ia ? a0 + i : c0 + i - na, gj = ja ? a0 + j : c0 + j - na;
   if (threadIdx.x == 0) zeta[((long long)mock * (lmax + 1) + l) * nbt * nbt + (long long)gi * nbt + gj] += scale * s;
@@ -2780,12 +2780,13 @@ hipError_t launch_fbar_subtract(int prec, const double* P, const void* jtab, int
   return hipGetLastError();
 }
 
-hipError_t launch_reduce_partials_map(const double* partials, int nwg, const BinPair& bp, double* zeta, int l,
-                                      int lmax, double scale, bool own_a, bool own_c, int batch, hipStream_t st) {
+hipError_t launch_reduce_partials_map(const double* partials, int nwg, int part, int parts, const BinPair& bp,
+                                      double* zeta, int l, int lmax, double scale, bool own_a, bool own_c, int batch,
+                                      hipStream_t st) {
   const int nl = bp.na + bp.nc;
   const dim3 gs(nl * nl, batch);
-  k_reduce_partials_map<<<gs, 256, 0, st>>>(partials, nwg, nl, zeta, l, lmax, scale, bp.nbt, bp.a0, bp.na, bp.c0,
-                                            own_a ? 1 : 0, own_c ? 1 : 0);
+  k_reduce_partials_map<<<gs, 256, 0, st>>>(partials, nwg, part, parts, nl, zeta, l, lmax, scale, bp.nbt, bp.a0, bp.na,
+                                            bp.c0, own_a ? 1 : 0, own_c ? 1 : 0);
   return hipGetLastError();
 }
 

@@ -112,15 +112,20 @@ struct BandRule {
 constexpr int kBandBins = 32;   // bins of one contraction launch (more: pairs of chunks)
 // forward partials [batch][nwg][nl^2] over the pair's local bins, fields bin-interleaved (band.hip)
 hipError_t launch_band_contract(int prec, const void* fields, const void* prim, int n, const BinPair& bp,
-                                const BandRule& rule, double* partials, int nwg, int batch, hipStream_t st);
+                                const BandRule& rule, double* partials, int nwg, bool pair, int batch, hipStream_t st);
+// (pair: partials [batch][nwg][2][nl^2], of the fields' real and of their imaginary parts)
 // adjoint sources of fields in the cotangent's eigenbasis (eigenvalues lam_d [batch][nbt]) added to
 // out [batch][N^3][nbt] (zeroed by the caller), wm times the primary's share added to direct
-hipError_t launch_band_adjoint(int prec, const void* fields, const void* prim, const void* lam_d, int n, int nbt,
+// lam_d2: NULL, or for a pair item the eigenvalues of its second multipole (the imaginary parts)
+hipError_t launch_band_adjoint(int prec, const void* fields, const void* prim, const void* lam_d, const void* lam_d2,
+                               int n, int nbt,
                                const BandRule& rule, double wm, int batch, void* out, void* direct, hipStream_t st);
 // zeta += the pair's partials at their stored-bin positions (cross block always,
 // diagonal blocks when owned)
-hipError_t launch_reduce_partials_map(const double* partials, int nwg, const BinPair& bp, double* zeta, int l,
-                                      int lmax, double scale, bool own_a, bool own_c, int batch, hipStream_t st);
+// (part of parts: the sums interleaved per workgroup)
+hipError_t launch_reduce_partials_map(const double* partials, int nwg, int part, int parts, const BinPair& bp,
+                                      double* zeta, int l, int lmax, double scale, bool own_a, bool own_c, int batch,
+                                      hipStream_t st);
 hipError_t launch_zpass_store(int n, int prec, const ZpassArgs& a, void* out, hipStream_t st);
 // z transform of bin-interleaved sources [batch][N^3][nbins] into fields [batch][nbins][N^3]
 hipError_t launch_zpass_load(int n, int prec, const ZpassArgs& a, const void* in, void* fields, hipStream_t st);

@@ -613,7 +613,8 @@ int mp3_plan_create(const mp3_plan_desc* d, mp3_plan_t* out) {
   // work items: the real m = 0 fields of neighbouring multipoles two by two (half their transforms)
   // where the contraction keeps the parts apart (matrix cores), then everything else
   p->work0 = (int)p->items.size();
-  const bool pairs = p->summation == MP3_SUM_NODAL && !p->split && p->nbins <= (p->prec ? 16 : 32);
+  const bool pairs = p->summation == MP3_SUM_GRID_GAMMA ||
+                     (p->summation == MP3_SUM_NODAL && !p->split && p->nbins <= (p->prec ? 16 : 32));
   if (pairs) {
     for (int l = 0; l + 1 <= p->lmax; l += 2) {
       mp3::ItemRec it = p->items[item_index(l, 0)];
@@ -834,17 +835,21 @@ std::vector<GammaPass> gamma_passes(const mp3_plan_s* p) {
   return out;
 }
 
-// the contraction of the stored bin-interleaved fields of one (l, m), all passes, into zeta
+// the contraction of the stored bin-interleaved fields of one item, all passes, into zeta
 int gamma_contract_all(const mp3_plan_s* p, const void* Fi, const void* prim, double* partials, int gwg, double* zeta,
-                       int l, double scale, hipStream_t st) {
+                       const mp3::ItemRec& it, double scale, hipStream_t st) {
+  const int parts = it.l2 >= 0 ? 2 : 1;
+  gwg = std::max(1, gwg / parts);
   for (const GammaPass& g : gamma_passes(p)) {
     MP3_HIP(timed(p, MP3_PASS_GAMMA, st, [&] {
-              return mp3::launch_band_contract(p->prec, Fi, prim, p->n, g.bp, p->band, partials, gwg, p->batch, st);
+              return mp3::launch_band_contract(p->prec, Fi, prim, p->n, g.bp, p->band, partials, gwg, parts == 2,
+                                               p->batch, st);
             }),
             "grid-Gamma contraction");
-    MP3_HIP(mp3::launch_reduce_partials_map(partials, gwg, g.bp, zeta, l, p->lmax, scale, g.own_a, g.own_c, p->batch,
-                                            st),
-            "reduce");
+    for (int part = 0; part < parts; ++part)
+      MP3_HIP(mp3::launch_reduce_partials_map(partials, gwg, part, parts, g.bp, zeta, part ? it.l2 : it.l, p->lmax,
+                                              it.wm * scale, g.own_a, g.own_c, p->batch, st),
+              "reduce");
   }
   return MP3_OK;
 }
@@ -945,20 +950,17 @@ int zeta_gamma(mp3_plan_t p, const void* delta, double* zeta, void* ws, const La
   void* Fi = at(ws, L.fields_i);
   double* partials = reinterpret_cast<double*>(at(ws, L.partials));
   const int gwg = gamma_wgs(p);
-  for (int l = 0; l <= p->lmax; ++l) {
-    for (int m = 0; m <= l; ++m) {
-      if (int s = fields_xy(p, ws, L, F, item_index(l, m), 1, st)) return s;
-      mp3::ZpassArgs z{};
-      z.fields = F;
-      z.tw = p->tw;
-      z.nbins = p->nbins;
-      z.nwg = L.nwg;
-      z.ppw = L.ppw;
-      z.batch = p->batch;
-      MP3_HIP(timed(p, MP3_PASS_Z_STORE, st, [&] { return mp3::launch_zpass_store(p->n, p->prec, z, Fi, st); }), "z pass (store)");
-      const double wm = m == 0 ? 1.0 : 2.0;
-      if (int s = gamma_contract_all(p, Fi, delta, partials, gwg, zeta, l, wm * kFourPi / n3, st)) return s;
-    }
+  for (int item = first_item(p, L); group_size(p, L, item) > 0; ++item) {
+    if (int s = fields_xy(p, ws, L, F, item, 1, st)) return s;
+    mp3::ZpassArgs z{};
+    z.fields = F;
+    z.tw = p->tw;
+    z.nbins = p->nbins;
+    z.nwg = L.nwg;
+    z.ppw = L.ppw;
+    z.batch = p->batch;
+    MP3_HIP(timed(p, MP3_PASS_Z_STORE, st, [&] { return mp3::launch_zpass_store(p->n, p->prec, z, Fi, st); }), "z pass (store)");
+    if (int s = gamma_contract_all(p, Fi, delta, partials, gwg, zeta, p->items[item], kFourPi / n3, st)) return s;
   }
   return MP3_OK;
 }
@@ -1265,34 +1267,33 @@ int backward_gamma(mp3_plan_t p, const void* delta, const double* dzeta, void* d
   MP3_HIP(mp3::launch_fill(p->prec, direct, n3 * p->batch, 0.0, st), "zero direct");
   const int gwg = gamma_wgs(p);
   const bool rotated = rotated_tables(p);
-  for (int l = 0; l <= p->lmax; ++l) {
-    for (int m = 0; m <= l; ++m) {
-      const double wm = m == 0 ? 1.0 : 2.0;
-      if (int s = fields_xy(p, ws, L, F, item_index(l, m), 1, st, rotated)) return s;
-      mp3::ZpassArgs z{};
-      z.fields = F;
-      z.tw = p->tw;
-      z.nbins = p->nbins;
-      z.nwg = L.nwg;
-      z.ppw = L.ppw;
-      z.batch = p->batch;
-      MP3_HIP(timed(p, MP3_PASS_Z_STORE, st, [&] { return mp3::launch_zpass_store(p->n, p->prec, z, Fi, st); }), "z pass (store)");
-      if (zeta)
-        if (int s = gamma_contract_all(p, Fi, prim, partials, gwg, zeta, l, wm * kFourPi / (double)n3, st)) return s;
-      // bin-interleaved sources into F (free once stored), their transform into Fi
-      MP3_HIP(mp3::launch_fill(p->prec, F, 2 * n3 * p->batch * p->nbins, 0.0, st), "zero sources");
-      MP3_HIP(timed(p, MP3_PASS_GAMMA, st, [&] {
-                return mp3::launch_band_adjoint(p->prec, Fi, prim, lam_d_at(p, ws, L, l), p->n, p->nbins, p->band, wm,
-                                                p->batch, F, direct, st);
-              }),
-              "grid-Gamma adjoint");
-      MP3_HIP(timed(p, MP3_PASS_Z_ADJOINT, st, [&] { return mp3::launch_zpass_load(p->n, p->prec, z, F, Fi, st); }),
-              "adjoint z pass");
-      MP3_HIP(timed(p, MP3_PASS_X, st, [&] { return mp3::launch_fft_x(p->n, p->prec, +1, Fi, p->batch * p->nbins, p->tw, p->tune[MP3_TUNE_FFT_X_PLAN], st); }),
-              "adjoint x pass");
-      mp3::FilterArgs a = filter_args(p, ws, L, Fi, G, item_index(l, m), 1, rotated);
-      MP3_HIP(timed(p, MP3_PASS_ADJOINT, st, [&] { return mp3::launch_adjoint_y(p->n, p->prec, a, st); }), "adjoint window pass");
-    }
+  for (int item = first_item(p, L); group_size(p, L, item) > 0; ++item) {
+    const mp3::ItemRec& it = p->items[item];
+    if (int s = fields_xy(p, ws, L, F, item, 1, st, rotated)) return s;
+    mp3::ZpassArgs z{};
+    z.fields = F;
+    z.tw = p->tw;
+    z.nbins = p->nbins;
+    z.nwg = L.nwg;
+    z.ppw = L.ppw;
+    z.batch = p->batch;
+    MP3_HIP(timed(p, MP3_PASS_Z_STORE, st, [&] { return mp3::launch_zpass_store(p->n, p->prec, z, Fi, st); }), "z pass (store)");
+    if (zeta)
+      if (int s = gamma_contract_all(p, Fi, prim, partials, gwg, zeta, it, kFourPi / (double)n3, st)) return s;
+    // bin-interleaved sources into F (free once stored), their transform into Fi
+    MP3_HIP(mp3::launch_fill(p->prec, F, 2 * n3 * p->batch * p->nbins, 0.0, st), "zero sources");
+    MP3_HIP(timed(p, MP3_PASS_GAMMA, st, [&] {
+              return mp3::launch_band_adjoint(p->prec, Fi, prim, lam_d_at(p, ws, L, it.l),
+                                              it.l2 >= 0 ? lam_d_at(p, ws, L, it.l2) : nullptr, p->n, p->nbins, p->band, it.wm,
+                                              p->batch, F, direct, st);
+            }),
+            "grid-Gamma adjoint");
+    MP3_HIP(timed(p, MP3_PASS_Z_ADJOINT, st, [&] { return mp3::launch_zpass_load(p->n, p->prec, z, F, Fi, st); }),
+            "adjoint z pass");
+    MP3_HIP(timed(p, MP3_PASS_X, st, [&] { return mp3::launch_fft_x(p->n, p->prec, +1, Fi, p->batch * p->nbins, p->tw, p->tune[MP3_TUNE_FFT_X_PLAN], st); }),
+            "adjoint x pass");
+    mp3::FilterArgs a = filter_args(p, ws, L, Fi, G, item, 1, rotated);
+    MP3_HIP(timed(p, MP3_PASS_ADJOINT, st, [&] { return mp3::launch_adjoint_y(p->n, p->prec, a, st); }), "adjoint window pass");
   }
   // the value was summed over the rotated fields: back to the bins
   if (zeta && rotated)
