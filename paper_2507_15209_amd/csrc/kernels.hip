@@ -1238,14 +1238,17 @@ template <typename T, bool MF, bool SPLIT, bool QUAD, bool SRC, int WB>
 __global__ void __launch_bounds__(256) k_gather_contract(const c2<T>* fields, const int* tcell, const T* twt,
                                                           const float* w, const int* perm, const long long* off,
                                                           const double* W, int n, int nbins, double* partials,
-                                                          const T* lam_d, T wm, double* FJ, c2<T>* src) {
+                                                          const T* lam_d, const T* lam_d2, int pair, T wm, double* FJ,
+                                                          c2<T>* src) {
   constexpr int K = kGatherSlots;                       // particle slots per contraction slice
   constexpr int RS = K + K / 16 + 1;
   extern __shared__ __align__(16) char smem[];
   c2<T>* A = reinterpret_cast<c2<T>*>(smem);
   T* wk = reinterpret_cast<T*>(A + nbins * RS);
   int* pk = reinterpret_cast<int*>(wk + K);             // SRC: particle of slot k (-1: none)
-  T* lam = reinterpret_cast<T*>(pk + K);                // SRC: the eigenvalues d_b
+  T* lam = reinterpret_cast<T*>(pk + K);                // SRC: the eigenvalues d_b of the real parts
+  T* lam2 = lam + nbins;                                // and of the imaginary parts (a pair item's second multipole)
+  const T sgn = pair ? (T)1 : (T)-1;                    // real fields' sources carry no conjugate
   const long long mock = blockIdx.y;
   const long long n3 = (long long)n * n * n;
   const long long a0 = off[mock], a1 = off[mock + 1];
@@ -1274,11 +1277,17 @@ __global__ void __launch_bounds__(256) k_gather_contract(const c2<T>* fields, co
   const int ppp = nw * ppw;                             // particles per pass
   const c2<T>* fm = fields + mock * n3 * nbins;
   const double fw = (double)n3 / W[mock];
-  T dl[WB];
+  T dl[WB], dl2[WB];
 #pragma unroll
-  for (int i = 0; i < WB; ++i) dl[i] = (SRC && lane_ok) ? lam_d[mock * nbins + b + i] : (T)0;
+  for (int i = 0; i < WB; ++i) {
+    dl[i] = (SRC && lane_ok) ? lam_d[mock * nbins + b + i] : (T)0;
+    dl2[i] = (SRC && lane_ok) ? lam_d2[mock * nbins + b + i] : (T)0;
+  }
   if constexpr (SRC) {
-    for (int t = threadIdx.x; t < nbins; t += blockDim.x) lam[t] = lam_d[mock * nbins + t];
+    for (int t = threadIdx.x; t < nbins; t += blockDim.x) {
+      lam[t] = lam_d[mock * nbins + t];
+      lam2[t] = lam_d2[mock * nbins + t];
+    }
   }
   Contractor<T, MF, SPLIT, QUAD> ctr;
   ctr.init(nbins);
@@ -1300,7 +1309,7 @@ __global__ void __launch_bounds__(256) k_gather_contract(const c2<T>* fields, co
         if constexpr (SRC) {
           const T f = (T)(fw * wi);
 #pragma unroll
-          for (int e = 0; e < WB; ++e) src[si * nbins + b + e] = mk<T>(f * (dl[e] * acc[e].x), -(f * (dl[e] * acc[e].y)));
+          for (int e = 0; e < WB; ++e) src[si * nbins + b + e] = mk<T>(f * (dl[e] * acc[e].x), sgn * (f * (dl2[e] * acc[e].y)));
         }
       }
       if (lane_ok) {
@@ -1323,7 +1332,7 @@ __global__ void __launch_bounds__(256) k_gather_contract(const c2<T>* fields, co
           T fj = 0;
           for (int bb = 0; bb < nbins; ++bb) {
             const c2<T> a = A[bb * RS + kp];
-            fj += lam[bb] * (a.x * a.x + a.y * a.y);
+            fj += lam[bb] * (a.x * a.x) + lam2[bb] * (a.y * a.y);
           }
           FJ[ip] += (double)wm * (double)fj;
         }
@@ -1331,8 +1340,8 @@ __global__ void __launch_bounds__(256) k_gather_contract(const c2<T>* fields, co
     }
     __syncthreads();
   }
-  ctr.finish(reinterpret_cast<double*>(smem), partials + ((long long)mock * gridDim.x + blockIdx.x) * nbins * nbins,
-             nbins);
+  ctr.finish(reinterpret_cast<double*>(smem),
+             partials + ((long long)mock * gridDim.x + blockIdx.x) * nbins * nbins * (pair ? 2 : 1), nbins, pair != 0);
 }
 
 // sum_s A(s) e^{-i theta s} over the autocorrelation samples of the basis
@@ -1411,13 +1420,14 @@ __global__ void k_reduce_items(const double* partials, int nwg, int nb2, double*
 }
 
 // fixed summation order (deterministic)
-__global__ void k_reduce_partials(const double* partials, int nwg, int nb2, double* zeta, int l, int lmax, double scale) {
+__global__ void k_reduce_partials(const double* partials, int nwg, int part, int parts, int nb2, double* zeta, int l,
+                                  int lmax, double scale) {
   __shared__ double sh[32];
   const int e = blockIdx.x;
   const int j = blockIdx.y;
-  const double* p = partials + (long long)j * nwg * nb2 + e;
+  const double* p = partials + ((long long)j * nwg * parts + part) * nb2 + e;
   double s = 0.0;
-  for (int w = threadIdx.x; w < nwg; w += blockDim.x) s += p[(long long)w * nb2];
+  for (int w = threadIdx.x; w < nwg; w += blockDim.x) s += p[(long long)w * parts * nb2];
   s = block_sum(s, sh);
   if (threadIdx.x == 0) zeta[((long long)j * (lmax + 1) + l) * nb2 + e] += scale * s;
 }
@@ -1966,8 +1976,8 @@ __global__ void k_grad_combine(const T* direct, const c2<T>* ghat, T* ddelta, lo
 template <typename T>
 __global__ void __launch_bounds__(256) k_gather_source(const c2<T>* fields, const int* tcell, const T* twt,
                                                         const float* w, const int* perm, const long long* off,
-                                                        const double* W, const T* lam_d, int n, int nbins, T wm,
-                                                        double* FJ, c2<T>* src) {
+                                                        const double* W, const T* lam_d, const T* lam_d2, int n,
+                                                        int nbins, T wm, T sgn, double* FJ, c2<T>* src) {
   const int lpp = nbins <= 32 ? 32 : 64;
   const int ppp = blockDim.x / lpp;
   const long long mock = blockIdx.y;
@@ -1978,6 +1988,7 @@ __global__ void __launch_bounds__(256) k_gather_source(const c2<T>* fields, cons
   const double fw = (double)n3 / W[mock];
   const int b = threadIdx.x % lpp, g = threadIdx.x / lpp;
   const T d = b < nbins ? lam_d[mock * nbins + b] : (T)0;
+  const T d2 = b < nbins ? lam_d2[mock * nbins + b] : (T)0;   // of the imaginary part
   const c2<T>* fm = fields + mock * n3 * nbins;
   for (long long c0 = s0; c0 < s1; c0 += ppp) {
     const long long si = c0 + g;
@@ -1988,10 +1999,10 @@ __global__ void __launch_bounds__(256) k_gather_source(const c2<T>* fields, cons
       c2<T> acc = mk<T>(0, 0);
       const int cell = tcell[si];
       if (cell >= 0) gather_record<T, 1>(fm, cell, twt + si * 12, n, nbins, b, &acc);
-      const T e = d * acc.x, f2 = d * acc.y;
+      const T e = d * acc.x, f2 = d2 * acc.y;
       fj = e * acc.x + f2 * acc.y;
       const T f = (T)(fw * (w ? (double)w[i] : 1.0));
-      src[si * nbins + b] = mk<T>(f * e, -(f * f2));
+      src[si * nbins + b] = mk<T>(f * e, sgn * (f * f2));
     }
     for (int o = lpp / 2; o > 0; o >>= 1) fj += __shfl_xor(fj, o, lpp);
     if (has && b == 0) FJ[i] += (double)wm * (double)fj;
@@ -2552,10 +2563,10 @@ hipError_t launch_rotate_zeta(double* zeta, const double* evec, int nbins, int l
   return hipGetLastError();
 }
 
-hipError_t launch_reduce_partials(const double* partials, int nwg, int nb2, double* zeta, int l, int lmax, double scale,
+hipError_t launch_reduce_partials(const double* partials, int nwg, int part, int parts, int nb2, double* zeta, int l, int lmax, double scale,
                                   int batch, hipStream_t st) {
   const dim3 gs(nb2, batch);
-  k_reduce_partials<<<gs, 256, 0, st>>>(partials, nwg, nb2, zeta, l, lmax, scale);
+  k_reduce_partials<<<gs, 256, 0, st>>>(partials, nwg, part, parts, nb2, zeta, l, lmax, scale);
   return hipGetLastError();
 }
 
@@ -2724,7 +2735,7 @@ hipError_t gather_contract_v(const GatherArgs& a, hipStream_t st) {
   constexpr int K = kGatherSlots;
   const size_t rs = K + K / 16 + 1;
   size_t lds = (size_t)a.nbins * rs * sizeof(CT<T>) + K * sizeof(T);
-  if (SRC) lds += K * sizeof(int) + (size_t)a.nbins * sizeof(T);
+  if (SRC) lds += K * sizeof(int) + (size_t)2 * a.nbins * sizeof(T);
   const size_t red = Contractor<T, MF, SPLIT, QUAD>::scratch_bytes(256);
   if (lds < red) lds = red;
   hipError_t e = allow_lds(k_gather_contract<T, MF, SPLIT, QUAD, SRC, W>, lds);
@@ -2732,7 +2743,7 @@ hipError_t gather_contract_v(const GatherArgs& a, hipStream_t st) {
   const dim3 gs(a.nwg, a.batch);
   k_gather_contract<T, MF, SPLIT, QUAD, SRC, W><<<gs, 256, lds, st>>>(
       static_cast<const CT<T>*>(a.fields), a.tcell, static_cast<const T*>(a.twt), a.w, a.perm, a.off, a.W, a.n, a.nbins,
-      a.partials, static_cast<const T*>(a.lam), (T)a.wm, a.FJ, static_cast<CT<T>*>(a.src));
+      a.partials, static_cast<const T*>(a.lam), static_cast<const T*>(a.lam2 ? a.lam2 : a.lam), a.pair ? 1 : 0, (T)a.wm, a.FJ, static_cast<CT<T>*>(a.src));
   return hipGetLastError();
 }
 
@@ -2750,7 +2761,9 @@ hipError_t gather_contract_t(const GatherArgs& a, hipStream_t st) {
 }
 
 hipError_t launch_gather_contract(int prec, const GatherArgs& a, hipStream_t st) {
-  if (prec) return gather_contract_t<double, false>(a, st);
+  // float64: the matrix cores up to 16 bins (9 bins: the same time as the vector ALUs), which keep a pair
+  // item's parts apart
+  if (prec) return a.nbins <= 16 ? gather_contract_t<double, true>(a, st) : gather_contract_t<double, false>(a, st);
   if (a.nbins <= 32) {
     if (a.split) return gather_contract_t<float, true, true>(a, st);
     if (a.nbins > 16 && a.nbins <= 20) return gather_contract_t<float, true, false, true>(a, st);
@@ -2791,18 +2804,21 @@ hipError_t launch_reduce_partials_map(const double* partials, int nwg, int part,
 }
 
 hipError_t launch_gather_source(int prec, const void* fields, const int* tcell, const void* twt, const float* w,
-                                const int* perm, const long long* off, const double* W, const void* lam_d, int n,
+                                const int* perm, const long long* off, const double* W, const void* lam_d, const void* lam_d2, int n,
                                 int nbins, double wm, int nwg, int batch, double* FJ, void* src, hipStream_t st) {
   const dim3 gs(nwg, batch);
   if (prec)
     k_gather_source<double><<<gs, 256, 0, st>>>(static_cast<const double2*>(fields), tcell,
                                                 static_cast<const double*>(twt), w, perm, off, W,
-                                                static_cast<const double*>(lam_d), n, nbins, wm, FJ,
+                                                static_cast<const double*>(lam_d),
+                                               static_cast<const double*>(lam_d2 ? lam_d2 : lam_d), n, nbins, wm, lam_d2 ? 1.0 : -1.0, FJ,
                                                 static_cast<double2*>(src));
   else
     k_gather_source<float><<<gs, 256, 0, st>>>(static_cast<const float2*>(fields), tcell,
                                                static_cast<const float*>(twt), w, perm, off, W,
-                                               static_cast<const float*>(lam_d), n, nbins, (float)wm, FJ,
+                                               static_cast<const float*>(lam_d),
+                                              static_cast<const float*>(lam_d2 ? lam_d2 : lam_d), n, nbins, (float)wm,
+                                              lam_d2 ? 1.f : -1.f, FJ,
                                                static_cast<float2*>(src));
   return hipGetLastError();
 }

@@ -85,9 +85,11 @@ struct GatherArgs {
   int n, nbins, nwg, batch;
   double sc;              // N / box
   bool split;             // float32 contraction with BF16-split inputs on the matrix cores
+  bool pair;              // pair item: partials [batch][nwg][2][nbins^2], of the real and the imaginary parts
   // adjoint sources from the same gather (value and gradient in one sweep) when src != NULL:
   // the fields are those of the rotated radial tables, lam the cotangent's eigenvalues
   const void* lam;        // [batch][nbins] eigenvalues of the symmetrised cotangent
+  const void* lam2;       // of a pair item's second multipole (the imaginary parts), else NULL
   double wm;              // m weight
   double* FJ;             // [np_total] F_J accumulator
   void* src;              // [np_total][nbins] sources in sorted order
@@ -175,7 +177,8 @@ hipError_t launch_rotate_zeta(double* zeta, const double* evec, int nbins, int l
 // partials of a group of items [item][batch][nwg][nb2] into zeta at each item's l (times scale and the item's m weight)
 hipError_t launch_reduce_items(const double* partials, int nwg, int nb2, double* zeta, int lmax, double scale,
                                const ItemRec* items, int item0, int nitems, int batch, hipStream_t st);
-hipError_t launch_reduce_partials(const double* partials, int nwg, int nb2, double* zeta, int l, int lmax, double scale,
+// (part of parts: the sums interleaved per workgroup)
+hipError_t launch_reduce_partials(const double* partials, int nwg, int part, int parts, int nb2, double* zeta, int l, int lmax, double scale,
                                   int batch, hipStream_t st);
 hipError_t launch_weight_sum(const float* w, const long long* off, int batch, long long np_max, double* W, hipStream_t st);
 // out[j] = sum over mock j of w_i f_i (w NULL = unit weights)
@@ -185,7 +188,8 @@ hipError_t launch_weighted_sum(const float* w, const double* f, const long long*
 // grid ([batch][nbins][N^3], every node written), the volume-mean term into G
 // and the primary vertex's share of dJ/dw
 hipError_t launch_gather_source(int prec, const void* fields, const int* tcell, const void* twt, const float* w,
-                                const int* perm, const long long* off, const double* W, const void* lam_d, int n,
+                                const int* perm, const long long* off, const double* W, const void* lam_d,
+                                const void* lam_d2, int n,
                                 int nbins, double wm, int nwg, int batch, double* FJ, void* src, hipStream_t st);
 hipError_t launch_scatter_source(int prec, const int* tcell, const void* twt, const int* toff, const void* src, int n,
                                  int nbins, int batch, void* out, hipStream_t st);

@@ -614,7 +614,7 @@ int mp3_plan_create(const mp3_plan_desc* d, mp3_plan_t* out) {
   // where the contraction keeps the parts apart (matrix cores), then everything else
   p->work0 = (int)p->items.size();
   const bool pairs = p->summation == MP3_SUM_GRID_GAMMA ||
-                     (p->summation == MP3_SUM_NODAL && !p->split && p->nbins <= (p->prec ? 16 : 32));
+                     (!p->split && p->nbins <= (p->prec ? 16 : 32));
   if (pairs) {
     for (int l = 0; l + 1 <= p->lmax; l += 2) {
       mp3::ItemRec it = p->items[item_index(l, 0)];
@@ -898,40 +898,44 @@ int zeta_particle(mp3_plan_t p, const float* pos, const float* w, const int64_t*
   void* Fi = at(ws, L.fields_i);
   double* partials = reinterpret_cast<double*>(at(ws, L.partials));
   const int gwg = gather_wgs(p, np_max);
-  for (int l = 0; l <= p->lmax; ++l) {
-    for (int m = 0; m <= l; ++m) {
-      if (int s = fields_xy(p, ws, L, F, item_index(l, m), 1, st)) return s;
-      mp3::ZpassArgs z{};
-      z.fields = F;
-      z.tw = p->tw;
-      z.nbins = p->nbins;
-      z.nwg = L.nwg;
-      z.ppw = L.ppw;
-      z.batch = p->batch;
-      MP3_HIP(timed(p, MP3_PASS_Z_STORE, st, [&] { return mp3::launch_zpass_store(p->n, p->prec, z, Fi, st); }), "z pass (store)");
-      mp3::GatherArgs g{};
-      g.fields = Fi;
-      g.tcell = tcell;
-      g.twt = twt;
-      g.pos = pos;
-      g.w = w;
-      g.perm = perm;
-      g.off = off;
-      g.W = W;
-      g.partials = partials;
-      g.n = p->n;
-      g.nbins = p->nbins;
-      g.nwg = gwg;
-      g.batch = p->batch;
-      g.sc = sc;
-      g.split = p->split;
-      MP3_HIP(timed(p, MP3_PASS_GATHER, st, [&] { return mp3::launch_gather_contract(p->prec, g, st); }), "gather");
-      const double wm = m == 0 ? 1.0 : 2.0;
-      MP3_HIP(mp3::launch_reduce_partials(partials, gwg, nb2, zeta, l, p->lmax, wm * kFourPi, p->batch, st), "reduce");
-    }
+  for (int item = first_item(p, L); group_size(p, L, item) > 0; ++item) {
+    const mp3::ItemRec& it = p->items[item];
+    const int parts = it.l2 >= 0 ? 2 : 1;
+    if (int s = fields_xy(p, ws, L, F, item, 1, st)) return s;
+    mp3::ZpassArgs z{};
+    z.fields = F;
+    z.tw = p->tw;
+    z.nbins = p->nbins;
+    z.nwg = L.nwg;
+    z.ppw = L.ppw;
+    z.batch = p->batch;
+    MP3_HIP(timed(p, MP3_PASS_Z_STORE, st, [&] { return mp3::launch_zpass_store(p->n, p->prec, z, Fi, st); }), "z pass (store)");
+    mp3::GatherArgs g{};
+    g.fields = Fi;
+    g.tcell = tcell;
+    g.twt = twt;
+    g.pos = pos;
+    g.w = w;
+    g.perm = perm;
+    g.off = off;
+    g.W = W;
+    g.partials = partials;
+    g.n = p->n;
+    g.nbins = p->nbins;
+    g.nwg = std::max(1, gwg / parts);
+    g.pair = parts == 2;
+    g.batch = p->batch;
+    g.sc = sc;
+    g.split = p->split;
+    MP3_HIP(timed(p, MP3_PASS_GATHER, st, [&] { return mp3::launch_gather_contract(p->prec, g, st); }), "gather");
+    for (int part = 0; part < parts; ++part)
+      MP3_HIP(mp3::launch_reduce_partials(partials, g.nwg, part, parts, nb2, zeta, part ? it.l2 : it.l, p->lmax,
+                                          it.wm * kFourPi, p->batch, st),
+              "reduce");
+  }
+  for (int l = 0; l <= p->lmax; ++l)
     MP3_HIP(mp3::launch_fbar_subtract(p->prec, P, p->jtab, nq2, p->nbp, p->nbins, l, p->lmax, n3 * n3, zeta, p->batch, st),
             "volume mean");
-  }
   return MP3_OK;
 }
 
@@ -1063,34 +1067,33 @@ int backward_particle(mp3_plan_t p, const void* delta, const double* dzeta, void
   MP3_HIP(mp3::launch_fill(p->prec, direct, n3 * p->batch, 0.0, st), "zero direct");
   MP3_HIP(mp3::launch_fill_f64(FJ, np_total, 0.0, st), "zero F_J");
   const int gwg = gather_wgs(p, np_max);
-  for (int l = 0; l <= p->lmax; ++l) {
-    for (int m = 0; m <= l; ++m) {
-      const double wm = m == 0 ? 1.0 : 2.0;
-      if (int s = fields_xy(p, ws, L, F, item_index(l, m), 1, st, true)) return s;
-      mp3::ZpassArgs z{};
-      z.fields = F;
-      z.tw = p->tw;
-      z.nbins = p->nbins;
-      z.nwg = L.nwg;
-      z.ppw = L.ppw;
-      z.batch = p->batch;
-      MP3_HIP(timed(p, MP3_PASS_Z_STORE, st, [&] { return mp3::launch_zpass_store(p->n, p->prec, z, Fi, st); }), "z pass (store)");
-      MP3_HIP(timed(p, MP3_PASS_GATHER, st, [&] {
-                return mp3::launch_gather_source(p->prec, Fi, tcell, twt, w, perm, off, W, lam_d_at(p, ws, L, l), p->n, p->nbins,
-                                                 wm, gwg, p->batch, FJ, src, st);
-              }),
-              "gather (adjoint sources)");
-      MP3_HIP(timed(p, MP3_PASS_SCATTER, st, [&] {
-                return mp3::launch_scatter_source(p->prec, tcell, twt, toff, src, p->n, p->nbins, p->batch, F, st);
-              }),
-              "scatter (adjoint sources)");
-      MP3_HIP(timed(p, MP3_PASS_Z_ADJOINT, st, [&] { return mp3::launch_fft_z(p->n, p->prec, +1, F, F, p->batch * p->nbins, p->tw, st); }),
-              "adjoint z pass");
-      MP3_HIP(timed(p, MP3_PASS_X, st, [&] { return mp3::launch_fft_x(p->n, p->prec, +1, F, p->batch * p->nbins, p->tw, p->tune[MP3_TUNE_FFT_X_PLAN], st); }),
-              "adjoint x pass");
-      mp3::FilterArgs a = filter_args(p, ws, L, F, G, item_index(l, m), 1, true);
-      MP3_HIP(timed(p, MP3_PASS_ADJOINT, st, [&] { return mp3::launch_adjoint_y(p->n, p->prec, a, st); }), "adjoint window pass");
-    }
+  for (int item = first_item(p, L); group_size(p, L, item) > 0; ++item) {
+    const mp3::ItemRec& it = p->items[item];
+    if (int s = fields_xy(p, ws, L, F, item, 1, st, true)) return s;
+    mp3::ZpassArgs z{};
+    z.fields = F;
+    z.tw = p->tw;
+    z.nbins = p->nbins;
+    z.nwg = L.nwg;
+    z.ppw = L.ppw;
+    z.batch = p->batch;
+    MP3_HIP(timed(p, MP3_PASS_Z_STORE, st, [&] { return mp3::launch_zpass_store(p->n, p->prec, z, Fi, st); }), "z pass (store)");
+    MP3_HIP(timed(p, MP3_PASS_GATHER, st, [&] {
+              return mp3::launch_gather_source(p->prec, Fi, tcell, twt, w, perm, off, W, lam_d_at(p, ws, L, it.l),
+                                               it.l2 >= 0 ? lam_d_at(p, ws, L, it.l2) : nullptr, p->n, p->nbins,
+                                               it.wm, gwg, p->batch, FJ, src, st);
+            }),
+            "gather (adjoint sources)");
+    MP3_HIP(timed(p, MP3_PASS_SCATTER, st, [&] {
+              return mp3::launch_scatter_source(p->prec, tcell, twt, toff, src, p->n, p->nbins, p->batch, F, st);
+            }),
+            "scatter (adjoint sources)");
+    MP3_HIP(timed(p, MP3_PASS_Z_ADJOINT, st, [&] { return mp3::launch_fft_z(p->n, p->prec, +1, F, F, p->batch * p->nbins, p->tw, st); }),
+            "adjoint z pass");
+    MP3_HIP(timed(p, MP3_PASS_X, st, [&] { return mp3::launch_fft_x(p->n, p->prec, +1, F, p->batch * p->nbins, p->tw, p->tune[MP3_TUNE_FFT_X_PLAN], st); }),
+            "adjoint x pass");
+    mp3::FilterArgs a = filter_args(p, ws, L, F, G, item, 1, true);
+    MP3_HIP(timed(p, MP3_PASS_ADJOINT, st, [&] { return mp3::launch_adjoint_y(p->n, p->prec, a, st); }), "adjoint window pass");
   }
   MP3_HIP(mp3::launch_fbar_adjoint(p->prec, dzeta, p->jtab, p->nq2, p->nbp, p->nbins, p->lmax, at(ws, L.dhat), p->n,
                                    -1.0 / (kFourPi * (double)n3), reinterpret_cast<double*>(at(ws, L.hq)), G, p->batch,
@@ -1159,52 +1162,56 @@ int value_and_grad_particle(mp3_plan_t p, const void* delta, const double* dzeta
   MP3_HIP(mp3::launch_fill(p->prec, direct, n3 * p->batch, 0.0, st), "zero direct");
   MP3_HIP(mp3::launch_fill_f64(FJ, np_total, 0.0, st), "zero F_J");
   const int gwg = gather_wgs(p, np_max);
-  for (int l = 0; l <= p->lmax; ++l) {
-    for (int m = 0; m <= l; ++m) {
-      const double wm = m == 0 ? 1.0 : 2.0;
-      if (int s = fields_xy(p, ws, L, F, item_index(l, m), 1, st, true)) return s;
-      mp3::ZpassArgs z{};
-      z.fields = F;
-      z.tw = p->tw;
-      z.nbins = p->nbins;
-      z.nwg = L.nwg;
-      z.ppw = L.ppw;
-      z.batch = p->batch;
-      MP3_HIP(timed(p, MP3_PASS_Z_STORE, st, [&] { return mp3::launch_zpass_store(p->n, p->prec, z, Fi, st); }), "z pass (store)");
-      mp3::GatherArgs g{};
-      g.fields = Fi;
-      g.tcell = tcell;
-      g.twt = twt;
-      g.pos = pos;
-      g.w = w;
-      g.perm = perm;
-      g.off = off;
-      g.W = W;
-      g.partials = partials;
-      g.n = p->n;
-      g.nbins = p->nbins;
-      g.nwg = gwg;
-      g.batch = p->batch;
-      g.sc = sc;
-      g.split = p->split;
-      // one gather gives the contraction and the (diagonal) adjoint sources
-      g.lam = lam_d_at(p, ws, L, l);
-      g.wm = wm;
-      g.FJ = FJ;
-      g.src = src;
-      MP3_HIP(timed(p, MP3_PASS_GATHER, st, [&] { return mp3::launch_gather_contract(p->prec, g, st); }), "gather");
-      MP3_HIP(mp3::launch_reduce_partials(partials, gwg, nb2, zeta, l, p->lmax, wm * kFourPi, p->batch, st), "reduce");
-      MP3_HIP(timed(p, MP3_PASS_SCATTER, st, [&] {
-                return mp3::launch_scatter_source(p->prec, tcell, twt, toff, src, p->n, p->nbins, p->batch, F, st);
-              }),
-              "scatter (adjoint sources)");
-      MP3_HIP(timed(p, MP3_PASS_Z_ADJOINT, st, [&] { return mp3::launch_fft_z(p->n, p->prec, +1, F, F, p->batch * p->nbins, p->tw, st); }),
-              "adjoint z pass");
-      MP3_HIP(timed(p, MP3_PASS_X, st, [&] { return mp3::launch_fft_x(p->n, p->prec, +1, F, p->batch * p->nbins, p->tw, p->tune[MP3_TUNE_FFT_X_PLAN], st); }),
-              "adjoint x pass");
-      mp3::FilterArgs a = filter_args(p, ws, L, F, G, item_index(l, m), 1, true);
-      MP3_HIP(timed(p, MP3_PASS_ADJOINT, st, [&] { return mp3::launch_adjoint_y(p->n, p->prec, a, st); }), "adjoint window pass");
-    }
+  for (int item = first_item(p, L); group_size(p, L, item) > 0; ++item) {
+    const mp3::ItemRec& it = p->items[item];
+    const int parts = it.l2 >= 0 ? 2 : 1;
+    if (int s = fields_xy(p, ws, L, F, item, 1, st, true)) return s;
+    mp3::ZpassArgs z{};
+    z.fields = F;
+    z.tw = p->tw;
+    z.nbins = p->nbins;
+    z.nwg = L.nwg;
+    z.ppw = L.ppw;
+    z.batch = p->batch;
+    MP3_HIP(timed(p, MP3_PASS_Z_STORE, st, [&] { return mp3::launch_zpass_store(p->n, p->prec, z, Fi, st); }), "z pass (store)");
+    mp3::GatherArgs g{};
+    g.fields = Fi;
+    g.tcell = tcell;
+    g.twt = twt;
+    g.pos = pos;
+    g.w = w;
+    g.perm = perm;
+    g.off = off;
+    g.W = W;
+    g.partials = partials;
+    g.n = p->n;
+    g.nbins = p->nbins;
+    g.nwg = std::max(1, gwg / parts);
+    g.pair = parts == 2;
+    g.batch = p->batch;
+    g.sc = sc;
+    g.split = p->split;
+    // one gather gives the contraction and the (diagonal) adjoint sources
+    g.lam = lam_d_at(p, ws, L, it.l);
+    g.lam2 = parts == 2 ? lam_d_at(p, ws, L, it.l2) : nullptr;
+    g.wm = it.wm;
+    g.FJ = FJ;
+    g.src = src;
+    MP3_HIP(timed(p, MP3_PASS_GATHER, st, [&] { return mp3::launch_gather_contract(p->prec, g, st); }), "gather");
+    for (int part = 0; part < parts; ++part)
+      MP3_HIP(mp3::launch_reduce_partials(partials, g.nwg, part, parts, nb2, zeta, part ? it.l2 : it.l, p->lmax,
+                                          it.wm * kFourPi, p->batch, st),
+              "reduce");
+    MP3_HIP(timed(p, MP3_PASS_SCATTER, st, [&] {
+              return mp3::launch_scatter_source(p->prec, tcell, twt, toff, src, p->n, p->nbins, p->batch, F, st);
+            }),
+            "scatter (adjoint sources)");
+    MP3_HIP(timed(p, MP3_PASS_Z_ADJOINT, st, [&] { return mp3::launch_fft_z(p->n, p->prec, +1, F, F, p->batch * p->nbins, p->tw, st); }),
+            "adjoint z pass");
+    MP3_HIP(timed(p, MP3_PASS_X, st, [&] { return mp3::launch_fft_x(p->n, p->prec, +1, F, p->batch * p->nbins, p->tw, p->tune[MP3_TUNE_FFT_X_PLAN], st); }),
+            "adjoint x pass");
+    mp3::FilterArgs a = filter_args(p, ws, L, F, G, item, 1, true);
+    MP3_HIP(timed(p, MP3_PASS_ADJOINT, st, [&] { return mp3::launch_adjoint_y(p->n, p->prec, a, st); }), "adjoint window pass");
   }
   // the value was summed over the rotated fields: back to the bins, then the volume means
   MP3_HIP(mp3::launch_rotate_zeta(zeta, reinterpret_cast<const double*>(at(ws, L.evec)), p->nbins, p->lmax, p->batch,

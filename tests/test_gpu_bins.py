@@ -91,3 +91,36 @@ def test_paired_multipoles(prec, form, lmax, nb):
         assert_zeta_close(z[j], ref, TOL[prec])
         assert_grad_close(g[j], gref, TOL[prec], "one sweep")
         assert_grad_close(g2[j], gref, TOL[prec], "backward")
+
+
+@pytest.mark.parametrize("lmax,nb", [(1, 3), (2, 16), (3, 20)])
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+def test_paired_multipoles_particle(prec, lmax, nb):
+    """The same in the particle form (float64 beyond 16 bins stays unpaired): value, dJ/ddelta and dJ/dw at
+    the particle gradient's bars (1e-10 float64, 1e-4 float32)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2507_15209_amd as mp3
+    from oracle import adjoint as A
+    from tests._common import assert_grad_close
+    print("[case] paired multipoles, particle form", prec, lmax, nb, flush=True)
+    n, box = 16, 160.0
+    tol = {"f64": 1e-10, "f32": 1e-4}[prec]
+    edges = np.linspace(16.0, 56.0, nb + 1)
+    pos, w = lognormal_catalogue(n, box, 900, 8.0, 621, 622, 623, (0.5, 1.5))
+    lam = np.random.default_rng(624).standard_normal((lmax + 1, nb, nb))
+    plan = mp3.Plan(n, box, lmax, edges, precision=prec, summation="particle")
+    pt, wt = torch.as_tensor(pos, device="cuda"), torch.as_tensor(w, device="cuda")
+    delta = plan.deposit(pt, wt)
+    lt = torch.as_tensor(lam[None], device="cuda")
+    z, g, dw = plan.zeta_value_and_grad(delta, lt, pt, wt)
+    g2, dw2 = plan.zeta_backward(delta, lt, pt, wt)
+    op = E.Plan(n, box, lmax, edges)
+    ref = E.zeta_particle(op, pos, w)
+    gref, wref = A.zeta_particle_grad(op, pos, w, lam)
+    for zz in (plan.zeta(delta, pt, wt), z):
+        assert_zeta_close(zz.cpu().numpy()[0], ref, tol)
+    for a, b in ((g, gref), (g2, gref)):
+        assert_grad_close(a.cpu().numpy()[0], b, tol, "dJ/ddelta")
+    for a in (dw, dw2):
+        assert_grad_close(a.cpu().numpy(), wref, tol, "dJ/dw")
