@@ -1094,39 +1094,6 @@ __global__ void k_tile_scatter(const float* pos, const long long* off, int batch
   }
 }
 
-// Order of the particles within each 4^3-cell tile: by cell, z fastest, one wave
-// per tile (counting sort over the 64 cells in LDS), perm -> out.  Neighbours
-// in this order share most of their taps, so the gather finds them in L1 rather
-// than in L2.
-__global__ void __launch_bounds__(256) k_tile_order(const float* pos, const int* perm, const int* toff, long long ntiles,
-                                                    int n, double sc, int* out) {
-  __shared__ int hist[4][64];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const long long tile = blockIdx.x * 4LL + wv;
-  const int a0 = tile < ntiles ? toff[tile] : 0, a1 = tile < ntiles ? toff[tile + 1] : 0;
-  auto key = [&](int i) {
-    const int c = tile_of(pos + 3 * (long long)i, n, sc, n, 0);   // (x n + y) n + z of the cell
-    return ((c / (n * n)) & 3) * 16 + ((c / n) & 3) * 4 + (c & 3);
-  };
-  hist[wv][lane] = 0;
-  __syncthreads();
-  for (int k = a0 + lane; k < a1; k += 64) atomicAdd(&hist[wv][key(perm[k])], 1);
-  __syncthreads();
-  const int c = hist[wv][lane];
-  int incl = c;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int v = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += v;
-  }
-  hist[wv][lane] = a0 + incl - c;
-  __syncthreads();
-  for (int k = a0 + lane; k < a1; k += 64) {
-    const int i = perm[k];
-    out[atomicAdd(&hist[wv][key(i)], 1)] = i;
-  }
-}
-
 // Per-particle stencil records in sorted order, computed once per call by
 // make_taps: the cell (floor of x n / box per axis, packed 10 bits each; -1
 // for a position that is not finite) and the 12 tap weights in the working
@@ -1136,14 +1103,11 @@ __device__ __forceinline__ int pack_cell(const Taps& t) {
   return t.ok ? ((t.base[0] + 1) | ((t.base[1] + 1) << 10) | ((t.base[2] + 1) << 20)) : -1;
 }
 
-// On entry tcell holds the particles' final order (k_tile_order), which moves to perm.
 template <typename T>
-__global__ void k_tap_records(const float* pos, int* perm, long long np_total, int n, double sc, int* tcell,
+__global__ void k_tap_records(const float* pos, const int* perm, long long np_total, int n, double sc, int* tcell,
                               T* twt, const double* btab) {
   for (long long k = blockIdx.x * (long long)blockDim.x + threadIdx.x; k < np_total; k += (long long)gridDim.x * blockDim.x) {
-    const int i = tcell[k];
-    perm[k] = i;
-    const Taps t = make_taps(pos + 3 * (long long)i, n, sc, btab);
+    const Taps t = make_taps(pos + 3 * (long long)perm[k], n, sc, btab);
     tcell[k] = pack_cell(t);
 #pragma unroll
     for (int d = 0; d < 3; ++d)
@@ -1182,7 +1146,8 @@ __device__ __forceinline__ void gather_record(const c2<T>* fm, int cell, const T
 #pragma unroll
   for (int e = 0; e < 2 * W; ++e) acc[e] = 0;
   // as many x rows unrolled as 128 registers of loads in flight hold
-#pragma unroll(W == 2 ? 2 : 4)
+  constexpr int ROWS = W == 2 ? 2 : 4;
+#pragma unroll ROWS
   for (int ax = 0; ax < 4; ++ax) {
     const c2<T>* px = fm + wrapi(cx - 1 + ax, n) * rowx;
     T sy[2 * W];
@@ -2823,10 +2788,8 @@ hipError_t launch_gather_source(int prec, const void* fields, const int* tcell, 
   return hipGetLastError();
 }
 
-hipError_t launch_tap_records(int prec, const float* pos, int* perm, const int* toff, long long ntiles,
-                              long long np_total, int n, double sc, int* tcell, void* twt, const double* btab,
-                              hipStream_t st) {
-  k_tile_order<<<(unsigned)((ntiles + 3) / 4), 256, 0, st>>>(pos, perm, toff, ntiles, n, sc, tcell);
+hipError_t launch_tap_records(int prec, const float* pos, const int* perm, long long np_total, int n, double sc,
+                              int* tcell, void* twt, const double* btab, hipStream_t st) {
   const unsigned g = grid_for(np_total, 256, 16384);
   if (prec)
     k_tap_records<double><<<g, 256, 0, st>>>(pos, perm, np_total, n, sc, tcell, static_cast<double*>(twt), btab);

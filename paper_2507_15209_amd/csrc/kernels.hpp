@@ -193,12 +193,10 @@ hipError_t launch_gather_source(int prec, const void* fields, const int* tcell, 
                                 int nbins, double wm, int nwg, int batch, double* FJ, void* src, hipStream_t st);
 hipError_t launch_scatter_source(int prec, const int* tcell, const void* twt, const int* toff, const void* src, int n,
                                  int nbins, int batch, void* out, hipStream_t st);
-// per-particle stencil records: the particles of every 4^3-cell tile put in cell order (perm
-// rewritten; toff from launch_tile_sort with shift 2), then per sorted slot the packed cell (-1 if
-// not finite) and 12 tap weights in the working precision
-hipError_t launch_tap_records(int prec, const float* pos, int* perm, const int* toff, long long ntiles,
-                              long long np_total, int n, double sc, int* tcell, void* twt, const double* btab,
-                              hipStream_t st);
+// per-particle stencil records in sorted order: packed cell (-1 if not
+// finite) and 12 tap weights in the working precision
+hipError_t launch_tap_records(int prec, const float* pos, const int* perm, long long np_total, int n, double sc,
+                              int* tcell, void* twt, const double* btab, hipStream_t st);
 hipError_t launch_fbar_adjoint(int prec, const double* dzeta, const void* jtab, int nq2, int nbp, int nbins, int lmax,
                                const void* dhat, int n, double scale, double* h, void* G, int batch, const void* phi,
                                const Acf& acf, hipStream_t st);

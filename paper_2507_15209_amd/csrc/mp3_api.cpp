@@ -97,12 +97,6 @@ size_t contract_wgs(const mp3_plan_s* p) {
   return (size_t)(g > 1 ? g : 1);
 }
 
-// 4^3-cell tiles of the particle sort, all mocks
-long long sort_tiles(const mp3_plan_s* p) {
-  const long long t = p->n / 4;
-  return t * t * t * p->batch;
-}
-
 size_t deposit_tiles(const mp3_plan_s* p) {
   const size_t t = (size_t)(p->n / p->tune[MP3_TUNE_DEPOSIT_TILE]);
   return t * t * t * (size_t)p->batch;
@@ -889,7 +883,7 @@ int zeta_particle(mp3_plan_t p, const float* pos, const float* w, const int64_t*
           "tile sort");
   int* tcell = reinterpret_cast<int*>(at(ws, L.tcell));
   void* twt = at(ws, L.twt);
-  MP3_HIP(mp3::launch_tap_records(p->prec, pos, perm, reinterpret_cast<const int*>(at(ws, L.offs)), sort_tiles(p), np_total, p->n, sc, tcell, twt, p->btab, st), "stencil records");
+  MP3_HIP(mp3::launch_tap_records(p->prec, pos, perm, np_total, p->n, sc, tcell, twt, p->btab, st), "stencil records");
   double* P = reinterpret_cast<double*>(at(ws, L.power));
   const int nq2 = mp3::nq2_count(p->n);
   MP3_HIP(mp3::launch_fill_f64(P, (long long)p->batch * nq2, 0.0, st), "zero power");
@@ -1056,7 +1050,7 @@ int backward_particle(mp3_plan_t p, const void* delta, const double* dzeta, void
           "tile sort");
   int* tcell = reinterpret_cast<int*>(at(ws, L.tcell));
   void* twt = at(ws, L.twt);
-  MP3_HIP(mp3::launch_tap_records(p->prec, pos, perm, reinterpret_cast<const int*>(at(ws, L.offs)), sort_tiles(p), np_total, p->n, sc, tcell, twt, p->btab, st), "stencil records");
+  MP3_HIP(mp3::launch_tap_records(p->prec, pos, perm, np_total, p->n, sc, tcell, twt, p->btab, st), "stencil records");
   void* F = at(ws, L.fields);
   void* Fi = at(ws, L.fields_i);
   void* G = at(ws, L.G);
@@ -1146,7 +1140,7 @@ int value_and_grad_particle(mp3_plan_t p, const void* delta, const double* dzeta
           "tile sort");
   int* tcell = reinterpret_cast<int*>(at(ws, L.tcell));
   void* twt = at(ws, L.twt);
-  MP3_HIP(mp3::launch_tap_records(p->prec, pos, perm, reinterpret_cast<const int*>(at(ws, L.offs)), sort_tiles(p), np_total, p->n, sc, tcell, twt, p->btab, st), "stencil records");
+  MP3_HIP(mp3::launch_tap_records(p->prec, pos, perm, np_total, p->n, sc, tcell, twt, p->btab, st), "stencil records");
   double* P = reinterpret_cast<double*>(at(ws, L.power));
   const int nq2 = mp3::nq2_count(p->n);
   MP3_HIP(mp3::launch_fill_f64(P, (long long)p->batch * nq2, 0.0, st), "zero power");
