@@ -528,10 +528,18 @@ def main():
               key=lambda k: passes[k][0])
     ms_tot, cnt = passes[dom]
     avg_ms = ms_tot / cnt
-    # (l, m) items per launch of the pass on average (1 unless the plan groups items)
-    per_item = {"filter": 1, "x": 2, "z_fused": 1, "adjoint": 1}.get(dom, 1)
+    # Fields per launch of the pass on average (1 unless the plan groups them).  A plan that runs
+    # more than one launch may carry the real m = 0 fields of two multipoles in one complex field,
+    # which moves the bytes of one: never more fields are counted than such a plan moves, so the
+    # rate is not overstated.
     items = (wl.lmax + 1) * (wl.lmax + 2) // 2
-    ipl = per_item * items * prof_steps / cnt
+    paired = items - (wl.lmax + 1) // 2
+
+    def fields_per_launch(name, count):
+        launches = count / prof_steps / {"x": 2}.get(name, 1)
+        return (items if launches <= 1 or launches > paired else paired) / launches
+
+    ipl = fields_per_launch(dom, cnt)
     abytes = pass_bytes(dom, wl.n, wl.nbins, 1, real_bytes) * ipl
     achieved = abytes / (avg_ms * 1e-3) / 1e9
     log("per-pass totals (ms, launches):", {k: (round(v[0], 2), v[1]) for k, v in passes.items()})
@@ -541,8 +549,7 @@ def main():
         b = pass_bytes(k, wl.n, wl.nbins, 1, real_bytes)
         if b is None:
             continue
-        ipk = {"filter": 1, "x": 2, "z_fused": 1, "adjoint": 1}.get(k, 1) * items * prof_steps / c
-        ach_k = b * ipk / (mt / c * 1e-3) / 1e9
+        ach_k = b * fields_per_launch(k, c) / (mt / c * 1e-3) / 1e9
         per_pass[k] = {"avg_launch_ms": mt / c, "achieved": ach_k, "frac": ach_k / HBM_PEAK_GBS}
     traffic = read_pmc(dom)
 
