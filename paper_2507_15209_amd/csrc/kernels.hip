@@ -479,8 +479,8 @@ __global__ void __launch_bounds__((strided_threads<N, T, VB>())) k_filter_y(cons
 
 // ---------------------------------------------------------------------------
 // pass z of the forward: z-transform of every bin of a pencil into LDS, then
-// the nodal contraction  P[b1,b2] += sum_z delta_z Re(a_b1 conj(a_b2))
-// in 4x4 register blocks (float32 per pencil, float64 across pencils).
+// the nodal contraction  P[b1,b2] += sum_z delta_z Re(a_b1 conj(a_b2)), where the
+// matrix cores do not take it in 4x4 register blocks (PairBlocks).
 // ---------------------------------------------------------------------------
 struct PairBlocks {
   int nblk, npb, zch;
@@ -589,32 +589,38 @@ typedef mfma_f4 mp3_f4;
 // 16x16x4 instruction per upper-triangular 16x16 block of (b1, b2) and part,
 // k = z:  A[b1][k] = delta_z re(a_b1(z)),  B[k][b2] = re(a_b2(z)), then im.
 // Lane l supplies A[l%16][l/16] and B[l/16][l%16].
-// the products of the real and of the imaginary parts apart: a pair item's parts belong to two multipoles
-template <typename T> struct MfmaAcc {
-  typename acc4<T>::type r00, r01, r11, i00, i01, i11;
+// B: 1 block (0,0) up to 16 bins, 3 blocks (0,0), (0,1), (1,1) beyond; 2 for 4x4 blocks of even and of odd k.
+// APART: the products of the real and of the imaginary parts in sums of their own, r and i (a pair item's parts
+// belong to two multipoles), else all in r, which halves the registers that the blocks beyond the first need
+template <typename T, int B, bool APART> struct MfmaAcc {
+  typename acc4<T>::type r[B], im[APART ? B : 1];
+  __device__ __forceinline__ typename acc4<T>::type& i(int k) { return APART ? im[APART ? k : 0] : r[k]; }
 };
 
-template <typename T>
-__device__ __forceinline__ void mfma_contract_step(const c2<T>* r0, const c2<T>* r1, const T* dl, int z, bool two,
-                                                   MfmaAcc<T>& acc) {
+template <typename T, int B, bool APART>
+__device__ __forceinline__ void mfma_contract_step(const c2<T>* r0, const c2<T>* r1, const T* dl, int z,
+                                                   MfmaAcc<T, B, APART>& acc) {
   const int off = lds_pos<true>(z);
   const T d = dl[z];
   const c2<T> v0 = r0[off];
-  acc.r00 = mfma16(d * v0.x, v0.x, acc.r00);
-  acc.i00 = mfma16(d * v0.y, v0.y, acc.i00);
-  if (two) {
-    const c2<T> v1 = r1[off];
-    acc.r01 = mfma16(d * v0.x, v1.x, acc.r01);
-    acc.i01 = mfma16(d * v0.y, v1.y, acc.i01);
-    acc.r11 = mfma16(d * v1.x, v1.x, acc.r11);
-    acc.i11 = mfma16(d * v1.y, v1.y, acc.i11);
+  c2<T> v1 = v0;
+  acc.r[0] = mfma16(d * v0.x, v0.x, acc.r[0]);
+  if constexpr (B == 3) {
+    v1 = r1[off];
+    acc.r[1] = mfma16(d * v0.x, v1.x, acc.r[1]);
+    acc.r[2] = mfma16(d * v1.x, v1.x, acc.r[2]);
+  }
+  acc.i(0) = mfma16(d * v0.y, v0.y, acc.i(0));
+  if constexpr (B == 3) {
+    acc.i(1) = mfma16(d * v0.y, v1.y, acc.i(1));
+    acc.i(2) = mfma16(d * v1.y, v1.y, acc.i(2));
   }
 }
 
 // N a multiple of 4
-template <typename T>
+template <typename T, int B, bool APART>
 __device__ __forceinline__ void mfma_contract_pencil(const c2<T>* A, const T* dl, int nbins, int RS, int N,
-                                                     MfmaAcc<T>& acc) {
+                                                     MfmaAcc<T, B, APART>& acc) {
   const int lane = threadIdx.x & 63;
   const int w = threadIdx.x >> 6;
   const int nw = blockDim.x >> 6;
@@ -623,19 +629,19 @@ __device__ __forceinline__ void mfma_contract_pencil(const c2<T>* A, const T* dl
   // entries of P that the reduction drops, and the loads need no mask
   const c2<T>* r0 = A + (col < nbins ? col : 0) * RS;
   const c2<T>* r1 = A + (16 + col < nbins ? 16 + col : 0) * RS;
-  for (int z = 4 * w; z < N; z += 4 * nw) mfma_contract_step<T>(r0, r1, dl, z + kq, nbins > 16, acc);
+  for (int z = 4 * w; z < N; z += 4 * nw) mfma_contract_step<T, B, APART>(r0, r1, dl, z + kq, acc);
 }
 
 // the same for z in [z0, z1) (bounds multiples of 4), all by the calling wave
-template <typename T>
+template <typename T, int B, bool APART>
 __device__ __forceinline__ void mfma_contract_pencil_range(const c2<T>* A, const T* dl, int nbins, int RS, int z0,
-                                                           int z1, MfmaAcc<T>& acc) {
+                                                           int z1, MfmaAcc<T, B, APART>& acc) {
   const int lane = threadIdx.x & 63;
   const int col = lane & 15, kq = lane >> 4;
   const c2<T>* r0 = A + (col < nbins ? col : 0) * RS;
   const c2<T>* r1 = A + (16 + col < nbins ? 16 + col : 0) * RS;
 #pragma unroll 4
-  for (int z = z0; z < z1; z += 4) mfma_contract_step<T>(r0, r1, dl, z + kq, nbins > 16, acc);
+  for (int z = z0; z < z1; z += 4) mfma_contract_step<T, B, APART>(r0, r1, dl, z + kq, acc);
 }
 
 // 17..20 bins: the 15 upper-triangle 4x4 blocks (g1 <= g2 of 5 bin groups)
@@ -652,8 +658,9 @@ __device__ __forceinline__ void pair_group(int beta, int& g1, int& g2) {
   g2 = r + rem;
 }
 
+template <bool APART>
 __device__ __forceinline__ void mfma_contract_4x4(const float2* A, const float* dl, int nbins, int RS, int K,
-                                                  MfmaAcc<float>& acc) {
+                                                  MfmaAcc<float, 2, APART>& acc) {
   const int lane = threadIdx.x & 63;
   const int w = threadIdx.x >> 6;
   const int nw = blockDim.x >> 6;
@@ -670,16 +677,17 @@ __device__ __forceinline__ void mfma_contract_4x4(const float2* A, const float* 
     const int zp0 = lds_pos<true>(z), zp1 = lds_pos<true>(z + 1);
     const float d0 = dl[z], d1 = dl[z + 1];
     const float2 u0 = ra[zp0], v0 = rb[zp0], u1 = ra[zp1], v1 = rb[zp1];
-    acc.r00 = __builtin_amdgcn_mfma_f32_4x4x1f32(d0 * u0.x, v0.x, acc.r00, 0, 0, 0);
-    acc.i00 = __builtin_amdgcn_mfma_f32_4x4x1f32(d0 * u0.y, v0.y, acc.i00, 0, 0, 0);
-    acc.r01 = __builtin_amdgcn_mfma_f32_4x4x1f32(d1 * u1.x, v1.x, acc.r01, 0, 0, 0);
-    acc.i01 = __builtin_amdgcn_mfma_f32_4x4x1f32(d1 * u1.y, v1.y, acc.i01, 0, 0, 0);
+    acc.r[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(d0 * u0.x, v0.x, acc.r[0], 0, 0, 0);
+    acc.i(0) = __builtin_amdgcn_mfma_f32_4x4x1f32(d0 * u0.y, v0.y, acc.i(0), 0, 0, 0);
+    acc.r[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(d1 * u1.x, v1.x, acc.r[1], 0, 0, 0);
+    acc.i(1) = __builtin_amdgcn_mfma_f32_4x4x1f32(d1 * u1.y, v1.y, acc.i(1), 0, 0, 0);
   }
 }
 
 // the same for z in [z0, z1) (even bounds), all by the calling wave
+template <bool APART>
 __device__ __forceinline__ void mfma_contract_4x4_range(const float2* A, const float* dl, int nbins, int RS, int z0,
-                                                        int z1, MfmaAcc<float>& acc) {
+                                                        int z1, MfmaAcc<float, 2, APART>& acc) {
   const int lane = threadIdx.x & 63;
   const int beta = lane >> 2, i = lane & 3;
   int g1 = 0, g2 = 0;
@@ -695,10 +703,10 @@ __device__ __forceinline__ void mfma_contract_4x4_range(const float2* A, const f
     const int zp0 = lds_pos<true>(z), zp1 = lds_pos<true>(z + 1);
     const float d0 = dl[z], d1 = dl[z + 1];
     const float2 u0 = ra[zp0], v0 = rb[zp0], u1 = ra[zp1], v1 = rb[zp1];
-    acc.r00 = __builtin_amdgcn_mfma_f32_4x4x1f32(d0 * u0.x, v0.x, acc.r00, 0, 0, 0);
-    acc.i00 = __builtin_amdgcn_mfma_f32_4x4x1f32(d0 * u0.y, v0.y, acc.i00, 0, 0, 0);
-    acc.r01 = __builtin_amdgcn_mfma_f32_4x4x1f32(d1 * u1.x, v1.x, acc.r01, 0, 0, 0);
-    acc.i01 = __builtin_amdgcn_mfma_f32_4x4x1f32(d1 * u1.y, v1.y, acc.i01, 0, 0, 0);
+    acc.r[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(d0 * u0.x, v0.x, acc.r[0], 0, 0, 0);
+    acc.i(0) = __builtin_amdgcn_mfma_f32_4x4x1f32(d0 * u0.y, v0.y, acc.i(0), 0, 0, 0);
+    acc.r[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(d1 * u1.x, v1.x, acc.r[1], 0, 0, 0);
+    acc.i(1) = __builtin_amdgcn_mfma_f32_4x4x1f32(d1 * u1.y, v1.y, acc.i(1), 0, 0, 0);
   }
 }
 
@@ -734,13 +742,13 @@ __device__ __forceinline__ mp3_f4 mfma3(const mp3_s4& ah, const mp3_s4& al, cons
 
 // K must be a multiple of 8.  Lane l supplies A[l%16][4 (l/16) + j] and
 // B[4 (l/16) + j][l%16], j = 0..3: k = 2 (z - z0) + comp over z = z0 + 2 (l/16) + {0, 1}.
+template <int B, bool APART>
 __device__ __forceinline__ void mfma_contract_bf16x3(const float2* A, const float* dl, int nbins, int RS, int K,
-                                                     MfmaAcc<float>& acc) {
+                                                     MfmaAcc<float, B, APART>& acc) {
   const int lane = threadIdx.x & 63;
   const int w = threadIdx.x >> 6;
   const int nw = blockDim.x >> 6;
   const int col = lane & 15, kq = lane >> 4;
-  const bool two = nbins > 16;
   const bool ok0 = col < nbins, ok1 = 16 + col < nbins;
   const float2* r0 = A + col * RS;
   const float2* r1 = A + (16 + col) * RS;
@@ -755,8 +763,8 @@ __device__ __forceinline__ void mfma_contract_bf16x3(const float2* A, const floa
     mp3_s4 ah, al, bh, bl;
     bf16_split4(xa, ah, al);
     bf16_split4(xb, bh, bl);
-    acc.r00 = mfma3(ah, al, bh, bl, acc.r00);
-    if (two) {
+    acc.r[0] = mfma3(ah, al, bh, bl, acc.r[0]);
+    if constexpr (B == 3) {
       u0 = ok1 ? r1[p0] : make_float2(0.f, 0.f);
       u1 = ok1 ? r1[p1] : make_float2(0.f, 0.f);
       float ya[4] = {d0 * u0.x, d0 * u0.y, d1 * u1.x, d1 * u1.y};
@@ -764,25 +772,45 @@ __device__ __forceinline__ void mfma_contract_bf16x3(const float2* A, const floa
       mp3_s4 ch, cl, dh, dlo;
       bf16_split4(ya, ch, cl);
       bf16_split4(yb, dh, dlo);
-      acc.r01 = mfma3(ah, al, dh, dlo, acc.r01);
-      acc.r11 = mfma3(ch, cl, dh, dlo, acc.r11);
+      acc.r[1] = mfma3(ah, al, dh, dlo, acc.r[1]);
+      acc.r[2] = mfma3(ch, cl, dh, dlo, acc.r[2]);
     }
   }
 }
 
+// MfmaAcc blocks of a contraction of at most maxnb bins
+constexpr int mf_blocks(bool mf, bool quad, int maxnb) { return quad ? 2 : mf && maxnb > 16 ? 3 : 1; }
+
+// a + b rounded, e its rounding error (Knuth's two-sum; none where the sum overflowed or is NaN)
+template <typename T> __device__ __forceinline__ T two_sum(T a, T b, T& e) {
+  const T s = a + b, t = s - a;
+  const T r = (a - (s - t)) + (b - t);
+  e = r - r == 0 ? r : (T)0;
+  return s;
+}
+
 // Per-workgroup accumulator of  P[b1,b2] = sum_k w_k Re(a_b1(k) conj(a_b2(k)))
 // over LDS rows A[b * RS + lds_pos(k)], either on the matrix cores (MF) or in
-// 4x4 register blocks on the vector ALUs.  Partial sums stay in the working
-// precision over the workgroup's slices and are written as float64.
-// QUAD: 4x4 blocks on the matrix cores (float32 inputs, 17..20 bins)
-template <typename T, bool MF, bool SPLIT = false, bool QUAD = false>
+// 4x4 register blocks on the vector ALUs.  Sums run in the working precision over
+// one pencil or slice; close() then moves them into hi and leaves their rounding
+// error to start the next one from, so that a workgroup may take any number of them:
+// the sum's error is that of one pencil (constant float32 field, 64^3, 2 bins, 91 items in a launch,
+// 92 pencils a workgroup: 7e-5 without it, 6e-7 with it; no time at 256^3, 20 bins or 128^3, 12 bins).
+// Written as float64.
+// QUAD: 4x4 blocks on the matrix cores (float32 inputs, 17..20 bins); B, APART: see MfmaAcc.
+// The float64 sums of the 4x4 register blocks stay plain: each thread adds a zch-th of a pencil, a few
+// hundred products a workgroup, and the kernel has no registers left (17..32 bins: 55 spilled with hi).
+template <typename T, bool MF, bool SPLIT, bool QUAD, int B, bool APART>
 struct Contractor {
-  static __host__ __device__ bool quad(int) { return QUAD; }
+  static_assert(QUAD ? B == 2 : B == 1 || B == 3, "matrix blocks");
+  static constexpr int HB = QUAD ? 1 : B;
+  static constexpr bool HI = MF || sizeof(T) == 4;
   PairBlocks pb;
   int bb1 = 0, bb2 = 0, zc = 0;
   bool has_item = false;
-  T acc[MF ? 1 : 16];
-  MfmaAcc<T> macc;
+  T acc[MF ? 1 : 16], hi[MF ? 1 : 16];
+  MfmaAcc<T, B, APART> macc;
+  MfmaAcc<T, HB, APART> mhi;
 
   __device__ void init(int nbins) {
     pb.init(nbins, blockDim.x);
@@ -792,19 +820,50 @@ struct Contractor {
       zc = threadIdx.x % pb.zch;
     }
 #pragma unroll
-    for (int i = 0; i < (MF ? 1 : 16); ++i) acc[i] = (T)0;
-    macc.r00 = typename acc4<T>::type{0, 0, 0, 0};
-    macc.r01 = macc.r11 = macc.i00 = macc.i01 = macc.i11 = macc.r00;
+    for (int i = 0; i < (MF ? 1 : 16); ++i) acc[i] = hi[i] = (T)0;
+#pragma unroll
+    for (int k = 0; k < B; ++k) macc.r[k] = macc.i(k) = typename acc4<T>::type{0, 0, 0, 0};
+#pragma unroll
+    for (int k = 0; k < HB; ++k) mhi.r[k] = mhi.i(k) = typename acc4<T>::type{0, 0, 0, 0};
+  }
+
+  // after the products of a pencil or slice
+  __device__ void close() {
+    if constexpr (MF) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        close_part(mhi.r, macc.r, i);
+        if constexpr (APART) close_part(mhi.im, macc.im, i);
+      }
+    } else if constexpr (HI) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        T e;
+        hi[i] = two_sum<T>(hi[i], acc[i], e);
+        acc[i] = e;
+      }
+    }
+  }
+  // element i of one part's blocks; the even and the odd sum of a 4x4 block have one hi
+  template <typename V> static __device__ __forceinline__ void close_part(V* h, V* a, int i) {
+#pragma unroll
+    for (int k = 0; k < HB; ++k) {
+      T e, e2 = 0;
+      const T v = QUAD ? two_sum<T>(a[0][i], a[B - 1][i], e2) : a[k][i];
+      h[k][i] = two_sum<T>(h[k][i], v, e);
+      a[k][i] = e + e2;
+      if constexpr (QUAD) a[B - 1][i] = 0;
+    }
   }
 
   // K positions (even), weights w[k] in LDS
   __device__ void add(const c2<T>* A, const T* w, int nbins, int RS, int K) {
     if constexpr (MF && SPLIT) {
-      mfma_contract_bf16x3(reinterpret_cast<const float2*>(A), reinterpret_cast<const float*>(w), nbins, RS, K, macc);
+      mfma_contract_bf16x3<B, APART>(reinterpret_cast<const float2*>(A), reinterpret_cast<const float*>(w), nbins, RS, K, macc);
     } else if constexpr (MF && QUAD) {
-      mfma_contract_4x4(reinterpret_cast<const float2*>(A), reinterpret_cast<const float*>(w), nbins, RS, K, macc);
+      mfma_contract_4x4<APART>(reinterpret_cast<const float2*>(A), reinterpret_cast<const float*>(w), nbins, RS, K, macc);
     } else if constexpr (MF) {
-      mfma_contract_pencil<T>(A, w, nbins, RS, K, macc);
+      mfma_contract_pencil<T, B, APART>(A, w, nbins, RS, K, macc);
     } else if (has_item) {
       const int b1o = 4 * bb1, b2o = 4 * bb2;
       for (int z = zc; z < K; z += pb.zch) {
@@ -829,21 +888,21 @@ struct Contractor {
   __device__ void add_range(const c2<T>* A, const T* w, int nbins, int RS, int z0, int z1) {
     static_assert(MF && !SPLIT, "range contraction: matrix-core forms with full inputs");
     if constexpr (QUAD)
-      mfma_contract_4x4_range(reinterpret_cast<const float2*>(A), reinterpret_cast<const float*>(w), nbins, RS, z0, z1,
+      mfma_contract_4x4_range<APART>(reinterpret_cast<const float2*>(A), reinterpret_cast<const float*>(w), nbins, RS, z0, z1,
                               macc);
     else
-      mfma_contract_pencil_range<T>(A, w, nbins, RS, z0, z1, macc);
+      mfma_contract_pencil_range<T, B, APART>(A, w, nbins, RS, z0, z1, macc);
   }
 
   // LDS bytes finish() needs as scratch
   static __host__ __device__ size_t scratch_bytes(int threads) {
-    return MF ? (size_t)(threads / 64) * 3 * 256 * sizeof(double) : (size_t)threads * 16 * sizeof(double);
+    return MF ? (size_t)(threads / 64) * B * 256 * sizeof(double) : (size_t)threads * 16 * sizeof(double);
   }
 
   // workgroup reduction through LDS scratch red, symmetric partial to out[nbins^2]; pair (matrix-core
   // forms): the real parts' sum there and the imaginary parts' behind it
   __device__ void finish(double* red, double* out, int nbins, bool pair = false) {
-    if constexpr (MF) {
+    if constexpr (APART) {
       if (pair) {
         finish_part(red, out, nbins, 1.0, 0.0);
         __syncthreads();
@@ -854,6 +913,13 @@ struct Contractor {
     finish_part(red, out, nbins, 1.0, 1.0);
   }
 
+  // element i of block k: wr times the real parts' sum plus wi times the imaginary parts' (every part: r alone)
+  __device__ double total(int k, int i, double wr, double wi) {
+    const double r = (double)mhi.r[k][i] + (double)macc.r[k][i];
+    if constexpr (APART) return wr * r + wi * ((double)mhi.im[k][i] + (double)macc.im[k][i]);
+    return r;
+  }
+
   // wr times the real parts' sum plus wi times the imaginary parts'
   __device__ void finish_part(double* red, double* out, int nbins, double wr, double wi) {
     const int tid = threadIdx.x;
@@ -862,8 +928,7 @@ struct Contractor {
       const int lane = tid & 63, w = tid >> 6, nw = blockDim.x >> 6;
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        red[(w * 16 + (lane >> 2)) * 16 + i * 4 + (lane & 3)] =
-            wr * ((double)macc.r00[i] + (double)macc.r01[i]) + wi * ((double)macc.i00[i] + (double)macc.i01[i]);
+        red[(w * 16 + (lane >> 2)) * 16 + i * 4 + (lane & 3)] = total(0, i, wr, wi);
       __syncthreads();
       for (int t = tid; t < 15 * 16; t += blockDim.x) {
         const int beta = t / 16, row = (t / 4) % 4, col = t % 4;
@@ -879,20 +944,20 @@ struct Contractor {
         }
       }
     } else if constexpr (MF) {
-      // red[w][blk][row][col], blk 0 = (0,0), 1 = (0,1), 2 = (1,1)
+      // red[w][blk][row][col]
       const int lane = tid & 63, w = tid >> 6, nw = blockDim.x >> 6;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int row = mfma_row<T>(lane, i), col = lane & 15;
-        red[((w * 3 + 0) * 16 + row) * 16 + col] = wr * (double)macc.r00[i] + wi * (double)macc.i00[i];
-        red[((w * 3 + 1) * 16 + row) * 16 + col] = wr * (double)macc.r01[i] + wi * (double)macc.i01[i];
-        red[((w * 3 + 2) * 16 + row) * 16 + col] = wr * (double)macc.r11[i] + wi * (double)macc.i11[i];
+#pragma unroll
+        for (int k = 0; k < B; ++k)
+          red[((w * B + k) * 16 + row) * 16 + col] = total(k, i, wr, wi);
       }
       __syncthreads();
-      for (int t = tid; t < 3 * 256; t += blockDim.x) {
+      for (int t = tid; t < B * 256; t += blockDim.x) {
         const int blk = t / 256, row = (t / 16) % 16, col = t % 16;
         double sacc = 0.0;
-        for (int ww = 0; ww < nw; ++ww) sacc += red[((ww * 3 + blk) * 16 + row) * 16 + col];
+        for (int ww = 0; ww < nw; ++ww) sacc += red[((ww * B + blk) * 16 + row) * 16 + col];
         const int b1 = row + (blk == 2 ? 16 : 0), b2 = col + (blk >= 1 ? 16 : 0);
         if (b1 < nbins && b2 < nbins && b1 <= b2) {
           out[b1 * nbins + b2] = sacc;
@@ -902,7 +967,7 @@ struct Contractor {
     } else {
       if (has_item) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) red[tid * 16 + i] = (double)acc[i];
+        for (int i = 0; i < 16; ++i) red[tid * 16 + i] = HI ? (double)hi[i] + (double)acc[i] : (double)acc[i];
       }
       __syncthreads();
       for (int t = tid; t < pb.npb * 16; t += blockDim.x) {
@@ -1199,8 +1264,9 @@ constexpr int kGatherSlots = 256;
 // of the cotangent, lam_d its eigenvalues): per lane v_b = d_b conj(atilde_b),
 // src = N^3 (w_i / W) v_b, and wm sum_b d_b |atilde_b|^2 added to F_J(u_i),
 // all at gather time.
-template <typename T, bool MF, bool SPLIT, bool QUAD, bool SRC, int WB>
-__global__ void __launch_bounds__(256) k_gather_contract(const c2<T>* fields, const int* tcell, const T* twt,
+template <typename T, bool MF, bool SPLIT, bool QUAD, int B, bool APART, bool SRC, int WB>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 2 : 1)))
+k_gather_contract(const c2<T>* fields, const int* tcell, const T* twt,
                                                           const float* w, const int* perm, const long long* off,
                                                           const double* W, int n, int nbins, double* partials,
                                                           const T* lam_d, const T* lam_d2, int pair, T wm, double* FJ,
@@ -1254,7 +1320,7 @@ __global__ void __launch_bounds__(256) k_gather_contract(const c2<T>* fields, co
       lam2[t] = lam_d2[mock * nbins + t];
     }
   }
-  Contractor<T, MF, SPLIT, QUAD> ctr;
+  Contractor<T, MF, SPLIT, QUAD, B, APART> ctr;
   ctr.init(nbins);
   for (long long c0 = s0; c0 < s1; c0 += kcount) {
     for (int k0 = 0; k0 < kcount; k0 += ppp) {
@@ -1288,6 +1354,7 @@ __global__ void __launch_bounds__(256) k_gather_contract(const c2<T>* fields, co
     }
     __syncthreads();
     ctr.add(A, wk, nbins, RS, kcount);
+    ctr.close();
     if constexpr (SRC) {
       // the primary vertex's share: F_J(u_i) += wm sum_b d_b |atilde_b|^2, one thread per slot
       for (int k = threadIdx.x; k < kcount; k += blockDim.x) {
@@ -1414,8 +1481,8 @@ __global__ void k_reduce_partials(const double* partials, int nwg, int part, int
 // ---------------------------------------------------------------------------
 // MODE: what the pass does with the transformed pencil
 constexpr int Z_ADJOINT = 0, Z_FUSED = 1, Z_FORWARD = 2;
-template <int N, typename T, int MAXNB, int MODE, bool MF, bool QUAD, bool SPLIT>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(MODE != Z_ADJOINT && MF ? 3 : 1)))
+template <int N, typename T, int MAXNB, int MODE, bool MF, bool QUAD, bool SPLIT, bool APART>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(MODE != Z_ADJOINT && (MF || sizeof(T) == 4) ? 3 : 1)))
 k_zpass(c2<T>* fields, const T* delta, const T* __restrict__ lam_d, T* direct, int nbins, int ppw,
                 const c2<T>* tw, double* partials, const ItemRec* items, int item0, int nitems, int batch, int nwg,
                 int* counter) {
@@ -1467,7 +1534,7 @@ k_zpass(c2<T>* fields, const T* delta, const T* __restrict__ lam_d, T* direct, i
       }
     }
     __syncthreads();
-    Contractor<T, MF, SPLIT, QUAD> ctr;
+    Contractor<T, MF, SPLIT, QUAD, mf_blocks(MF, QUAD, MAXNB), APART> ctr;
     if constexpr (FUSED) ctr.init(nbins);
     const int p0 = chunk * ppw;
     const int p1 = min(p0 + ppw, N * N);
@@ -1533,6 +1600,7 @@ k_zpass(c2<T>* fields, const T* delta, const T* __restrict__ lam_d, T* direct, i
           ctr.add(A, dl, nbins, RS, N);
           __syncthreads();
         }
+        ctr.close();
       }
       if constexpr (GRAD) {
 #pragma unroll
@@ -2315,19 +2383,19 @@ template <int N, typename T> inline size_t zpass_fused_lds(int nbins, int thread
 // kZpassResident workgroups take units from the counter (zeroed here first)
 constexpr int kZpassResident = 2048;
 
-template <int N, typename T, int MAXNB, int MODE, bool MF, bool QUAD = false, bool SPLIT = false>
-hipError_t zpass_mode(const ZpassArgs& a, hipStream_t st) {
+template <int N, typename T, int MAXNB, int MODE, bool MF, bool QUAD, bool SPLIT, bool APART>
+hipError_t zpass_parts(const ZpassArgs& a, hipStream_t st) {
   // the forward takes the fewest whole waves with a thread per z point; on the vector ALUs the 4x4 pair
   // blocks (136 at 64 bins) need a thread each
   const int threads = MODE == Z_FUSED     ? zpass_fused_threads<N, T>(a.nbins, a.waves)
                       : MODE == Z_FORWARD ? zpass_fused_threads<N, T>(a.nbins, MF ? 1 : 4)
                                           : zpass_threads<N, VZA<T>>(a.nbins);
-  const size_t scratch = MODE == Z_ADJOINT ? 0 : Contractor<T, MF, SPLIT, QUAD>::scratch_bytes(threads);
+  const size_t scratch = MODE == Z_ADJOINT ? 0 : Contractor<T, MF, SPLIT, QUAD, mf_blocks(MF, QUAD, MAXNB), APART>::scratch_bytes(threads);
   size_t lds = MODE == Z_ADJOINT ? zpass_adjoint_lds<N, T>(a.nbins)
                : MODE == Z_FUSED ? zpass_fused_lds<N, T>(a.nbins, threads, scratch)
                                  : zpass_nodal_lds<N, T>(a.nbins, 0);
   if (lds < scratch) lds = scratch;
-  auto kern = k_zpass<N, T, MAXNB, MODE, MF, QUAD, SPLIT>;
+  auto kern = k_zpass<N, T, MAXNB, MODE, MF, QUAD, SPLIT, APART>;
   hipError_t e = allow_lds(kern, lds);
   if (e != hipSuccess) return e;
   k_fill<int><<<1, 64, 0, st>>>(a.counter, 1, 0);
@@ -2338,6 +2406,19 @@ hipError_t zpass_mode(const ZpassArgs& a, hipStream_t st) {
       static_cast<T*>(a.direct), a.nbins, a.ppw, static_cast<const CT<T>*>(a.tw), a.partials, a.items, a.item0,
       a.nitems, a.batch, a.nwg, a.counter);
   return hipGetLastError();
+}
+
+// one 16x16 block keeps the parts apart for every item (its registers allow it), the others for pair items alone
+template <int N, typename T, int MAXNB, int MODE, bool MF, bool QUAD = false, bool SPLIT = false>
+hipError_t zpass_mode(const ZpassArgs& a, hipStream_t st) {
+  if constexpr (MODE == Z_ADJOINT || !MF || SPLIT) {
+    return zpass_parts<N, T, MAXNB, MODE, MF, QUAD, SPLIT, false>(a, st);
+  } else {
+    if constexpr (mf_blocks(MF, QUAD, MAXNB) > 1) {
+      if (!a.pair) return zpass_parts<N, T, MAXNB, MODE, MF, QUAD, SPLIT, false>(a, st);
+    }
+    return zpass_parts<N, T, MAXNB, MODE, MF, QUAD, SPLIT, true>(a, st);
+  }
 }
 
 // Contraction of the z passes on the matrix cores: float32 up to 32 bins; float64 up to 16, where one
@@ -2361,12 +2442,14 @@ hipError_t zpass_fused_t(const ZpassArgs& a, hipStream_t st) {
 // forward contraction (float32: also with BF16-split inputs)
 template <int N, typename T>
 hipError_t zpass_nodal_t(const ZpassArgs& a, hipStream_t st) {
-  if (a.nbins > mf_bins<T>()) return zpass_mode<N, T, 4, Z_FORWARD, false>(a, st);
+  if (a.nbins > mf_bins<T>()) return zpass_mode<N, T, 64, Z_FORWARD, false>(a, st);
   if constexpr (std::is_same<T, float>::value) {
-    if (a.split) return zpass_mode<N, T, 4, Z_FORWARD, true, false, true>(a, st);
-    if (a.nbins > 16 && a.nbins <= 20) return zpass_mode<N, T, 4, Z_FORWARD, true, true>(a, st);
+    if (a.split && a.nbins > 16) return zpass_mode<N, T, 32, Z_FORWARD, true, false, true>(a, st);
+    if (a.split) return zpass_mode<N, T, 16, Z_FORWARD, true, false, true>(a, st);
+    if (a.nbins > 20) return zpass_mode<N, T, 32, Z_FORWARD, true>(a, st);
+    if (a.nbins > 16) return zpass_mode<N, T, 20, Z_FORWARD, true, true>(a, st);
   }
-  return zpass_mode<N, T, 4, Z_FORWARD, true>(a, st);
+  return zpass_mode<N, T, 16, Z_FORWARD, true>(a, st);
 }
 
 template <int N, typename T>
@@ -2436,8 +2519,8 @@ template <int N, typename T> size_t zpass_fused_lds_need_t(int nbins) {
   if (nbins > 32) return (size_t)1 << 40;
   const int threads = 512;   // the largest workgroup any waves setting gives
   return zpass_fused_lds<N, T>(nbins, threads,
-                               nbins <= mf_bins<T>() ? Contractor<T, true>::scratch_bytes(threads)
-                                                     : Contractor<T, false>::scratch_bytes(threads));
+                               nbins <= mf_bins<T>() ? Contractor<T, true, false, false, 3, false>::scratch_bytes(threads)
+                                                     : Contractor<T, false, false, false, 1, false>::scratch_bytes(threads));
 }
 
 size_t zpass_fused_lds_need(int n, int prec, int nbins) {
@@ -2695,18 +2778,18 @@ hipError_t launch_deposit_tiled(int prec, int tside, const float* pos, const flo
                                 btab, st);
 }
 
-template <typename T, bool MF, bool SPLIT, bool QUAD, bool SRC, int W>
+template <typename T, bool MF, bool SPLIT, bool QUAD, int B, bool APART, bool SRC, int W>
 hipError_t gather_contract_v(const GatherArgs& a, hipStream_t st) {
   constexpr int K = kGatherSlots;
   const size_t rs = K + K / 16 + 1;
   size_t lds = (size_t)a.nbins * rs * sizeof(CT<T>) + K * sizeof(T);
   if (SRC) lds += K * sizeof(int) + (size_t)2 * a.nbins * sizeof(T);
-  const size_t red = Contractor<T, MF, SPLIT, QUAD>::scratch_bytes(256);
+  const size_t red = Contractor<T, MF, SPLIT, QUAD, B, APART>::scratch_bytes(256);
   if (lds < red) lds = red;
-  hipError_t e = allow_lds(k_gather_contract<T, MF, SPLIT, QUAD, SRC, W>, lds);
+  hipError_t e = allow_lds(k_gather_contract<T, MF, SPLIT, QUAD, B, APART, SRC, W>, lds);
   if (e != hipSuccess) return e;
   const dim3 gs(a.nwg, a.batch);
-  k_gather_contract<T, MF, SPLIT, QUAD, SRC, W><<<gs, 256, lds, st>>>(
+  k_gather_contract<T, MF, SPLIT, QUAD, B, APART, SRC, W><<<gs, 256, lds, st>>>(
       static_cast<const CT<T>*>(a.fields), a.tcell, static_cast<const T*>(a.twt), a.w, a.perm, a.off, a.W, a.n, a.nbins,
       a.partials, static_cast<const T*>(a.lam), static_cast<const T*>(a.lam2 ? a.lam2 : a.lam), a.pair ? 1 : 0, (T)a.wm, a.FJ, static_cast<CT<T>*>(a.src));
   return hipGetLastError();
@@ -2714,27 +2797,38 @@ hipError_t gather_contract_v(const GatherArgs& a, hipStream_t st) {
 
 // float32 reads two bins per lane in 16-byte loads (half the load instructions: 512^3, 20 bins
 // 42.0 -> 35.5 ms; 128^3, 15 bins 0.66 -> 0.51 ms); float64 bins are 16 bytes each
-template <typename T, bool MF, bool SPLIT = false, bool QUAD = false>
-hipError_t gather_contract_t(const GatherArgs& a, hipStream_t st) {
+template <typename T, bool MF, int B, bool SPLIT, bool QUAD, bool APART>
+hipError_t gather_contract_w(const GatherArgs& a, hipStream_t st) {
   if constexpr (std::is_same<T, float>::value) {
     if (a.nbins > 1)
-      return a.src ? gather_contract_v<T, MF, SPLIT, QUAD, true, 2>(a, st)
-                   : gather_contract_v<T, MF, SPLIT, QUAD, false, 2>(a, st);
+      return a.src ? gather_contract_v<T, MF, SPLIT, QUAD, B, APART, true, 2>(a, st)
+                   : gather_contract_v<T, MF, SPLIT, QUAD, B, APART, false, 2>(a, st);
   }
-  if (a.src) return gather_contract_v<T, MF, SPLIT, QUAD, true, 1>(a, st);
-  return gather_contract_v<T, MF, SPLIT, QUAD, false, 1>(a, st);
+  if (a.src) return gather_contract_v<T, MF, SPLIT, QUAD, B, APART, true, 1>(a, st);
+  return gather_contract_v<T, MF, SPLIT, QUAD, B, APART, false, 1>(a, st);
+}
+
+template <typename T, bool MF, int B, bool SPLIT = false, bool QUAD = false>
+hipError_t gather_contract_t(const GatherArgs& a, hipStream_t st) {
+  if constexpr (MF && !SPLIT) {
+    if (B == 1 || a.pair) return gather_contract_w<T, MF, B, SPLIT, QUAD, true>(a, st);
+  }
+  if constexpr (!MF || SPLIT || B > 1) return gather_contract_w<T, MF, B, SPLIT, QUAD, false>(a, st);
+  return hipErrorInvalidValue;   // unreachable
 }
 
 hipError_t launch_gather_contract(int prec, const GatherArgs& a, hipStream_t st) {
   // float64: the matrix cores up to 16 bins (9 bins: the same time as the vector ALUs), which keep a pair
   // item's parts apart
-  if (prec) return a.nbins <= 16 ? gather_contract_t<double, true>(a, st) : gather_contract_t<double, false>(a, st);
+  if (prec) return a.nbins <= 16 ? gather_contract_t<double, true, 1>(a, st) : gather_contract_t<double, false, 1>(a, st);
+  if (a.nbins <= 16)
+    return a.split ? gather_contract_t<float, true, 1, true>(a, st) : gather_contract_t<float, true, 1>(a, st);
   if (a.nbins <= 32) {
-    if (a.split) return gather_contract_t<float, true, true>(a, st);
-    if (a.nbins > 16 && a.nbins <= 20) return gather_contract_t<float, true, false, true>(a, st);
-    return gather_contract_t<float, true>(a, st);
+    if (a.split) return gather_contract_t<float, true, 3, true>(a, st);
+    if (a.nbins <= 20) return gather_contract_t<float, true, 2, false, true>(a, st);
+    return gather_contract_t<float, true, 3>(a, st);
   }
-  return gather_contract_t<float, false>(a, st);
+  return gather_contract_t<float, false, 1>(a, st);
 }
 
 hipError_t launch_power_hist(int prec, const void* dhat, int n, int nq2, double* P, int batch, const void* phi,

@@ -64,6 +64,7 @@ struct ZpassArgs {
   const void* tw;
   int nbins, nwg, ppw, batch, l, lmax;
   bool split;           // float32 contraction with BF16-split inputs on the matrix cores
+  bool pair = false;    // pair items (a launch holds one kind)
   int waves = 0;        // one-sweep z pass: waves per workgroup (0 = default)
   // adjoint passes: the group of items (table, first item, count) and the
   // persistent launch's work counter (device int, zeroed by the launch)

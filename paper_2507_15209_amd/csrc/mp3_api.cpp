@@ -449,6 +449,7 @@ mp3::ZpassArgs adjoint_zargs(const mp3_plan_s* p, void* ws, const Layout& L, voi
   z.lmax = p->lmax;
   z.items = p->items_dev;
   z.item0 = item0;
+  z.pair = p->items[item0].l2 >= 0;
   z.nitems = nitems;
   z.counter = reinterpret_cast<int*>(at(ws, L.counter));
   return z;
