@@ -254,14 +254,15 @@ int mp3_zeta_backward(mp3_plan_t plan, const void* delta, const double* dzeta,
  * nor computed twice.  Particle form: the per-call steps (tile sort, stencil
  * records, power histogram) run once and each (l, m)'s stored fields feed
  * both the gather contraction and the adjoint sources.  Grid-Gamma form:
- * each (l, m)'s stored fields feed both kernels.
+ * each (l, m)'s stored fields are contracted as in mp3_zeta (the same zeta,
+ * whatever dzeta) and then turned into the cotangent's eigenbasis.
  * Nodal and particle BF16-split plans and nodal plans above 32 bins run
- * mp3_zeta and then mp3_zeta_backward.  zeta is contracted over the fields of
- * the cotangent's eigenbasis (see mp3_zeta_backward) and rotated back,
- * zeta = V zetabar V^T (exactly symmetric); the particle form then
- * subtracts its volume means.  The results agree with the two separate calls
- * to rounding (per multipole: an entry's rounding follows the largest entry
- * of its multipole). */
+ * mp3_zeta and then mp3_zeta_backward.  In the nodal and particle forms zeta
+ * is contracted over the fields of the cotangent's eigenbasis (see
+ * mp3_zeta_backward) and rotated back, zeta = V zetabar V^T (exactly
+ * symmetric); the particle form then subtracts its volume means.  Their
+ * results agree with the two separate calls to rounding (per multipole: an
+ * entry's rounding follows the largest entry of its multipole). */
 int mp3_zeta_value_and_grad(mp3_plan_t plan, const void* delta, const double* dzeta,
                             double* zeta, void* ddelta, const float* pos, const float* w,
                             const int64_t* np_off, void* dw, void* workspace,

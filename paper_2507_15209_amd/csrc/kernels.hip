@@ -1854,6 +1854,48 @@ __global__ void __launch_bounds__(256) k_rotate_zeta(double* zeta, const double*
   }
 }
 
+// f[mock][cell][k] = sum_b V[b][k] f[mock][cell][b] in place: stored fields of the plan's own tables turned into
+// the cotangent's eigenbasis (V = evec[mock], of a pair item's imaginary parts evec2[mock]).  The grid-Gamma one
+// sweep contracts the fields before this, so that its value has the error of each entry's own bins and not of the
+// multipole's largest (64^3, smoothed float32 field, l = 4: the smallest entry 9e-2 off when summed over rotated
+// fields and turned back, 9e-6 so).  A pass over the fields, bound by their traffic and by one LDS read of V and
+// one of the cell per product: 128^3, 15 bins float32 0.17 ms a launch (3.0 TB/s), 3 % of that step.
+template <typename T>
+__global__ void __launch_bounds__(256) k_rotate_fields(c2<T>* f, const double* evec, const double* evec2, int nbins,
+                                                       long long cells, int chunk) {
+  extern __shared__ __align__(16) char smem[];
+  const int nb2 = nbins * nbins, tid = threadIdx.x;
+  c2<T>* a = reinterpret_cast<c2<T>*>(smem);   // [chunk][nbins]
+  T* v = reinterpret_cast<T*>(a + chunk * nbins);
+  T* v2 = v + nb2;
+  const long long mock = blockIdx.y;
+  c2<T>* fm = f + mock * cells * nbins;
+  for (int t = tid; t < nb2; t += blockDim.x) {
+    v[t] = (T)evec[mock * nb2 + t];
+    v2[t] = (T)evec2[mock * nb2 + t];
+  }
+  // the thread's first (cell, bin) of a chunk and its step, without a division per element
+  const int c0 = tid / nbins, k0 = tid % nbins, dc = blockDim.x / nbins, dk = blockDim.x % nbins;
+  for (long long p = (long long)blockIdx.x * chunk; p < cells; p += (long long)gridDim.x * chunk) {
+    const int count = (int)(cells - p < chunk ? cells - p : chunk) * nbins;
+    c2<T>* g = fm + p * nbins;
+    __syncthreads();   // the chunk before is written
+    for (int t = tid; t < count; t += blockDim.x) a[t] = g[t];
+    __syncthreads();
+    int c = c0, k = k0;
+    for (int t = tid; t < count; t += blockDim.x) {
+      const c2<T>* row = a + c * nbins;
+      c2<T> s = mk<T>(0, 0);
+      for (int b = 0; b < nbins; ++b) {
+        s.x += v[b * nbins + k] * row[b].x;
+        s.y += v2[b * nbins + k] * row[b].y;
+      }
+      g[t] = s;
+      next_element(c, k, dc, dk, nbins);
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // last adjoint pass: y-transform of every adjoint source c_b, summed over the
 // bins with the radial window, times the angular factor (common to the bins),
@@ -2600,6 +2642,26 @@ hipError_t launch_rotate_jtab(int prec, const void* jtab, void* jrot, const doub
   if (nbins < 1 || nbins > kEigMaxBins || nbp < nbins) return hipErrorInvalidValue;
   return prec ? rotate_jtab_t<double>(jtab, jrot, evec, nq2, nbins, nbp, lmax, batch, st)
               : rotate_jtab_t<float>(jtab, jrot, evec, nq2, nbins, nbp, lmax, batch, st);
+}
+
+template <typename T>
+hipError_t rotate_fields_t(void* fields, const double* evec, const double* evec2, int nbins, long long cells, int batch,
+                           hipStream_t st) {
+  // 32 KB of cells at a time (at least one thread per element), with both tables at most 96 KB of LDS
+  const int chunk = (int)(32768 / (nbins * sizeof(CT<T>)));
+  const size_t lds = (size_t)chunk * nbins * sizeof(CT<T>) + (size_t)2 * nbins * nbins * sizeof(T);
+  hipError_t e = allow_lds(k_rotate_fields<T>, lds);
+  if (e != hipSuccess) return e;
+  const long long blocks = (cells + chunk - 1) / chunk;
+  const dim3 gs((unsigned)(blocks < 4096 ? blocks : 4096), batch);
+  k_rotate_fields<T><<<gs, 256, lds, st>>>(static_cast<CT<T>*>(fields), evec, evec2 ? evec2 : evec, nbins, cells, chunk);
+  return hipGetLastError();
+}
+
+hipError_t launch_rotate_fields(int prec, void* fields, const double* evec, const double* evec2, int nbins,
+                                long long cells, int batch, hipStream_t st) {
+  return prec ? rotate_fields_t<double>(fields, evec, evec2, nbins, cells, batch, st)
+              : rotate_fields_t<float>(fields, evec, evec2, nbins, cells, batch, st);
 }
 
 hipError_t launch_rotate_zeta(double* zeta, const double* evec, int nbins, int lmax, int batch, hipStream_t st) {

@@ -175,6 +175,10 @@ hipError_t launch_rotate_jtab(int prec, const void* jtab, void* jrot, const doub
                               int lmax, int batch, hipStream_t st);
 // zeta[batch][l] = evec zeta evec^T for every l (the value of the rotated fields back to the bins)
 hipError_t launch_rotate_zeta(double* zeta, const double* evec, int nbins, int lmax, int batch, hipStream_t st);
+// bin-interleaved fields [batch][cells][nbins] into the eigenbasis evec [batch][nbins][nbins], in place
+// (evec2: NULL, or for a pair item the basis of its second multipole, the imaginary parts)
+hipError_t launch_rotate_fields(int prec, void* fields, const double* evec, const double* evec2, int nbins,
+                                long long cells, int batch, hipStream_t st);
 // partials of a group of items [item][batch][nwg][nb2] into zeta at each item's l (times scale and the item's m weight)
 hipError_t launch_reduce_items(const double* partials, int nwg, int nb2, double* zeta, int lmax, double scale,
                                const ItemRec* items, int item0, int nitems, int batch, hipStream_t st);

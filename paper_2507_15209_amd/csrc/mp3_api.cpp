@@ -377,6 +377,11 @@ void* lam_d_at(const mp3_plan_s* p, void* ws, const Layout& L, int l) {
   return at(ws, L.lam + (size_t)l * p->batch * p->nbins * p->elt);
 }
 
+// its eigenvectors: [batch][nbins][nbins] float64, columns
+const double* evec_at(const mp3_plan_s* p, void* ws, const Layout& L, int l) {
+  return reinterpret_cast<const double*>(at(ws, L.evec)) + (size_t)l * p->batch * p->nbins * p->nbins;
+}
+
 // The gradients run in the eigenbasis of each symmetrised cotangent
 // lam_s = V diag(d) V^T (per l and mock): the eigenvalues d into the lambda
 // slot, V into L.evec, and the radial tables rotated by V into L.jrot.
@@ -1239,7 +1244,7 @@ int value_and_grad_particle(mp3_plan_t p, const void* delta, const double* dzeta
 // replaced by the trilinear form (k_band_adjoint adds c_b and the direct term
 // per (l, m), from the fields in the cotangent's eigenbasis); the same adjoint
 // transforms and deposit chain rule follow.  zeta != NULL: one sweep, the
-// stored fields are also contracted and the value is turned back to the bins.
+// plain fields are contracted as in zeta_gamma, then turned into the eigenbasis.
 int backward_gamma(mp3_plan_t p, const void* delta, const double* dzeta, void* ddelta, const float* pos,
                    const float* w, const int64_t* np_off, void* dw, void* ws, size_t wsb, void* stream,
                    double* zeta = nullptr) {
@@ -1271,7 +1276,7 @@ int backward_gamma(mp3_plan_t p, const void* delta, const double* dzeta, void* d
   const bool rotated = rotated_tables(p);
   for (int item = first_item(p, L); group_size(p, L, item) > 0; ++item) {
     const mp3::ItemRec& it = p->items[item];
-    if (int s = fields_xy(p, ws, L, F, item, 1, st, rotated)) return s;
+    if (int s = fields_xy(p, ws, L, F, item, 1, st, rotated && !zeta)) return s;
     mp3::ZpassArgs z{};
     z.fields = F;
     z.tw = p->tw;
@@ -1280,8 +1285,16 @@ int backward_gamma(mp3_plan_t p, const void* delta, const double* dzeta, void* d
     z.ppw = L.ppw;
     z.batch = p->batch;
     MP3_HIP(timed(p, MP3_PASS_Z_STORE, st, [&] { return mp3::launch_zpass_store(p->n, p->prec, z, Fi, st); }), "z pass (store)");
-    if (zeta)
+    if (zeta) {
       if (int s = gamma_contract_all(p, Fi, prim, partials, gwg, zeta, it, kFourPi / (double)n3, st)) return s;
+      if (rotated)
+        MP3_HIP(timed(p, MP3_PASS_GAMMA, st, [&] {
+                  return mp3::launch_rotate_fields(p->prec, Fi, evec_at(p, ws, L, it.l),
+                                                   it.l2 >= 0 ? evec_at(p, ws, L, it.l2) : nullptr, p->nbins, n3,
+                                                   p->batch, st);
+                }),
+                "fields into the eigenbasis");
+    }
     // bin-interleaved sources into F (free once stored), their transform into Fi
     MP3_HIP(mp3::launch_fill(p->prec, F, 2 * n3 * p->batch * p->nbins, 0.0, st), "zero sources");
     MP3_HIP(timed(p, MP3_PASS_GAMMA, st, [&] {
@@ -1297,11 +1310,6 @@ int backward_gamma(mp3_plan_t p, const void* delta, const double* dzeta, void* d
     mp3::FilterArgs a = filter_args(p, ws, L, Fi, G, item, 1, rotated);
     MP3_HIP(timed(p, MP3_PASS_ADJOINT, st, [&] { return mp3::launch_adjoint_y(p->n, p->prec, a, st); }), "adjoint window pass");
   }
-  // the value was summed over the rotated fields: back to the bins
-  if (zeta && rotated)
-    MP3_HIP(mp3::launch_rotate_zeta(zeta, reinterpret_cast<const double*>(at(ws, L.evec)), p->nbins, p->lmax, p->batch,
-                                    st),
-            "zeta out of the eigenbasis");
   MP3_HIP(timed(p, MP3_PASS_DFT, st, [&] { return mp3::launch_fft3d(p->n, p->prec, -1, false, G, G, p->batch, p->tw, st); }), "adjoint final FFT");
   if (int s = filter_direct(p, direct, ws, L, st)) return s;
   MP3_HIP(mp3::launch_grad_combine(p->prec, direct, G, ddelta, n3 * p->batch, kFourPi / (double)n3, st), "combine");

@@ -1,0 +1,38 @@
+"""GPU: what the value and the gradient of one sweep owe to the cotangent."""
+import numpy as np
+import pytest
+
+from mockgen import random_field
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+# gradients of two orders of the same float operations (bars as in test_gpu_bins.py)
+TOL = {"f64": 1.1e-11, "f32": 1.9e-5}
+
+
+def _fields(n, nb, lmax, prec, seed):
+    """Two mocks and two cotangents on the GPU."""
+    rd = torch.float64 if prec == "f64" else torch.float32
+    d = np.stack([random_field(n, seed), random_field(n, seed + 1)])
+    lam = np.random.default_rng(seed + 2).standard_normal((2, lmax + 1, nb, nb))
+    return torch.as_tensor(d, dtype=rd, device="cuda"), torch.as_tensor(lam, device="cuda")
+
+
+@pytest.mark.parametrize("basis,nb", [("b3", 1), ("b3", 2), ("b3", 5), ("b3", 20), ("b3", 33), ("b3", 64), ("d4", 6)])
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+def test_gamma_value_does_not_depend_on_the_cotangent(prec, basis, nb):
+    """The grid-Gamma one sweep contracts the plain fields: zeta is mp3_zeta's, bit for bit, and the fields
+    turned into the eigenbasis afterwards give mp3_zeta_backward's gradient."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2507_15209_amd as mp3
+    print("[case] gamma value", prec, basis, nb, flush=True)
+    n, lmax = 16, 2
+    d, lam = _fields(n, nb, lmax, prec, 810)
+    plan = mp3.Plan(n, 160.0, lmax, np.linspace(5.0, 60.0, nb + 1), precision=prec, summation="gamma", basis=basis,
+                    batch=2)
+    z, g, _ = plan.zeta_value_and_grad(d, lam)
+    assert torch.equal(z, plan.zeta(d))
+    g2 = plan.zeta_backward(d, lam)[0]
+    assert (g - g2).abs().max() <= 2 * TOL[prec] * g2.abs().max()
