@@ -222,7 +222,9 @@ int mp3_zeta(mp3_plan_t plan, const void* delta, const float* pos, const float* 
  * cotangent (dzeta_l + dzeta_l^T) / 2 = V diag(d) V^T, decomposed per (l,
  * mock) on the device in float64: their fields come from the radial window
  * rotated by V, so the adjoint sources are diagonal in the bins; the
- * gradient is the same to rounding.
+ * gradient is the same to rounding.  A NaN or an infinity in a mock's dzeta
+ * makes its gradient NaN (its zeta in mp3_zeta_value_and_grad stays that of
+ * finite fields); other mocks are not touched.
  * The fields are recomputed per (l, m); nothing is kept from mp3_zeta.
  *   ddelta = dJ/ddelta                                          (device real [batch][N^3])
  *            For the particle form this is the dependence through the

@@ -1682,9 +1682,10 @@ inline size_t lam_eig_lds(int nbins) {
 // One workgroup per (l, mock): cyclic Jacobi in float64 with the round-robin
 // pair order (each round rotates nbins / 2 disjoint index pairs at once, which
 // commute), until the off-diagonal norm is below 1e-14 of the matrix norm or
-// after kEigSweeps sweeps.  Writes the eigenvalues d [l][mock][nbins] at the
-// plan precision and the eigenvectors V [l][mock][nbins][nbins] (columns) in
-// float64.
+// after kEigSweeps sweeps.  Writes the
+// eigenvalues d [l][mock][nbins] at the plan precision and the eigenvectors
+// V [l][mock][nbins][nbins] (columns) in float64.  A matrix with a NaN or an infinity
+// has no eigenbasis: V = 1 and every d NaN, so that the gradient says so and the fields stay finite.
 constexpr int kEigSweeps = 40;
 
 template <typename T>
@@ -1702,13 +1703,22 @@ __global__ void __launch_bounds__(256) k_lam_eig(const double* dzeta, T* lam_d, 
   int* pq = pp + half;
   const int tid = threadIdx.x, nt = blockDim.x;
   const double* dz = dzeta + ((long long)j * (lmax + 1) + l) * nb * nb;
+  const long long lj = (long long)l * batch + j;
+  double top = 0.0;   // the largest |entry|, infinity where one is not finite
   for (int t = tid; t < nb * nb; t += nt) {
     const int b = t / nb, c = t % nb;
-    A[b * ld + c] = 0.5 * (dz[b * nb + c] + dz[c * nb + b]);
+    const double a = 0.5 * dz[b * nb + c] + 0.5 * dz[c * nb + b];
+    A[b * ld + c] = a;
     V[b * ld + c] = b == c ? 1.0 : 0.0;
+    top = fabs(a) <= 1.7976931348623157e308 ? fmax(top, fabs(a)) : HUGE_VAL;
   }
+  for (int o = warpSize / 2; o > 0; o >>= 1) top = fmax(top, __shfl_down(top, o));
+  if (tid % warpSize == 0) red[tid / warpSize] = top;
   __syncthreads();
-  for (int sweep = 0; sweep < kEigSweeps; ++sweep) {
+  for (int w = 0; w < (nt + warpSize - 1) / warpSize; ++w) top = w == 0 ? red[0] : fmax(top, red[w]);
+  const bool finite = top <= 1.7976931348623157e308;
+  __syncthreads();   // every thread has read red before it is written again
+  for (int sweep = 0; finite && sweep < kEigSweeps; ++sweep) {
     double off = 0.0, tot = 0.0;
     for (int t = tid; t < nb * nb; t += nt) {
       const int b = t / nb, c = t % nb;
@@ -1790,8 +1800,7 @@ __global__ void __launch_bounds__(256) k_lam_eig(const double* dzeta, T* lam_d, 
       __syncthreads();
     }
   }
-  const long long lj = (long long)l * batch + j;
-  for (int b = tid; b < nb; b += nt) lam_d[lj * nb + b] = (T)A[b * ld + b];
+  for (int b = tid; b < nb; b += nt) lam_d[lj * nb + b] = finite ? (T)A[b * ld + b] : (T)NAN;
   for (int t = tid; t < nb * nb; t += nt) evec[lj * nb * nb + t] = V[(t / nb) * ld + t % nb];
 }
 

@@ -36,3 +36,25 @@ def test_gamma_value_does_not_depend_on_the_cotangent(prec, basis, nb):
     assert torch.equal(z, plan.zeta(d))
     g2 = plan.zeta_backward(d, lam)[0]
     assert (g - g2).abs().max() <= 2 * TOL[prec] * g2.abs().max()
+
+
+@pytest.mark.parametrize("form", ["nodal", "gamma"])
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+def test_non_finite_cotangent(prec, value, form):
+    """One entry off the diagonal that is not finite: no finite gradient of its mock, the other mock's as without
+    it, and the value as ever."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2507_15209_amd as mp3
+    print("[case] non-finite cotangent", prec, value, form, flush=True)
+    n, nb, lmax = 16, 5, 2
+    d, lam = _fields(n, nb, lmax, prec, 830)
+    plan = mp3.Plan(n, 160.0, lmax, np.linspace(5.0, 60.0, nb + 1), precision=prec, summation=form, batch=2)
+    ref, zref = plan.zeta_backward(d, lam)[0], plan.zeta(d)
+    lam[0, 1, 3, 1] = value
+    z, g, _ = plan.zeta_value_and_grad(d, lam)
+    for a in (g, plan.zeta_backward(d, lam)[0]):
+        assert not torch.isfinite(a[0]).any()
+        assert (a[1] - ref[1]).abs().max() <= 2 * TOL[prec] * ref[1].abs().max()
+    assert (z - zref).abs().max() <= TOL[prec] * zref.abs().max()
