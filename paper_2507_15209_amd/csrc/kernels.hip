@@ -1682,7 +1682,8 @@ inline size_t lam_eig_lds(int nbins) {
 // One workgroup per (l, mock): cyclic Jacobi in float64 with the round-robin
 // pair order (each round rotates nbins / 2 disjoint index pairs at once, which
 // commute), until the off-diagonal norm is below 1e-14 of the matrix norm or
-// after kEigSweeps sweeps.  Writes the
+// after kEigSweeps sweeps, on the matrix times a power of two that brings its largest
+// entry to [1/2, 1) (the squares of the norms neither overflow nor vanish).  Writes the
 // eigenvalues d [l][mock][nbins] at the plan precision and the eigenvectors
 // V [l][mock][nbins][nbins] (columns) in float64.  A matrix with a NaN or an infinity
 // has no eigenbasis: V = 1 and every d NaN, so that the gradient says so and the fields stay finite.
@@ -1717,7 +1718,10 @@ __global__ void __launch_bounds__(256) k_lam_eig(const double* dzeta, T* lam_d, 
   __syncthreads();
   for (int w = 0; w < (nt + warpSize - 1) / warpSize; ++w) top = w == 0 ? red[0] : fmax(top, red[w]);
   const bool finite = top <= 1.7976931348623157e308;
-  __syncthreads();   // every thread has read red before it is written again
+  int e = 0;
+  if (finite) frexp(top, &e);
+  for (int t = tid; t < nb * nb; t += nt) A[(t / nb) * ld + t % nb] = ldexp(A[(t / nb) * ld + t % nb], -e);
+  __syncthreads();
   for (int sweep = 0; finite && sweep < kEigSweeps; ++sweep) {
     double off = 0.0, tot = 0.0;
     for (int t = tid; t < nb * nb; t += nt) {
@@ -1800,7 +1804,7 @@ __global__ void __launch_bounds__(256) k_lam_eig(const double* dzeta, T* lam_d, 
       __syncthreads();
     }
   }
-  for (int b = tid; b < nb; b += nt) lam_d[lj * nb + b] = finite ? (T)A[b * ld + b] : (T)NAN;
+  for (int b = tid; b < nb; b += nt) lam_d[lj * nb + b] = finite ? (T)ldexp(A[b * ld + b], e) : (T)NAN;
   for (int t = tid; t < nb * nb; t += nt) evec[lj * nb * nb + t] = V[(t / nb) * ld + t % nb];
 }
 

@@ -39,6 +39,24 @@ def test_gamma_value_does_not_depend_on_the_cotangent(prec, basis, nb):
 
 
 @pytest.mark.parametrize("form", ["nodal", "gamma"])
+@pytest.mark.parametrize("exponent", [-600, 600])
+def test_gradient_is_linear_in_the_cotangent(form, exponent):
+    """A cotangent times 2^+-600 (its entries' squares leave float64) gives the gradient times the same."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2507_15209_amd as mp3
+    print("[case] scaled cotangent", form, exponent, flush=True)
+    n, nb, lmax = 16, 5, 2
+    d, lam = _fields(n, nb, lmax, "f64", 820)
+    plan = mp3.Plan(n, 160.0, lmax, np.linspace(5.0, 60.0, nb + 1), precision="f64", summation=form, batch=2)
+    ref, zref = plan.zeta_backward(d, lam)[0], plan.zeta(d)
+    z, g, _ = plan.zeta_value_and_grad(d, lam * 2.0 ** exponent)
+    for a in (g, plan.zeta_backward(d, lam * 2.0 ** exponent)[0]):
+        assert (a * 2.0 ** -exponent - ref).abs().max() <= 2 * TOL["f64"] * ref.abs().max()
+    assert (z - zref).abs().max() <= TOL["f64"] * zref.abs().max()
+
+
+@pytest.mark.parametrize("form", ["nodal", "gamma"])
 @pytest.mark.parametrize("value", [float("nan"), float("inf")])
 @pytest.mark.parametrize("prec", ["f64", "f32"])
 def test_non_finite_cotangent(prec, value, form):
