@@ -1319,6 +1319,7 @@ k_gather_contract(const c2<T>* fields, const int* tcell, const T* twt,
       lam[t] = lam_d[mock * nbins + t];
       lam2[t] = lam_d2[mock * nbins + t];
     }
+    __syncthreads();   // a workgroup without particles goes straight to the reduction, whose scratch lies over lam
   }
   Contractor<T, MF, SPLIT, QUAD, B, APART> ctr;
   ctr.init(nbins);

@@ -54,3 +54,31 @@ def test_scatter_stages(prec, kind, nb):
     for g, dw in (plan.zeta_backward(delta, lt, pt, wt), plan.zeta_value_and_grad(delta, lt, pt, wt)[1:]):
         assert_grad_close(g.cpu().numpy()[0], gref, TOL[prec], "dJ/ddelta")
         assert_grad_close(dw.cpu().numpy(), wref, TOL[prec], "dJ/dw")
+
+
+@pytest.mark.parametrize("nb", [3, 9, 20])
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+def test_workgroups_without_particles(prec, nb):
+    """Mocks of 20000, 90 and 1 particles in one call: the gather's twenty workgroups per mock leave two and
+    nineteen without a particle in the small ones.  Each mock against a call of its own."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2507_15209_amd as mp3
+    print("[case] workgroups without particles", prec, nb, flush=True)
+    rng = np.random.default_rng(73)
+    off = np.cumsum([0, 20000, 90, 1])
+    pos = torch.as_tensor((rng.random((off[-1], 3)) * 159.9).astype(np.float32), device="cuda")
+    w = torch.as_tensor(rng.uniform(0.5, 1.5, off[-1]).astype(np.float32), device="cuda")
+    lam = torch.as_tensor(rng.standard_normal((3, LMAX + 1, nb, nb)), device="cuda")
+    edges = np.linspace(15.0, 56.0, nb + 1)
+    plan = mp3.Plan(N, BOX, LMAX, edges, precision=prec, summation="particle", batch=3)
+    z, g, dw = plan.zeta_value_and_grad(plan.deposit(pos, w, off), lam, pos, w, off)
+    one = mp3.Plan(N, BOX, LMAX, edges, precision=prec, summation="particle")
+    for j in range(3):
+        p, u = pos[off[j]:off[j + 1]].contiguous(), w[off[j]:off[j + 1]].contiguous()
+        z1, g1, dw1 = one.zeta_value_and_grad(one.deposit(p, u), lam[j:j + 1].contiguous(), p, u)
+        pairs = [(z[j], z1[0]), (g[j], g1[0])]
+        if j < 2:   # one particle's weight does not change its contrast: dJ/dw is zero, a difference of large terms
+            pairs.append((dw[off[j]:off[j + 1]], dw1))
+        for got, ref in pairs:
+            assert (got - ref).abs().max() <= TOL[prec] * ref.abs().max()
