@@ -386,8 +386,9 @@ int mp3_profile_read(mp3_plan_t plan, int pass, double* total_ms, int64_t* launc
  * and caches the winners (the package ships those of its benchmark
  * workloads). */
 enum mp3_tune_knob {
-  MP3_TUNE_ZPASS_WGS = 0,     /* workgroups of the z passes per call, split over the batch;
-                                 64 .. 65536, default 4096                                       */
+  MP3_TUNE_ZPASS_WGS = 0,     /* workgroups of the z passes per (l, m), split over the batch; in the
+                                 nodal form a launch of several (l, m) has this many, or 4096 if that
+                                 is more, over all of them; 64 .. 65536, default 4096              */
   MP3_TUNE_CONTRACT_WGS = 1,  /* workgroups of the particle gather and the grid-Gamma
                                  contraction per call; 64 .. 65536, default 4096                 */
   MP3_TUNE_FFT_X_PLAN = 2,    /* radix plan of the strided x pass: 0 = largest radix first

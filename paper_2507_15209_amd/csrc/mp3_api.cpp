@@ -431,6 +431,9 @@ mp3::FilterArgs filter_args(const mp3_plan_s* p, void* ws, const Layout& L, cons
   return a;
 }
 
+// work units of a grouped z pass that keep the chip busy: two for each workgroup of its persistent launch
+constexpr int kZpassUnits = 4096;
+
 // arguments of the adjoint z passes over a group of items
 mp3::ZpassArgs adjoint_zargs(const mp3_plan_s* p, void* ws, const Layout& L, void* F, const void* prim,
                              const double* dzeta, void* direct, int item0, int nitems) {
@@ -443,8 +446,9 @@ mp3::ZpassArgs adjoint_zargs(const mp3_plan_s* p, void* ws, const Layout& L, voi
   z.tw = p->tw;
   z.nbins = p->nbins;
   // the launch's workgroups over all of its items: several pencils each rather than a partial sum
-  // (and its reduction) per pencil on small grids
-  const int per = p->tune[MP3_TUNE_ZPASS_WGS] / (p->batch * nitems);
+  // (and its reduction) per pencil on small grids, but never fewer than keep the chip busy, whatever
+  // the knob leaves to one item (64^3, 45 items, 10 bins, knob 64: 19.0 ms without the floor, 2.3 ms with it)
+  const int per = std::max(p->tune[MP3_TUNE_ZPASS_WGS], kZpassUnits) / (p->batch * nitems);
   // pair items leave two partial sums per workgroup
   const int most = p->items[item0].l2 >= 0 ? std::max(1, L.nwg / 2) : L.nwg;
   const int pencils = p->n * p->n, nwg = per < 1 ? 1 : per < most ? per : most;

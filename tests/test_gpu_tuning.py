@@ -239,3 +239,28 @@ def test_gamma_adjoint_kernels_agree(mp3, prec, nb):
     assert np.abs(out[0][1] - out[1][1]).max() <= agree * np.abs(out[1][1]).max()
     op = E.Plan(n, box, lmax, edges)
     assert_grad_close(out[0][1], A.zeta_gamma_grad(op, delta, lam), 1e-10 if prec == "f64" else 1e-4, "dJ/ddelta")
+
+
+def test_few_zpass_workgroups_keep_the_chip_busy(mp3):
+    """The smallest zpass_wgs on a grid whose 45 items share a launch: every item keeps its own 64 workgroups,
+    so the step takes at most four times the default's (1.3 expected; 8.5 where the launch has 64 in all)."""
+    _say("few z-pass workgroups")
+    n, lmax, nb = 64, 8, 10
+    d = _dev(random_field(n, 281)[None], torch.float32)
+    lam = _dev(np.random.default_rng(282).standard_normal((1, lmax + 1, nb, nb)), torch.float64)
+    plan = mp3.Plan(n, 640.0, lmax, np.linspace(30.0, 200.0, nb + 1), precision="f32")
+
+    def ms(wgs):
+        plan.tune_set("zpass_wgs", wgs)
+        plan.zeta_value_and_grad(d, lam)
+        best = float("inf")
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            plan.zeta_value_and_grad(d, lam)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+
+    assert ms(64) <= 4.0 * ms(4096)
