@@ -690,10 +690,19 @@ int band_segments(int n, long long tiles, int batch) {
   return s;
 }
 
+// rows of cells of a forward workgroup (TY), by registers: 16 waves (TY = 4, 128 registers) hold the float32
+// B-spline with up to 16 bins; two bin halves spill there (256^3, 20 bins: 19.2 ms against 17.8 ms
+// with 8 waves), as do float64 and the five points of Daubechies-4
+int contract_rows(int prec, int q, int nl) {
+  if (q == 4) return !prec && nl <= 16 ? 4 : 2;
+  return prec && nl > 16 ? 1 : 2;
+}
+
 template <typename T, int Q, int TP, int H, int TY, int NH>
 hipError_t contract_t(const void* fields, const void* prim, int n, const BinPair& bp, const BandRule& rule,
                       double* partials, int nwg, bool pair, int batch, hipStream_t st) {
   const int nl = bp.na + bp.nc;
+  if (contract_rows(sizeof(T) == 8, Q, nl) != TY) return hipErrorInvalidValue;
   const size_t lds = ContractLds<T, Q, TP, TY, NH>(nl).total;
   auto kern = k_band_contract<T, Q, TP, H, TY, NH>;
   hipError_t e = allow_band_lds(kern, lds);
@@ -725,14 +734,16 @@ hipError_t adjoint_t(const void* fields, const void* prim, const void* lam_d, co
 
 }  // namespace
 
+int band_contract_tasks(int prec, int n, int nl, const BandRule& rule, int batch) {
+  const int tiles = (n / contract_rows(prec, rule.q, nl)) * (n / 4);
+  return tiles * band_segments(n, tiles, batch);
+}
+
 hipError_t launch_band_contract(int prec, const void* fields, const void* prim, int n, const BinPair& bp,
                                 const BandRule& rule, double* partials, int nwg, bool pair, int batch, hipStream_t st) {
   const int nl = bp.na + bp.nc;
   if (nl > kBandBins || n % 4) return hipErrorInvalidValue;
   const bool two = nl > 16;
-  // rows of cells per workgroup by registers: 16 waves (TY = 4, 128 registers) hold the float32
-  // B-spline with up to 16 bins; two bin halves spill there (256^3, 20 bins: 19.2 ms against 17.8 ms
-  // with 8 waves), as do float64 and the five points of Daubechies-4
   if (rule.q == 4) {
     if (prec) {
       return two ? contract_t<double, 4, 4, 3, 2, 2>(fields, prim, n, bp, rule, partials, nwg, pair, batch, st)

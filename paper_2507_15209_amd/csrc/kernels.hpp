@@ -113,6 +113,8 @@ struct BandRule {
   double f[5][5], p[5][5], g[4][7];
 };
 constexpr int kBandBins = 32;   // bins of one contraction launch (more: pairs of chunks)
+// tasks of a contraction launch of nl bins, each a whole workgroup's (more workgroups would idle)
+int band_contract_tasks(int prec, int n, int nl, const BandRule& rule, int batch);
 // forward partials [batch][nwg][nl^2] over the pair's local bins, fields bin-interleaved (band.hip)
 hipError_t launch_band_contract(int prec, const void* fields, const void* prim, int n, const BinPair& bp,
                                 const BandRule& rule, double* partials, int nwg, bool pair, int batch, hipStream_t st);

@@ -839,12 +839,19 @@ std::vector<GammaPass> gamma_passes(const mp3_plan_s* p) {
   return out;
 }
 
+// workgroups per mock of a grid-Gamma contraction of nl bins: the partial sums' room over the parts that each
+// leaves, and at most one per task of the launch
+int gamma_wgs(const mp3_plan_s* p, int nl, int parts) {
+  const int tasks = mp3::band_contract_tasks(p->prec, p->n, nl, p->band, p->batch);
+  return std::max(1, std::min((int)contract_wgs(p) / parts, tasks));
+}
+
 // the contraction of the stored bin-interleaved fields of one item, all passes, into zeta
-int gamma_contract_all(const mp3_plan_s* p, const void* Fi, const void* prim, double* partials, int gwg, double* zeta,
+int gamma_contract_all(const mp3_plan_s* p, const void* Fi, const void* prim, double* partials, double* zeta,
                        const mp3::ItemRec& it, double scale, hipStream_t st) {
   const int parts = it.l2 >= 0 ? 2 : 1;
-  gwg = std::max(1, gwg / parts);
   for (const GammaPass& g : gamma_passes(p)) {
+    const int gwg = gamma_wgs(p, g.bp.na + g.bp.nc, parts);
     MP3_HIP(timed(p, MP3_PASS_GAMMA, st, [&] {
               return mp3::launch_band_contract(p->prec, Fi, prim, p->n, g.bp, p->band, partials, gwg, parts == 2,
                                                p->batch, st);
@@ -943,13 +950,6 @@ int zeta_particle(mp3_plan_t p, const float* pos, const float* w, const int64_t*
   return MP3_OK;
 }
 
-// workgroups per mock of the grid-Gamma contraction: at most one per column of cells
-int gamma_wgs(const mp3_plan_s* p) {
-  const long long cols = (long long)(p->n / 2) * (p->n / 4) * 8;
-  const long long g = (long long)contract_wgs(p);
-  return (int)(g < cols ? g : cols);
-}
-
 // grid summation with connection coefficients:
 // zeta_l = (4 pi / N^3) int delta_B sum_m atilde_b1 conj(atilde_b2) d^3u
 int zeta_gamma(mp3_plan_t p, const void* delta, double* zeta, void* ws, const Layout& L, hipStream_t st) {
@@ -957,7 +957,6 @@ int zeta_gamma(mp3_plan_t p, const void* delta, double* zeta, void* ws, const La
   void* F = at(ws, L.fields);
   void* Fi = at(ws, L.fields_i);
   double* partials = reinterpret_cast<double*>(at(ws, L.partials));
-  const int gwg = gamma_wgs(p);
   for (int item = first_item(p, L); group_size(p, L, item) > 0; ++item) {
     if (int s = fields_xy(p, ws, L, F, item, 1, st)) return s;
     mp3::ZpassArgs z{};
@@ -968,7 +967,7 @@ int zeta_gamma(mp3_plan_t p, const void* delta, double* zeta, void* ws, const La
     z.ppw = L.ppw;
     z.batch = p->batch;
     MP3_HIP(timed(p, MP3_PASS_Z_STORE, st, [&] { return mp3::launch_zpass_store(p->n, p->prec, z, Fi, st); }), "z pass (store)");
-    if (int s = gamma_contract_all(p, Fi, delta, partials, gwg, zeta, p->items[item], kFourPi / n3, st)) return s;
+    if (int s = gamma_contract_all(p, Fi, delta, partials, zeta, p->items[item], kFourPi / n3, st)) return s;
   }
   return MP3_OK;
 }
@@ -1276,7 +1275,6 @@ int backward_gamma(mp3_plan_t p, const void* delta, const double* dzeta, void* d
   if (zeta) MP3_HIP(mp3::launch_fill_f64(zeta, (long long)p->batch * (p->lmax + 1) * nb2, 0.0, st), "zero zeta");
   MP3_HIP(mp3::launch_fill(p->prec, G, 2 * n3 * p->batch, 0.0, st), "zero G");
   MP3_HIP(mp3::launch_fill(p->prec, direct, n3 * p->batch, 0.0, st), "zero direct");
-  const int gwg = gamma_wgs(p);
   const bool rotated = rotated_tables(p);
   for (int item = first_item(p, L); group_size(p, L, item) > 0; ++item) {
     const mp3::ItemRec& it = p->items[item];
@@ -1290,7 +1288,7 @@ int backward_gamma(mp3_plan_t p, const void* delta, const double* dzeta, void* d
     z.batch = p->batch;
     MP3_HIP(timed(p, MP3_PASS_Z_STORE, st, [&] { return mp3::launch_zpass_store(p->n, p->prec, z, Fi, st); }), "z pass (store)");
     if (zeta) {
-      if (int s = gamma_contract_all(p, Fi, prim, partials, gwg, zeta, it, kFourPi / (double)n3, st)) return s;
+      if (int s = gamma_contract_all(p, Fi, prim, partials, zeta, it, kFourPi / (double)n3, st)) return s;
       if (rotated)
         MP3_HIP(timed(p, MP3_PASS_GAMMA, st, [&] {
                   return mp3::launch_rotate_fields(p->prec, Fi, evec_at(p, ws, L, it.l),
