@@ -28,7 +28,7 @@ CANDIDATES = {
     "contract_wgs": (1024, 2048, 4096, 8192, 16384),
     "fused_waves": (0, 4, 8),
     "item_group": (0, 1, 2, 4),
-    "gamma_adjoint": (0, 1),
+    "gamma_adjoint": (0,),   # without effect, never descended: here so that every knob has its candidates
 }
 
 

@@ -76,3 +76,27 @@ def test_non_finite_cotangent(prec, value, form):
         assert not torch.isfinite(a[0]).any()
         assert (a[1] - ref[1]).abs().max() <= 2 * TOL[prec] * ref[1].abs().max()
     assert (z - zref).abs().max() <= TOL[prec] * zref.abs().max()
+
+
+@pytest.mark.parametrize("basis", ["b3", "d4"])
+@pytest.mark.parametrize("prec,nb", [("f64", 3), ("f64", 20), ("f32", 3), ("f32", 20), ("bf16x3", 20)])
+def test_gamma_task_loop(basis, prec, nb):
+    """The grid-Gamma contraction with several tasks to a workgroup (contract_wgs 64: 8 or 4 tasks each at 32^3)
+    against one task each, and the gradient beside it, which no knob cuts."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    if prec == "bf16x3" and basis == "d4":
+        pytest.skip("not a plan")
+    import paper_2507_15209_amd as mp3
+    print("[case] gamma task loop", basis, prec, nb, flush=True)
+    n, lmax = 32, 1
+    tol = TOL["f64" if prec == "f64" else "f32"]
+    d, lam = _fields(n, nb, lmax, prec, 840)
+    out = []
+    for wgs in (64, 4096):
+        plan = mp3.Plan(n, 320.0, lmax, np.linspace(5.0, 110.0, nb + 1), precision=prec, summation="gamma",
+                        basis=basis, batch=2)
+        plan.tune_set("contract_wgs", wgs)
+        out.append(plan.zeta_value_and_grad(d, lam)[:2])
+    for a, b in zip(*out):
+        assert (a - b).abs().max() <= tol * b.abs().max()
