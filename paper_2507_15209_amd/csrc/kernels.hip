@@ -2429,9 +2429,8 @@ template <int N, typename T> inline int zpass_fused_threads(int nbins, int waves
   return (zpass_threads<N, VZA<T>>(nbins) + 63) / 64 * 64;
 }
 
-template <int N, typename T> inline size_t zpass_fused_lds(int nbins, int threads, size_t scratch) {
+template <int N, typename T> inline size_t zpass_fused_lds(int nbins, size_t scratch) {
   const size_t a = zpass_adjoint_lds<N, T>(nbins) + (size_t)N * sizeof(T);
-  (void)threads;
   return a > scratch ? a : scratch;
 }
 
@@ -2448,7 +2447,7 @@ hipError_t zpass_parts(const ZpassArgs& a, hipStream_t st) {
                                           : zpass_threads<N, VZA<T>>(a.nbins);
   const size_t scratch = MODE == Z_ADJOINT ? 0 : Contractor<T, MF, SPLIT, QUAD, mf_blocks(MF, QUAD, MAXNB), APART>::scratch_bytes(threads);
   size_t lds = MODE == Z_ADJOINT ? zpass_adjoint_lds<N, T>(a.nbins)
-               : MODE == Z_FUSED ? zpass_fused_lds<N, T>(a.nbins, threads, scratch)
+               : MODE == Z_FUSED ? zpass_fused_lds<N, T>(a.nbins, scratch)
                                  : zpass_nodal_lds<N, T>(a.nbins, 0);
   if (lds < scratch) lds = scratch;
   auto kern = k_zpass<N, T, MAXNB, MODE, MF, QUAD, SPLIT, APART>;
@@ -2574,8 +2573,7 @@ hipError_t launch_zpass_fused(int n, int prec, const ZpassArgs& a, hipStream_t s
 template <int N, typename T> size_t zpass_fused_lds_need_t(int nbins) {
   if (nbins > 32) return (size_t)1 << 40;
   const int threads = 512;   // the largest workgroup any waves setting gives
-  return zpass_fused_lds<N, T>(nbins, threads,
-                               nbins <= mf_bins<T>() ? Contractor<T, true, false, false, 3, false>::scratch_bytes(threads)
+  return zpass_fused_lds<N, T>(nbins, nbins <= mf_bins<T>() ? Contractor<T, true, false, false, 3, false>::scratch_bytes(threads)
                                                      : Contractor<T, false, false, false, 1, false>::scratch_bytes(threads));
 }
 

@@ -58,11 +58,10 @@ struct ZpassArgs {
   const void* fields;   // [batch][nbins][N^3], layout [x][y][qz] (adjoint passes: [item][batch][nbins][N^3])
   const void* delta;    // [batch][N^3]
   double* partials;     // forward: [batch][nwg][nbins^2]; one sweep: [item][batch][nwg][nbins^2]
-  const double* dzeta;  // backward: [batch][lmax+1][nbins^2]
   void* direct;         // backward: [batch][N^3] explicit-primary gradient accumulator
   const void* lam;      // backward: eigenvalues of the symmetrised dzeta, [lmax+1][batch][nbins] real
   const void* tw;
-  int nbins, nwg, ppw, batch, l, lmax;
+  int nbins, nwg, ppw, batch, lmax;
   bool split;           // float32 contraction with BF16-split inputs on the matrix cores
   bool pair = false;    // pair items (a launch holds one kind)
   int waves = 0;        // one-sweep z pass: waves per workgroup (0 = default)
@@ -77,14 +76,12 @@ struct GatherArgs {
   const void* fields;     // bin-interleaved fields [batch][N^3][nbins]
   const int* tcell;       // stencil records in sorted order (launch_tap_records)
   const void* twt;
-  const float* pos;       // [np_total][3]
   const float* w;         // [np_total] or NULL
   const int* perm;        // particle order (tile-sorted), [np_total]
   const long long* off;   // device [batch+1]
   const double* W;        // device [batch] weight sums
   double* partials;       // [batch][nwg][nbins^2]
   int n, nbins, nwg, batch;
-  double sc;              // N / box
   bool split;             // float32 contraction with BF16-split inputs on the matrix cores
   bool pair;              // pair item: partials [batch][nwg][2][nbins^2], of the real and the imaginary parts
   // adjoint sources from the same gather (value and gradient in one sweep) when src != NULL:

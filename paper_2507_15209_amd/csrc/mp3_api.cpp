@@ -435,12 +435,11 @@ mp3::FilterArgs filter_args(const mp3_plan_s* p, void* ws, const Layout& L, cons
 constexpr int kZpassUnits = 4096;
 
 // arguments of the adjoint z passes over a group of items
-mp3::ZpassArgs adjoint_zargs(const mp3_plan_s* p, void* ws, const Layout& L, void* F, const void* prim,
-                             const double* dzeta, void* direct, int item0, int nitems) {
+mp3::ZpassArgs adjoint_zargs(const mp3_plan_s* p, void* ws, const Layout& L, void* F, const void* prim, void* direct,
+                             int item0, int nitems) {
   mp3::ZpassArgs z{};
   z.fields = F;
   z.delta = prim;
-  z.dzeta = dzeta;
   z.lam = at(ws, L.lam);
   z.direct = direct;
   z.tw = p->tw;
@@ -872,7 +871,7 @@ int zeta_nodal(mp3_plan_t p, const void* delta, double* zeta, void* ws, const La
   double* partials = reinterpret_cast<double*>(at(ws, L.partials));
   for (int item0 = first_item(p, L), ni; (ni = group_size(p, L, item0)) > 0; item0 += ni) {
     if (int s = fields_xy(p, ws, L, F, item0, ni, st)) return s;
-    mp3::ZpassArgs z = adjoint_zargs(p, ws, L, F, delta, nullptr, nullptr, item0, ni);
+    mp3::ZpassArgs z = adjoint_zargs(p, ws, L, F, delta, nullptr, item0, ni);
     z.partials = partials;
     z.split = p->split;
     MP3_HIP(timed(p, MP3_PASS_Z_NODAL, st, [&] { return mp3::launch_zpass_nodal(p->n, p->prec, z, st); }), "z pass (contraction)");
@@ -925,7 +924,6 @@ int zeta_particle(mp3_plan_t p, const float* pos, const float* w, const int64_t*
     g.fields = Fi;
     g.tcell = tcell;
     g.twt = twt;
-    g.pos = pos;
     g.w = w;
     g.perm = perm;
     g.off = off;
@@ -936,7 +934,6 @@ int zeta_particle(mp3_plan_t p, const float* pos, const float* w, const int64_t*
     g.nwg = std::max(1, gwg / parts);
     g.pair = parts == 2;
     g.batch = p->batch;
-    g.sc = sc;
     g.split = p->split;
     MP3_HIP(timed(p, MP3_PASS_GATHER, st, [&] { return mp3::launch_gather_contract(p->prec, g, st); }), "gather");
     for (int part = 0; part < parts; ++part)
@@ -1181,7 +1178,6 @@ int value_and_grad_particle(mp3_plan_t p, const void* delta, const double* dzeta
     g.fields = Fi;
     g.tcell = tcell;
     g.twt = twt;
-    g.pos = pos;
     g.w = w;
     g.perm = perm;
     g.off = off;
@@ -1192,7 +1188,6 @@ int value_and_grad_particle(mp3_plan_t p, const void* delta, const double* dzeta
     g.nwg = std::max(1, gwg / parts);
     g.pair = parts == 2;
     g.batch = p->batch;
-    g.sc = sc;
     g.split = p->split;
     // one gather gives the contraction and the (diagonal) adjoint sources
     g.lam = lam_d_at(p, ws, L, it.l);
@@ -1360,7 +1355,7 @@ int mp3_zeta_backward(mp3_plan_t p, const void* delta, const double* dzeta, void
   MP3_HIP(mp3::launch_fill(p->prec, direct, n3 * p->batch, 0.0, st), "zero direct");
   for (int item0 = first_item(p, L), ni; (ni = group_size(p, L, item0)) > 0; item0 += ni) {
     if (int s = fields_xy(p, ws, L, F, item0, ni, st, true)) return s;
-    mp3::ZpassArgs z = adjoint_zargs(p, ws, L, F, prim, dzeta, direct, item0, ni);
+    mp3::ZpassArgs z = adjoint_zargs(p, ws, L, F, prim, direct, item0, ni);
     MP3_HIP(timed(p, MP3_PASS_Z_ADJOINT, st, [&] { return mp3::launch_zpass_adjoint(p->n, p->prec, z, st); }), "z pass (adjoint)");
     MP3_HIP(timed(p, MP3_PASS_X, st, [&] { return mp3::launch_fft_x(p->n, p->prec, +1, F, ni * p->batch * p->nbins, p->tw, p->tune[MP3_TUNE_FFT_X_PLAN], st); }), "adjoint x pass");
     mp3::FilterArgs a = filter_args(p, ws, L, F, G, item0, ni, true);
@@ -1411,7 +1406,7 @@ int mp3_zeta_value_and_grad(mp3_plan_t p, const void* delta, const double* dzeta
   MP3_HIP(mp3::launch_fill(p->prec, direct, n3 * p->batch, 0.0, st), "zero direct");
   for (int item0 = first_item(p, L), ni; (ni = group_size(p, L, item0)) > 0; item0 += ni) {
     if (int s = fields_xy(p, ws, L, F, item0, ni, st, true)) return s;
-    mp3::ZpassArgs z = adjoint_zargs(p, ws, L, F, prim, dzeta, direct, item0, ni);
+    mp3::ZpassArgs z = adjoint_zargs(p, ws, L, F, prim, direct, item0, ni);
     z.partials = partials;
     z.waves = p->tune[MP3_TUNE_FUSED_WAVES];
     MP3_HIP(timed(p, MP3_PASS_Z_FUSED, st, [&] { return mp3::launch_zpass_fused(p->n, p->prec, z, st); }),
