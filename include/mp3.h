@@ -90,9 +90,9 @@ enum mp3_summation {
  *                          orthonormal filter taps, support 3 cells): node l
  *                          carries phi(u - l + 1), phi taken as the linear
  *                          interpolant of its values at the points i / 1024
- *                          of [0, 3] from the cascade algorithm.  Nodal and
- *                          particle summation; with MP3_SUM_GRID_GAMMA
- *                          mp3_plan_create returns MP3_EUNSUPPORTED.
+ *                          of [0, 3] from the cascade algorithm.  Every
+ *                          summation; MP3_SUM_GRID_GAMMA with MP3_F32_BF16X3
+ *                          is not a plan (MP3_EUNSUPPORTED).
  * The basis sets the deposit, the interpolation at particles (the particle
  * form), the autocorrelation in the particle form's volume mean and the
  * Phi-hat factor of MP3_KF_PHI_HAT. */
@@ -209,7 +209,9 @@ int mp3_multipole_fields(mp3_plan_t plan, const void* delta, int32_t l, int32_t 
  *   unit) and np_off as for mp3_deposit (delta must be their deposit).
  *   At most 2^31 - 1 particles in total.
  *
- * Both forms sum m >= 0 only (m > 0 counted twice).  Result real and symmetric.
+ * Every form sums m >= 0 only (m > 0 counted twice).  Result real and symmetric.
+ * The real m = 0 fields of multipoles l and l + 1 (l even) may share a complex
+ * transform: the rounding of each then follows the larger of the two.
  * delta  device real [batch][N^3];
  * zeta   device float64 [batch][lmax+1][nbins][nbins], overwritten. */
 int mp3_zeta(mp3_plan_t plan, const void* delta, const float* pos, const float* w, const int64_t* np_off,

@@ -73,8 +73,9 @@ struct ContractLds {
 // Only the half band d >= 0 is applied (d = 0 at half weight): the sum over
 // the transposed pairs is T + T^T, taken once at the end.
 // Bound by instruction issue (vector ALU, LDS and matrix products share a wave's
-// issue slots); partial sums are float32 over a wave's march as the fields are,
-// float64 beyond.  Against 5^3 Gauss points per cell interpolated into LDS rows: 256^3, 20
+// issue slots); partial sums are float32, as the fields are, over a workgroup's marches
+// (two at 256^3 with 4096 workgroups), float64 beyond.  float64 with 17..32 bins spills 100 to 113
+// of its 256 registers (two bin halves of the window).  Against 5^3 Gauss points per cell interpolated into LDS rows: 256^3, 20
 // bins 160.7 -> 17.8 ms per item; 128^3, 15 bins 14.0 -> 0.85 ms.
 template <typename T, int Q, int TP, int H, int TY, int NH>
 __global__ void __launch_bounds__(TY* Q * 64)
@@ -371,7 +372,8 @@ struct AdjointLds {
 // is a row of D.  Sources are added to out [cell][nbt] (zeroed by the caller:
 // tiles share their halo), wm times the primary's share to direct.
 // The primary's filter has PT taps from tap PO on (Daubechies-4: the node itself).
-// Bound by instruction issue.  Against the shift stencil (343 or 125 shifts per cell): 128^3, 15
+// Bound by instruction issue.  The B-spline spills: float32, 16 waves of 128 registers, 26, float64 15.
+// Against the shift stencil (343 or 125 shifts per cell): 128^3, 15
 // bins float32 38 -> 3.3 ms per (l, m) with the contraction apart; 32^3, 6 bins float64 0.46 -> 0.05 ms.
 template <typename T, int Q, int TP, int H, int TY, int PT, int PO>
 __global__ void __launch_bounds__(TY* Q * 64)

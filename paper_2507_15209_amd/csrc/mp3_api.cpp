@@ -396,8 +396,11 @@ int lam_eig_all(const mp3_plan_s* p, const double* dzeta, void* ws, const Layout
   return MP3_OK;
 }
 
-// whether a call runs the paired items: not where one launch takes every (l, m) (pairs would be a second
-// one: 32^3, 15 items 330 us plain, 412 us paired), nor with a single partial sum per item (pairs leave two)
+// whether a call runs the paired items: not where one launch takes every (l, m), since pairs would be a second
+// set of launches, nor with a single partial sum per item (pairs leave two).  One sweep, plain against paired,
+// where one launch holds every item: 32^3, 15 items 0.268 / 0.333 ms, 45 items 0.496 / 0.576; 64^3, 3 items
+// 0.301 / 0.376, 45 items 2.24 / 2.13; 128^3, 12 bins, 3 items 1.41 / 1.01, 6 items 2.58 / 2.28.  So the line
+// is right up to 64^3 and leaves a gain at 128^3 with few items, which nothing takes yet.
 bool paired(const mp3_plan_s* p, const Layout& L) { return p->npairs > 0 && L.nwg >= 2 && L.group < p->work0; }
 
 int first_item(const mp3_plan_s* p, const Layout& L) { return paired(p, L) ? p->work0 : 0; }

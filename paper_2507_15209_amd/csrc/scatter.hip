@@ -63,8 +63,9 @@ struct ScatterLds {
 // s[particle][column], 16 nodes (two y, eight z at the wave's x), four
 // particles and 16 of the 2 nbc real columns per instruction.  A row block takes the
 // particles of 4 x 5 of the 11 x 11 buckets, four contiguous runs of the
-// stage, so that a sixth of the stage is multiplied rather than all of it: 64 taps of
-// which 16 x 8 / 64 = 2 products each are spent, with no divergence.
+// stage, so that a sixth of the stage is multiplied rather than all of it: a particle's four y taps
+// meet 2 or 3 row blocks, so that 4 x 2.5 x 16 / 64 = 2.5 products are spent per tap, with no divergence.
+// (float64: 112 bytes of scratch a thread.)
 // Bound by the matrix loop (16 ms of 30 at 512^3: operand addresses and matrix
 // products share the issue slots) and the staging (8 ms).  Against one thread
 // per node walking its buckets, where a wave waits for the longest: 512^3, 5e7

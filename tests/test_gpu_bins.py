@@ -124,3 +124,29 @@ def test_paired_multipoles_particle(prec, lmax, nb):
         assert_grad_close(a.cpu().numpy()[0], b, tol, "dJ/ddelta")
     for a in (dw, dw2):
         assert_grad_close(a.cpu().numpy(), wref, tol, "dJ/dw")
+
+
+def test_paired_multipoles_of_unlike_size():
+    """float32 pairs where the two fields differ most: a field smooth on three cells, bins from r = 0, l <= 6 (the
+    innermost bin's zeta falls by about a hundred from l to l + 1).  Every multipole by its own norm within the
+    float32 bar, and within four times the error of the unpaired items (plus 4 x 2^-24, one field's rounding)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2507_15209_amd as mp3
+    print("[case] pairs of unlike size", flush=True)
+    n, lmax, nb = 32, 6, 6
+    f = np.fft.fftfreq(n) * 2 * np.pi
+    k2 = f[:, None, None] ** 2 + f[None, :, None] ** 2 + f[None, None, :] ** 2
+    x = np.fft.fftn(np.random.default_rng(631).standard_normal((4, n, n, n)), axes=(1, 2, 3)) * np.exp(-4.5 * k2)
+    x = np.fft.ifftn(x, axes=(1, 2, 3)).real
+    d = torch.as_tensor(x / x.std(), dtype=torch.float32, device="cuda")
+
+    def zeta(prec, group):
+        plan = mp3.Plan(n, 320.0, lmax, np.linspace(0.0, 80.0, nb + 1), precision=prec, batch=4)
+        plan.tune_set("item_group", group)
+        return plan.zeta(d.double() if prec == "f64" else d).cpu().numpy()
+
+    ref = zeta("f64", 1024)
+    err = {g: np.sqrt(((zeta("f32", g) - ref) ** 2).sum((0, 2, 3)) / (ref ** 2).sum((0, 2, 3))) for g in (1, 1024)}
+    assert (err[1] <= TOL["f32"]).all(), err
+    assert (err[1] <= 4 * err[1024] + 4 * 2.0 ** -24).all(), err
