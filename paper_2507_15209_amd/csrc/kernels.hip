@@ -391,7 +391,9 @@ __global__ void __launch_bounds__((contig_pencils<N, T>() * Fft<N>::TPC)) k_fft_
 // transform along y
 // ---------------------------------------------------------------------------
 // PAIR: items of two real fields (m = 0 of multipoles l and l2), window K_l + i K_l2: one pair costs
-// 1.5 ms at 256^3, 20 bins against 2 x 0.79 ms here, and the passes after it run once instead of twice
+// 1.5 ms at 256^3, 20 bins against 2 x 0.79 ms here, and the passes after it run once instead of twice.
+// At 512^3 the workgroup of 1024 threads leaves 128 registers and 55 spill: 24.2 against 2 x 8.7 ms here
+// (the adjoint pass 75 spilled, 25.2 against 2 x 9.0), still less than the 58 ms of a second set of passes
 template <int N, typename T, bool PAIR>
 __global__ void __launch_bounds__((strided_threads<N, T, VB>())) k_filter_y(const c2<T>* dhat, c2<T>* fields,
                                                                          const T* jtab, int jmocks, int nq2, int nbins,
@@ -1476,14 +1478,22 @@ __global__ void k_reduce_partials(const double* partials, int nwg, int part, int
 //             over the field;
 //   one sweep both, so that value and gradient share one computation of the
 //             fields when dJ/dzeta is fixed before the forward (J linear in zeta).
+// The float64 one sweep up to 16 bins spills up to 9 of its 168 registers, as do a few of the float32 ones.
 // The forward shares this kernel because it hides latency by several small
 // workgroups per CU rather than by a pencil of prefetch registers: 256^3, 11
 // bins 0.865 -> 0.482 ms per (l, m), 20 bins 1.40 -> 0.89 ms.
 // ---------------------------------------------------------------------------
 // MODE: what the pass does with the transformed pencil
 constexpr int Z_ADJOINT = 0, Z_FUSED = 1, Z_FORWARD = 2;
+// waves per SIMD that the kernel is held to.  Three hide each other's latency; the one sweep of pair items of
+// 21..32 bins (pair3) has 48 registers of sums, and at 256 its 44 spilled cost more than the third wave
+// (256^3, 30 bins, l <= 2: 48.9 ms with three, 47.1 with two; 128^3, 24 bins, 33 spilled: 7.49 and 7.55 ms)
+template <int N, typename T> constexpr int zpass_waves(int mode, bool mf, bool pair3) {
+  if (mode == Z_ADJOINT || (!mf && sizeof(T) == 8)) return 1;
+  return mode == Z_FUSED && pair3 && N == 256 ? 2 : 3;
+}
 template <int N, typename T, int MAXNB, int MODE, bool MF, bool QUAD, bool SPLIT, bool APART>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(MODE != Z_ADJOINT && (MF || sizeof(T) == 4) ? 3 : 1)))
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(zpass_waves<N, T>(MODE, MF, APART && mf_blocks(MF, QUAD, MAXNB) == 3))))
 k_zpass(c2<T>* fields, const T* delta, const T* __restrict__ lam_d, T* direct, int nbins, int ppw,
                 const c2<T>* tw, double* partials, const ItemRec* items, int item0, int nitems, int batch, int nwg,
                 int* counter) {
