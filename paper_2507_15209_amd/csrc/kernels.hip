@@ -1882,13 +1882,15 @@ __global__ void __launch_bounds__(256) k_rotate_zeta(double* zeta, const double*
 // the cotangent's eigenbasis (V = evec[mock], of a pair item's imaginary parts evec2[mock]).  The grid-Gamma one
 // sweep contracts the fields before this, so that its value has the error of each entry's own bins and not of the
 // multipole's largest (64^3, smoothed float32 field, l = 4: the smallest entry 9e-2 off when summed over rotated
-// fields and turned back, 9e-6 so).  A pass over the fields, bound by their traffic and by one LDS read of V and
-// one of the cell per product: 128^3, 15 bins float32 0.17 ms a launch (3.0 TB/s), 3 % of that step.
+// fields and turned back, 9e-6 so).  One pass over the fields, of which a chunk at a time is in LDS.  A thread
+// takes one k of RC cells, so that an entry of V is read once for all of them (256^3, 20 bins 1.4 ms a launch,
+// 3.8 TB/s; with one cell 2.26 ms, LDS reads): 2 % of the 128^3, 15 bins step.
+constexpr int RC = 4;
 template <typename T>
 __global__ void __launch_bounds__(256) k_rotate_fields(c2<T>* f, const double* evec, const double* evec2, int nbins,
                                                        long long cells, int chunk) {
   extern __shared__ __align__(16) char smem[];
-  const int nb2 = nbins * nbins, tid = threadIdx.x;
+  const int nb2 = nbins * nbins, tid = threadIdx.x, part = chunk / RC;   // chunk a multiple of RC
   c2<T>* a = reinterpret_cast<c2<T>*>(smem);   // [chunk][nbins]
   T* v = reinterpret_cast<T*>(a + chunk * nbins);
   T* v2 = v + nb2;
@@ -1901,20 +1903,29 @@ __global__ void __launch_bounds__(256) k_rotate_fields(c2<T>* f, const double* e
   // the thread's first (cell, bin) of a chunk and its step, without a division per element
   const int c0 = tid / nbins, k0 = tid % nbins, dc = blockDim.x / nbins, dk = blockDim.x % nbins;
   for (long long p = (long long)blockIdx.x * chunk; p < cells; p += (long long)gridDim.x * chunk) {
-    const int count = (int)(cells - p < chunk ? cells - p : chunk) * nbins;
+    const int here = (int)(cells - p < chunk ? cells - p : chunk), count = here * nbins;
     c2<T>* g = fm + p * nbins;
     __syncthreads();   // the chunk before is written
+#pragma unroll 4
     for (int t = tid; t < count; t += blockDim.x) a[t] = g[t];
     __syncthreads();
     int c = c0, k = k0;
-    for (int t = tid; t < count; t += blockDim.x) {
-      const c2<T>* row = a + c * nbins;
-      c2<T> s = mk<T>(0, 0);
+    while (c < part) {   // cells c, c + part, ..
+      c2<T> s[RC];
+#pragma unroll
+      for (int i = 0; i < RC; ++i) s[i] = mk<T>(0, 0);
       for (int b = 0; b < nbins; ++b) {
-        s.x += v[b * nbins + k] * row[b].x;
-        s.y += v2[b * nbins + k] * row[b].y;
+        const T w = v[b * nbins + k], w2 = v2[b * nbins + k];
+#pragma unroll
+        for (int i = 0; i < RC; ++i) {
+          const c2<T> x = a[(c + i * part) * nbins + b];   // beyond the last cell: unused
+          s[i].x += w * x.x;
+          s[i].y += w2 * x.y;
+        }
       }
-      g[t] = s;
+#pragma unroll
+      for (int i = 0; i < RC; ++i)
+        if (c + i * part < here) g[(c + i * part) * nbins + k] = s[i];
       next_element(c, k, dc, dk, nbins);
     }
   }
@@ -2669,8 +2680,8 @@ hipError_t launch_rotate_jtab(int prec, const void* jtab, void* jrot, const doub
 template <typename T>
 hipError_t rotate_fields_t(void* fields, const double* evec, const double* evec2, int nbins, long long cells, int batch,
                            hipStream_t st) {
-  // 32 KB of cells at a time (at least one thread per element), with both tables at most 96 KB of LDS
-  const int chunk = (int)(32768 / (nbins * sizeof(CT<T>)));
+  // 16 KB of cells at a time (32 KB: 256^3, 20 bins 0.5 ms a launch longer), with both tables at most 80 KB of LDS
+  const int chunk = (int)(16384 / (nbins * sizeof(CT<T>))) / RC * RC;
   const size_t lds = (size_t)chunk * nbins * sizeof(CT<T>) + (size_t)2 * nbins * nbins * sizeof(T);
   hipError_t e = allow_lds(k_rotate_fields<T>, lds);
   if (e != hipSuccess) return e;
