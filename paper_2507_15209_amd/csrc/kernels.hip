@@ -1883,8 +1883,8 @@ __global__ void __launch_bounds__(256) k_rotate_zeta(double* zeta, const double*
 // sweep contracts the fields before this, so that its value has the error of each entry's own bins and not of the
 // multipole's largest (64^3, smoothed float32 field, l = 4: the smallest entry 9e-2 off when summed over rotated
 // fields and turned back, 9e-6 so).  One pass over the fields, of which a chunk at a time is in LDS.  A thread
-// takes one k of RC cells, so that an entry of V is read once for all of them (256^3, 20 bins 1.4 ms a launch,
-// 3.8 TB/s; with one cell 2.26 ms, LDS reads): 2 % of the 128^3, 15 bins step.
+// takes one k of RC cells, so that an entry of V is read once for all of them (256^3, 20 bins 1.07 ms a launch,
+// 5.0 TB/s; with one cell 2.26 ms, LDS reads): 2 % of the 128^3, 15 bins step.
 constexpr int RC = 4;
 template <typename T>
 __global__ void __launch_bounds__(256) k_rotate_fields(c2<T>* f, const double* evec, const double* evec2, int nbins,
