@@ -78,15 +78,14 @@ def test_non_finite_cotangent(prec, value, form):
     assert (z - zref).abs().max() <= TOL[prec] * zref.abs().max()
 
 
-@pytest.mark.parametrize("basis", ["b3", "d4"])
-@pytest.mark.parametrize("prec,nb", [("f64", 3), ("f64", 20), ("f32", 3), ("f32", 20), ("bf16x3", 20)])
+@pytest.mark.parametrize("basis,prec,nb", [("b3", "f64", 3), ("b3", "f64", 20), ("b3", "f32", 3), ("b3", "f32", 20),
+                                           ("b3", "bf16x3", 20), ("d4", "f64", 3), ("d4", "f64", 20), ("d4", "f32", 3),
+                                           ("d4", "f32", 20)])
 def test_gamma_task_loop(basis, prec, nb):
     """The grid-Gamma contraction with several tasks to a workgroup (contract_wgs 64: 8 or 4 tasks each at 32^3)
     against one task each, and the gradient beside it, which no knob cuts."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
-    if prec == "bf16x3" and basis == "d4":
-        pytest.skip("not a plan")
     import paper_2507_15209_amd as mp3
     print("[case] gamma task loop", basis, prec, nb, flush=True)
     n, lmax = 32, 1
